@@ -10,21 +10,23 @@
 // filling 12870 x 12870 = 1.66e8 amplitudes, 2.6 GB, against 2^32 and
 // 64 GiB for the full vector).
 //
-// A hopping term of spin s changes only the spin-s pattern, so in the layout
-// whose rows are indexed by the other spin (layout A: rows r_dn, columns r_up;
-// layout B: the transpose) every spin-s gate acts inside rows, with the same
-// pairing of columns in every row.  A row pass holds one row per workgroup
-// in registers and applies a run of gates to it; a gate's partner amplitudes
-// come through LDS, each active element writing its value to its pair slot
-// and reading the partner's from the neighbouring slot (pair slots and the
-// Jordan-Wigner sign precomputed per gate and rank on the host).  Between
-// runs of the two spins the state is transposed (A <-> B).  The diagonal
-// phase acts element-wise in either layout.
+// A hopping term of spin s changes only the spin-s pattern, so it acts inside
+// the rows of the matrix (s = up) or inside its columns (s = down), with the
+// same pairing of elements in every row.  A row pass holds rows in a
+// workgroup and applies a run of gates to them; the hops of a layer go in
+// phases (sector_plan.hpp): a thread takes an orbit of 6, 4 and 4 elements
+// that all hops of a four-site cluster keep, so that a phase of three to four
+// hops costs one exchange through LDS.  The diagonal acts element-wise.
 //
-// Schedule of L layers: [D_0, up_0] (A), [dn_0, D_1, dn_1] (B),
-// [up_1, D_2, up_2] (A), ...: within a layer the up and down hops commute,
-// so each row pass carries the second half of one layer and the first half
-// of the next, L + 1 row passes and L transposes per sweep.
+// Schedule of L layers: [D_0, up_0], [dn_0, D_1, dn_1], [up_1, D_2, up_2],
+// ...: within a layer the up and down hops commute, so each row pass carries
+// the second half of one layer and the first half of the next, L + 1 row
+// passes per sweep.
+//
+// Rows of up to kShortRow elements live in LDS, 2^lr of them per workgroup;
+// down passes read the matrix by columns.  Longer rows (16 sites) live in
+// registers, one per workgroup, and the state is transposed between the
+// passes of the two spins (layout A: rows r_dn; layout B: the transpose).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,6 +44,7 @@
 #include "../../include/hubbard.h"
 #include "hubvqe.hpp"
 #include "phase.hpp"
+#include "sector_plan.hpp"
 
 namespace hv {
 
@@ -59,94 +62,55 @@ size_t lanczos_partial_bytes();
 
 namespace sec {
 
-constexpr int kT = 1024;                  // threads of a row workgroup
-constexpr int kWaves = kT / 64;
 constexpr int kMaxRed = 16;               // reduction slots of one row pass
-constexpr int kGrid = 1024;               // at most this many row workgroups
-constexpr int kMaxRows = 13 * kT;         // longest row: C(16, 8) = 12870
-constexpr int kZero = 16;                 // zeroed LDS slots (one per bank group) read by inactive elements
+constexpr int kGrid = 1024;               // at most this many workgroups write partials
 
-// Register tile of a row of n elements over kT threads: rpt_of(n) elements
-// per thread (element t + j kT in thread t).  A gate's code table holds
-// rp_of(rpt) >= rpt codes per thread in chunks of cw_of(rpt) consecutive
-// codes: element j of thread t is entry code_index(rpt, t, j), so that a
-// thread reads a chunk with one LDS load and a wave's loads are contiguous.
-__host__ __device__ constexpr int rpt_of(int n)
-{
-    return n <= kT ? 1 : n <= 2 * kT ? 2 : n <= 4 * kT ? 4 : n <= 8 * kT ? 8 : 13;
-}
-__host__ __device__ constexpr int rp_of(int rpt) { return rpt == 13 ? 16 : (rpt < 2 ? 2 : rpt); }
-__host__ __device__ constexpr int cw_of(int rpt) { return rp_of(rpt) < 8 ? rp_of(rpt) : 8; }
-__host__ __device__ constexpr int code_index(int rpt, int t, int j)
-{
-    return ((j / cw_of(rpt)) * kT + t) * cw_of(rpt) + j % cw_of(rpt);
-}
+enum { S_FWD = 0, S_REV = 1 };
+enum { SF_NO_STORE = 1, SF_START = 2 };
+// What a pass of H does with its part phi of H psi: out <- phi, out <- out +
+// phi, or lambda = out + phi and then psi <- lambda + i psi, out <- lambda -
+// i psi (the reverse sweep's two vectors).
+enum { HO_SET = 0, HO_ADD = 1, HO_MIX = 2 };
 
-enum { S_FWD = 0, S_REV = 1, S_HAM = 2 };
-enum { SOP_HOP = 0, SOP_DIAG = 1 };
-enum { SF_NO_STORE = 1, SF_NEGATE = 2 };
+typedef __attribute__((address_space(1))) double2 gc128;
+typedef const __attribute__((address_space(1))) uint16_t gu16;
+typedef const __attribute__((address_space(1))) uint32_t gu32;
+typedef const __attribute__((address_space(1))) uint4 gu128;
+typedef const __attribute__((address_space(1))) double gf64;
+// wave-uniform and read-only for the launch: scalar loads
+typedef const __attribute__((address_space(4))) SecPhase kPhase;
+typedef const __attribute__((address_space(4))) SecGate kGate;
+typedef const __attribute__((address_space(4))) double kf64;
+typedef const __attribute__((address_space(4))) uint32_t ku32;
 
-// One operation of a row pass (32 bytes).  HOP: the gate exp(-i th t h) of
-// one bond and spin (h = a+_i a_j + h.c. on that spin's sites); DIAG: the
-// layer's diagonal exp(-i th D).
-struct SecOp {
-    int32_t kind;
-    int32_t param;    // theta index
-    int32_t tab;      // HOP: offset of its code table (kT rp_of(rpt) entries)
-    int32_t red;      // REV: reduction slot of the parameter within the pass
-    double t;         // HOP: t_b
-    int32_t nxt[2];   // the HOP op that follows this one in the pass's list in
-                      // forward [0] and reverse [1] execution order, wrapping
-                      // around (its code table is fetched while this op runs)
-};
-
-// Device constants of a model's sector.
-struct SecModel {
-    int32_t ns, nvb;
-    int32_t n[2];              // patterns of each spin
+// One row pass: the rows' tables (of the spin whose patterns index the row),
+// the other spin's, and which layers' hops and diagonal it applies.
+struct RowsArgs {
+    const SecPhase *phases;
+    const SecGate *gates;
+    const Rec *recs;             // short rows
+    const uint4 *lcode;          // long rows: slots and signs, two uint4 per thread and phase
+    const uint4 *lpat;           //   patterns in phase 0's layout
+    const double *lbase;         //   base values in phase 0's layout
+    const uint16_t *colslot;     // slot of each row element
+    const uint16_t *patslot;     // short rows: pattern and base value of each slot
+    const double *baseslot;
+    const uint32_t *rpat;        // the other spin: pattern, base value and
+    const double *rbase;         //   coupling weights (16 per rank) of each row
+    const double *wrow;
+    const double *theta;
     double U;
-    const uint32_t *pat[2];    // site pattern of each rank
-    const double *base[2];     // sum_i eps_i p_i + sum_b V_b p_i p_j of each rank
-    const uint16_t *code;      // per gate: LDS slot | sign << 15 (a zero slot: not active)
-                               // of every column, at code_index (kT rp_of(rpt) entries)
-    int32_t vi[kMaxBonds], vj[kMaxBonds];
-    double vV[kMaxBonds];
+    int n, n_rows, nslots, lr;
+    int n_phases, per;
+    int l_pre, l_diag, l_post;   // layer of the hops before the diagonal, of the
+                                 // diagonal and of the hops after it (-1: none)
+    int64_t rs, cs;              // element (row, col) at row rs + col cs
+    double2 *v[2];
+    double *partial;
+    int row0[2];                 // first partial row of each vector
+    int n_red, pstride, flags;
+    int b0_row, b0_col;
 };
-
-// D of the basis state with row pattern rp and column pattern cp:
-// U #(doubly occupied) + base(rp) + base(cp) + sum_b V_b (rp_i cp_j + cp_i rp_j).
-template <typename MT>
-__device__ __forceinline__ double diag_d(const MT *M, uint32_t rp, double rb, uint32_t cp,
-                                         double cb)
-{
-    double d = M->U * (double)__popc(rp & cp) + rb + cb;
-    for (int v = 0; v < M->nvb; ++v) {
-        const int i = M->vi[v], j = M->vj[v];
-        const uint32_t x = (((rp >> i) & (cp >> j)) | ((cp >> i) & (rp >> j))) & 1u;
-        const uint32_t y = ((rp >> i) & (cp >> j) & (cp >> i) & (rp >> j)) & 1u;
-        d += M->vV[v] * (double)(x + y);
-    }
-    return d;
-}
-
-// The value is final here: the work that produced it stays before the next
-// workgroup barrier instead of being sunk past it (which would keep the
-// inputs, a partner value each, live across the barrier).
-__device__ __forceinline__ void pin(double2 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
-__device__ __forceinline__ void pin(double &v) { asm volatile("" : "+v"(v)); }
-
-// x <- x m + q, and acc <- acc + m q, computed in the registers of x (acc):
-// the register tile is updated in place.  (Left to itself the allocator
-// writes an op's results to fresh registers and copies the whole tile back
-// at the end of the op: twice the tile's registers and a copy per element.)
-__device__ __forceinline__ void fma_ip(double &x, double m, double q)
-{
-    asm("v_fma_f64 %0, %0, %1, %2" : "+v"(x) : "v"(m), "v"(q));
-}
-__device__ __forceinline__ void fmac_ip(double &acc, double m, double q)
-{
-    asm("v_fma_f64 %0, %1, %2, %0" : "+v"(acc) : "v"(m), "v"(q));
-}
 
 // x from another lane of the same 16-lane row (DPP control CTRL), both
 // 32-bit halves.
@@ -178,451 +142,961 @@ __device__ __forceinline__ double wave_sum(double x)
     return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
 }
 
-// A thread's gate codes, two 16-bit codes per register (LDS slot | sign <<
-// 15; an element the gate leaves alone has a zero slot, at or above the
-// first zero slot nz, with sign 0).
-template <int RPT>
-struct Codes {
-    uint32_t w[rp_of(RPT) / 2];
-    __device__ __forceinline__ uint32_t get(int j) const { return (w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu; }
+// ----------------------------------------------------------------- gates --
+
+// x with the sign bits of mask (0 or 0x80000000) flipped.
+__device__ __forceinline__ double xor_sign(double x, uint32_t mask)
+{
+    return __hiloint2double(__double2hiint(x) ^ (int)mask, __double2loint(x));
+}
+
+// x <- x m + q computed in the registers of x: the orbit is updated in place.
+// (Left to itself the allocator writes a hop's results to fresh registers and
+// copies the orbits back where the six cases of a hop meet: twice the
+// registers, and hundreds of bytes per lane in scratch memory.)
+__device__ __forceinline__ void fma_ip(double &x, double m, double q)
+{
+    asm("v_fma_f64 %0, %0, %1, %2" : "+v"(x) : "v"(m), "v"(q));
+}
+
+// (x, y) <- (c x + i s y, i s x + c y)
+__device__ __forceinline__ void rotate(double2 &x, double2 &y, double c, double s)
+{
+    const double p = -s * y.y, q = s * y.x, u = -s * x.y, v = s * x.x;
+    fma_ip(x.x, c, p);
+    fma_ip(x.y, c, q);
+    fma_ip(y.x, c, u);
+    fma_ip(y.y, c, v);
+}
+
+__device__ __forceinline__ double re_dot(double2 a, double2 b) { return fma(a.x, b.x, a.y * b.y); }
+
+// Position of the two-electron pattern {a, b} in an orbit of six.
+__host__ __device__ constexpr int duo(int a, int b)
+{
+    return a > b ? duo(b, a) : (a == 0 ? b - 1 : a + b);   // 01 02 03 12 13 23
+}
+
+// The hop at position Q of a phase (sites A, B) on a thread's orbits: x[0..5]
+// two electrons, x[6..9] one (by its site), x[10..13] three (by the empty
+// site).  The orbits' sign bits are those of Rec.
+//   REV: w <- w + the sum over the pairs of sign Re(conj(x_a) x_b), before the rotation
+template <bool REV, int Q>
+__device__ __forceinline__ void hop2(double2 (&x)[kOrbitElems], double2 cs, uint32_t f, double &w)
+{
+    constexpr int A = kPosA[Q], B = kPosB[Q];
+    constexpr int E0 = A != 0 && B != 0 ? 0 : (A != 1 && B != 1 ? 1 : 2);
+    constexpr int E1 = 6 - A - B - E0;   // the spectators, E0 < E1
+    constexpr int a0 = duo(A, E0), b0 = duo(B, E0), a1 = duo(A, E1), b1 = duo(B, E1);
+    const uint32_t m0 = (f << (2 * Q)) & 0x80000000u, m1 = (f << (2 * Q + 1)) & 0x80000000u;
+    if constexpr (REV)
+        w += xor_sign(re_dot(x[a0], x[b0]), m0) + xor_sign(re_dot(x[a1], x[b1]), m1);
+    rotate(x[a0], x[b0], cs.x, xor_sign(cs.y, m0));
+    rotate(x[a1], x[b1], cs.x, xor_sign(cs.y, m1));
+}
+
+template <bool REV, int Q>
+__device__ __forceinline__ void hop13(double2 (&x)[kOrbitElems], double2 cs, uint32_t f1,
+                                      uint32_t f3, double &w)
+{
+    constexpr int A = kPosA[Q], B = kPosB[Q];
+    const uint32_t m1 = (f1 << (8 + Q)) & 0x80000000u, m3 = (f3 << (12 + Q)) & 0x80000000u;
+    if constexpr (REV)
+        w += xor_sign(re_dot(x[6 + A], x[6 + B]), m1) +
+             xor_sign(re_dot(x[10 + A], x[10 + B]), m3);
+    rotate(x[6 + A], x[6 + B], cs.x, xor_sign(cs.y, m1));
+    rotate(x[10 + A], x[10 + B], cs.x, xor_sign(cs.y, m3));
+}
+
+// LDS of a row pass.
+struct RowLds {
+    uint32_t vec, ang, dtab, nib, rowp, rowb, acc, total;
+};
+__host__ __device__ inline RowLds row_lds(uint32_t vec_bytes, int rows, int n_phases, int n_red,
+                                          int threads, bool gen)
+{
+    RowLds L;
+    uint32_t at = vec_bytes;
+    L.vec = 0;
+    L.ang = at;
+    at += 2u * (uint32_t)(n_phases * kPositions) * 16u;
+    L.dtab = at;   // U-only: phases by the number of doubly occupied sites; else unit phases
+    at += (gen ? 1u << kCisBits : (uint32_t)kDiagTab) * 16u;
+    L.nib = at;    // per row: the coupling weights' sums over the pattern's nibbles
+    at += gen ? (uint32_t)rows * 64u * 8u : 0u;
+    L.rowb = at;
+    at += (uint32_t)rows * 8u;
+    L.rowp = at;
+    at += ((uint32_t)rows * 4u + 15u) & ~15u;
+    L.acc = at;
+    at += (uint32_t)n_red * ((uint32_t)threads / 4u) * 8u;
+    L.total = at;
+    return L;
+}
+__host__ __device__ inline uint32_t short_vec_bytes(int nslots, int lr)
+{
+    return ((uint32_t)(nslots + 1) << lr) * 16u;
+}
+__host__ __device__ inline uint32_t long_vec_bytes(int nslots)
+{
+    return (uint32_t)(nslots + kLongDummy) * 8u;
+}
+
+// Work common to both row kernels.  A pass's steps: the phases of the hops
+// before the diagonal, then those of the hops after it.
+template <int MODE, bool GEN>
+struct RowPassCtx {
+    static constexpr bool REV = MODE == S_REV;
+    const RowsArgs &A;
+    double2 *ang, *dtab;
+    double *acc;
+    int tid, T, dslot, post_slot;
+
+    __device__ RowPassCtx(const RowsArgs &a, char *smem, const RowLds &L)
+        : A(a), ang((double2 *)(smem + L.ang)), dtab((double2 *)(smem + L.dtab)),
+          acc((double *)(smem + L.acc)), tid(threadIdx.x), T(blockDim.x)
+    {
+        // reduction slots: the groups of the hops before, the diagonal, the
+        // groups of the hops after it
+        dslot = A.l_pre >= 0 ? A.per - 1 : 0;
+        post_slot = dslot + (A.l_diag >= 0 ? 1 : 0);
+    }
+    // rotation angles, phase tables, zeroed reduction rows (no barrier)
+    __device__ void prologue()
+    {
+        const int n_gates = A.n_phases * kPositions;
+        for (int i = tid; i < 2 * n_gates; i += T) {
+            const int run = i >= n_gates ? 1 : 0, layer = run ? A.l_post : A.l_pre;
+            if (layer < 0)
+                continue;
+            const SecGate &g = A.gates[i - run * n_gates];
+            double s, c;
+            sincos(A.theta[layer * A.per + g.slot] * g.t, &s, &c);
+            ang[i] = make_double2(c, REV ? -s : s);
+        }
+        if (A.l_diag >= 0) {
+            if constexpr (GEN) {
+                build_cis(dtab, tid, T);
+            } else {
+                const double th = A.theta[A.l_diag * A.per];
+                for (int k = tid; k < kDiagTab; k += T) {
+                    double s, c;
+                    sincos(th * (A.U * (double)k), &s, &c);
+                    dtab[k] = make_double2(c, REV ? s : -s);
+                }
+            }
+        }
+        for (int i = tid; i < A.n_red * (T / 4); i += T)
+            acc[i] = 0.0;
+    }
+    // a thread's sum of one reduction slot's terms into that slot: four lanes
+    // are added in registers, one of them adds to its LDS entry
+    __device__ __forceinline__ void flush(int slot, double &racc)
+    {
+        double x = racc;
+        x += row_dpp<0xB1>(x);
+        x += row_dpp<0x4E>(x);
+        if ((tid & 3) == 0)
+            acc[slot * (T / 4) + (tid >> 2)] += x;
+        racc = 0.0;
+    }
+    // positions Q, Q + 1 (one matching) of phase ph on a thread's orbits
+    template <int Q>
+    __device__ __forceinline__ void matching(double2 (&x)[kOrbitElems], int run, int ph,
+                                             uint32_t f2, uint32_t f1, uint32_t f3, bool w2,
+                                             bool w13, double &racc)
+    {
+        const double2 *an = ang + (run * A.n_phases + ph) * kPositions + Q;
+        const double2 c0 = an[0], c1 = an[1];
+        double p0 = 0.0, p1 = 0.0;
+        if (w2) {
+            hop2<REV, Q>(x, c0, f2, p0);
+            hop2<REV, Q + 1>(x, c1, f2, p1);
+        }
+        if (w13) {
+            hop13<REV, Q>(x, c0, f1, f3, p0);
+            hop13<REV, Q + 1>(x, c1, f1, f3, p1);
+        }
+        if constexpr (REV) {
+            // <chi|G|chi> counts every pair twice; the position executed
+            // next decides whether the sum goes on
+            const kGate *g = (const kGate *)A.gates + ph * kPositions + Q;
+            const int base = (run ? post_slot : 0) - 1;
+            racc = fma(-2.0 * g[1].t, p1, racc);
+            if (g[0].slot != g[1].slot)
+                flush(base + g[1].slot, racc);
+            racc = fma(-2.0 * g[0].t, p0, racc);
+            if (Q == 0 || g[-1].slot != g[0].slot)
+                flush(base + g[0].slot, racc);
+        }
+    }
+    // the phase's hops on a thread's orbits
+    __device__ __forceinline__ void gates(double2 (&x)[kOrbitElems], int run, int ph, uint32_t f2,
+                                          uint32_t f1, uint32_t f3, bool w2, bool w13)
+    {
+        double racc = 0.0;
+        if constexpr (!REV) {
+            matching<0>(x, run, ph, f2, f1, f3, w2, w13, racc);
+            matching<2>(x, run, ph, f2, f1, f3, w2, w13, racc);
+        } else {
+            matching<2>(x, run, ph, f2, f1, f3, w2, w13, racc);
+            matching<0>(x, run, ph, f2, f1, f3, w2, w13, racc);
+        }
+    }
+    // the workgroup's partial sums (after a barrier)
+    __device__ void finish(int vsel, bool negate)
+    {
+        const int lane = tid & 63, wave = tid >> 6, R = T / 4;
+        for (int r = wave; r < A.n_red; r += T >> 6) {
+            double s = 0.0;
+            for (int i = lane; i < R; i += 64)
+                s += acc[r * R + i];
+            s = wave_sum(s);
+            if (lane == 0)
+                A.partial[(size_t)(A.row0[vsel] + r) * A.pstride + blockIdx.x] = negate ? -s : s;
+        }
+    }
 };
 
-typedef const __attribute__((address_space(1))) uint32_t gu32;
-typedef const __attribute__((address_space(1))) uint16_t gu16;
-typedef const __attribute__((address_space(1))) double gf64;
-typedef __attribute__((address_space(1))) double2 gc128;
-// The op list, its angles and the model constants are read-only for the
-// whole launch: constant address space, so that their wave-uniform loads are
-// scalar loads (as generic pointers they became vector loads with a wait in
-// front of every op).
-typedef const __attribute__((address_space(4))) SecOp kSecOp;
-typedef const __attribute__((address_space(4))) SecModel kSecModel;
-typedef const __attribute__((address_space(4))) double2 kc128;
-typedef const __attribute__((address_space(4))) uint32_t ku32;
-typedef const __attribute__((address_space(4))) double kf64;
-
-// The gate's codes of thread t, from the LDS copy of its table: one load
-// per chunk (codes past the row end name zero slots in the table).
-template <int RPT>
-__device__ __forceinline__ Codes<RPT> load_codes(const uint16_t *cb, uint32_t t)
+// D's value of an element from its row's nibble sums: the row's and the
+// pattern's own terms and the coupling sum_j p_j w_j.
+__device__ __forceinline__ double diag_gen(double rb, double cb, const double *nib, uint32_t cp)
 {
-    constexpr int CW = cw_of(RPT), NCH = rp_of(RPT) / CW;
-    Codes<RPT> c;
-#pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-        const uint16_t *q = cb + ((size_t)ch * kT + t) * CW;
-        if constexpr (CW == 8) {
-            const uint4 v = *(const uint4 *)q;
-            c.w[ch * 4 + 0] = v.x;
-            c.w[ch * 4 + 1] = v.y;
-            c.w[ch * 4 + 2] = v.z;
-            c.w[ch * 4 + 3] = v.w;
-        } else if constexpr (CW == 4) {
-            const uint2 v = *(const uint2 *)q;
-            c.w[ch * 2 + 0] = v.x;
-            c.w[ch * 2 + 1] = v.y;
-        } else {
-            c.w[ch] = *(const uint32_t *)q;
-        }
-    }
-    return c;
+    return (rb + cb) + ((nib[cp & 15u] + nib[16 + ((cp >> 4) & 15u)]) +
+                        (nib[32 + ((cp >> 8) & 15u)] + nib[48 + (cp >> 12)]));
 }
 
-// The gate's codes of thread t straight from its table in global memory
-// (the same chunks as load_codes: a wave's loads are contiguous).
-template <int RPT>
-__device__ __forceinline__ Codes<RPT> load_codes_g(const gu16 *__restrict__ src, uint32_t t)
+__device__ __forceinline__ double nibble_sum(const gf64 *w, int e)
 {
-    constexpr int CW = cw_of(RPT), NCH = rp_of(RPT) / CW;
-    Codes<RPT> c;
+    const gf64 *q = w + (e >> 4) * 4;
+    double s = 0.0;
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-        // CW / 2 adjacent dwords: one vector load
-        const gu32 *q = (const gu32 *)(src + ((size_t)ch * kT + t) * CW);
-#pragma unroll
-        for (int k = 0; k < (CW + 1) / 2; ++k)
-            c.w[ch * ((CW + 1) / 2) + k] = q[k];
-    }
-    return c;
+    for (int b = 0; b < 4; ++b)
+        s += (e >> b) & 1 ? q[b] : 0.0;
+    return s;
 }
 
-// Asynchronous copy of a gate's code table (kT rp_of(RPT) 16-bit entries)
-// from global memory into LDS, a dword per lane and round, without
-// registers; complete for the issuing wave after its vmcnt wait.
-template <int TT, int RPT>
-__device__ __forceinline__ void fetch_codes(const gu16 *__restrict__ src, uint16_t *cb, int tid)
+// The diagonal on one element: exp(-i th D) forward, the bracket D |a|^2 and
+// exp(+i th D) in reverse.
+template <bool REV, bool GEN>
+__device__ __forceinline__ void diag_el(double2 &a, double d, double2 ph, double th,
+                                        const double2 *cis, double &racc)
 {
-    constexpr int ROUNDS = kT * rp_of(RPT) / 2 / TT;
-    // the wave's LDS base is uniform (a scalar register, no per-round
-    // readfirstlane); the lane's source offset is 32-bit (scalar base +
-    // vector offset addressing)
-    const uint32_t wbase = __builtin_amdgcn_readfirstlane((uint32_t)(tid & ~63));
-    const gu32 *__restrict__ s32 = (const gu32 *)src;
-#pragma unroll
-    for (int k = 0; k < ROUNDS; ++k) {
-        const uint32_t d0 = (uint32_t)k * TT;
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void *)(s32 + (d0 + (uint32_t)tid)),
-            (__attribute__((address_space(3))) void *)(cb + 2 * (d0 + wbase)), 4, 0, 0);
-    }
+    if constexpr (GEN)
+        ph = cis_neg(REV ? -th * d : th * d, cis);
+    if constexpr (REV)
+        racc = fma(d, fma(a.x, a.x, a.y * a.y), racc);
+    a = make_double2(fma(ph.x, a.x, -ph.y * a.y), fma(ph.x, a.y, ph.y * a.x));
 }
 
-// One gate's exchange of vector x through the pair slots: every active
-// element publishes its value to its slot, then every element calls use(j,
-// partner, active, sign bit) with the partner read from its slot XOR 1 (the
-// Jordan-Wigner sign (-1)^bit).  An inactive element's code names one of
-// the kZero zero slots, so its "partner" is zero and every term with it
-// vanishes whatever the sign: the reads and updates are branch-free and
-// take no select.  The zero slot of the inactive lanes of a group of 16
-// lanes is chosen by the host in a bank group that none of the group's
-// active reads uses (the lanes of a 16-byte LDS access are served in such
-// groups; all of the group's inactive lanes read the same slot, a
-// broadcast).  (Inactive elements writing to zero slots too, to make the
-// writes branch-free as well, cost 4 % of an evaluation in LDS traffic.)
-// The codes are in registers: they are made opaque before each half, so that
-// the decoded slot addresses are not kept across the barrier; mid() (the
-// next gate's table fetch into the LDS the codes came from) is issued after
-// the reads, before the closing barrier (every thread holds its codes since
-// the publishing barrier; issued right after that barrier, the copies
-// overlapped the reads and the gate took longer).
-template <int RPT, int INF, typename G, typename F>
-__device__ __forceinline__ void exchange(const double2 (&x)[RPT], Codes<RPT> cd, double2 *xch,
-                                         uint32_t nz, G &&mid, F &&use)
+// Workgroup i of a launch works on row group group_of(i): workgroups go to
+// the eight XCDs in turn, and each XCD takes a contiguous range of groups, so
+// that the lines shared by neighbouring groups of a column pass meet in one L2.
+__device__ __forceinline__ int group_of(int i, int n)
 {
-#pragma unroll
-    for (int k = 0; k < rp_of(RPT) / 2; ++k)
-        asm volatile("" : "+v"(cd.w[k]));
-#pragma unroll
-    for (int j = 0; j < RPT; ++j) {
-        const uint32_t sl = cd.get(j) & 0x7FFFu;
-        if (sl < nz)
-            xch[sl] = x[j];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < rp_of(RPT) / 2; ++k)
-        asm volatile("" : "+v"(cd.w[k]));
-    // INF partner values in flight per thread: element j + INF - 1's read is
-    // issued before element j is updated (the other waves hide the rest of
-    // the LDS latency; the register tile keeps its registers)
-    auto partner = [&](int j) __attribute__((always_inline)) {
-        return xch[(cd.get(j) & 0x7FFFu) ^ 1u];
-    };
-    double2 pq[INF];
-#pragma unroll
-    for (int k = 0; k + 1 < INF && k < RPT; ++k)
-        pq[k] = partner(k);
-#pragma unroll
-    for (int j = 0; j < RPT; ++j) {
-        const uint32_t c = cd.get(j);
-        if (j + INF - 1 < RPT)
-            pq[(j + INF - 1) % INF] = partner(j + INF - 1);
-        if constexpr (INF > 1)
-            __builtin_amdgcn_sched_barrier(0);
-        use(j, pq[j % INF], ((c & 0x7FFFu) ^ 1u) < nz, (c >> 15) & 1u);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    mid();
-    __builtin_amdgcn_s_waitcnt(0);   // this wave's part of mid()'s copies has landed
-    __syncthreads();
+    const int chunk = (n + 7) / 8;
+    const int g = (i & 7) * chunk + (i >> 3);
+    return (i >> 3) < chunk && g < n ? g : -1;
 }
 
-// Row pass.  Each workgroup takes rows blockIdx.x, blockIdx.x + gridDim.x, ...
-// of the layout whose columns are indexed by spin `col`; thread t holds the
-// row's elements t + j TT, j < RPT (TT = kT, the layout of the code tables).
-//   S_FWD: v0 <- ops applied in order.
-//   S_REV: v0 = chi <- ops un-applied in reverse order; the expectation
-//          <chi| G |chi> of every op before its un-application goes to its
-//          reduction slot (negated with SF_NEGATE).  The adjoint bracket
-//          Im <lambda|G|psi> is (<chi2|G|chi2> - <chi1|G|chi1>) / 4 with
-//          chi1, chi2 = lambda +- i psi, both of which evolve by the same
-//          un-applied gates: two one-vector sweeps instead of one sweep
-//          holding both psi and lambda.
-//   S_HAM: v1 <- sum of the ops' generators applied to v0 (D if a DIAG op
-//          is present), slot 0 <- Re <v0|v1>.
-// Reductions: per-wave sums in LDS, then per workgroup one partial per slot
-// at partial[(row0 + slot) * pstride + blockIdx.x] (fixed order).
-// GEN: the diagonal has eps or V terms (D from the pattern tables, its phase
-// by cis_neg); else D = U #(doubly occupied) and its phase comes from the
-// op's table dph[op.tab][k] = exp(-i th U k), copied into LDS at the start.
-template <int MODE, int TT, int RPT, bool GEN>
-__global__ void __launch_bounds__(TT)
-k_sec_rows(const SecOp *__restrict__ ops, int n_ops, int col, int n_red,
-           const double2 *__restrict__ ang, const double2 *__restrict__ dph,
-           const SecModel *__restrict__ M, double2 *__restrict__ v0, double2 *__restrict__ v1,
-           double *__restrict__ partial, int row0, int pstride, int flags, int xch_elems)
+// ------------------------------------------------------------ short rows --
+// 2^lr rows of up to kShortRow elements per workgroup, in LDS: element (slot,
+// row) at slot 2^lr + row, lanes with the row in their low bits.  Each phase
+// reads a thread's orbits, rotates them in registers and writes them back to
+// the same slots: one barrier per phase.  The slots' bank classes keep the
+// lanes of an LDS access apart (sector_plan.cpp).
+// Bound by latency and VALU, not by HBM (24-qubit ladder, 924 x 924: 13.6 MB
+// per vector).  One exchange per phase instead of one per hop, several rows
+// per workgroup and no transposes took its energy+gradient evaluation with
+// the general diagonal from 4.19 to 1.03 ms, and a 20-qubit chain's from 0.554
+// to 0.283 ms.
+//   S_FWD: v[0] <- ops applied.  SF_START: the input is |b0>, not read; the
+//          rows without it are zero.
+//   S_REV: blockIdx.y picks chi2 = v[0] or chi1 = v[1]; the ops un-applied in
+//          reverse order, <chi|G|chi> of every hop and of D before its
+//          un-application added to its reduction slot (chi1's negated).  The
+//          bracket Im <lambda|G|psi> is (<chi2|G|chi2> - <chi1|G|chi1>) / 4
+//          with chi1, chi2 = lambda +- i psi.
+template <int MODE, bool GEN>
+__global__ void __launch_bounds__(1024) k_sec_rows_short(RowsArgs A)
 {
-    static_assert(TT == kT, "the code tables are laid out for kT threads");
-    const kSecOp *__restrict__ kops = (const kSecOp *)ops;
-    const kc128 *__restrict__ kang = (const kc128 *)ang;
-    const kSecModel *__restrict__ kM = (const kSecModel *)M;
-    constexpr int N = RPT;         // elements per thread
-    constexpr int kWv = TT / 64;   // waves of the workgroup
     constexpr bool REV = MODE == S_REV;
-    // partner reads in flight per thread in a gate's exchange (H: one, its
-    // two register tiles leave no registers for more)
-    constexpr int kInFlight = MODE == S_HAM ? 1 : 3;
-    // gate codes: forward and reverse passes load the next gate's codes from
-    // global memory into registers while a gate is applied; H (no registers
-    // to spare) copies them into LDS (cbuf)
-    constexpr bool RC = MODE != S_HAM;
-    // column of thread u's element e
-    auto elem = [](uint32_t u, int e) -> uint32_t { return u + (uint32_t)(e * TT); };
     extern __shared__ __align__(16) char smem[];
-    double2 *xch = (double2 *)smem;   // pair slots below xch_elems, then kZero zero slots
-    double *acc = (double *)(smem + (size_t)(xch_elems + kZero) * 16);   // kMaxRed x kWaves
-    double2 *dloc = (double2 *)(acc + kMaxRed * kWaves);   // the pass's U-count phase table
-    double2 *cis = dloc + kDiagTab;                                       // unit phases
-    uint16_t *cbuf = (uint16_t *)(cis + (1u << kCisBits));                // the next gate's codes
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t n = (uint32_t)kM->n[col];
-    const int nr = kM->n[1 - col];
-    // the tables' pointers come from memory: global address space, so that
-    // the loads take a scalar base and a 32-bit offset
-    const gu32 *__restrict__ cpat = (const gu32 *)kM->pat[col];
-    const gf64 *__restrict__ cbase = (const gf64 *)kM->base[col];
-    const gu16 *__restrict__ gcode = (const gu16 *)kM->code;
-    // row-uniform: scalar loads
-    const ku32 *__restrict__ rpat = (const ku32 *)kM->pat[1 - col];
-    const kf64 *__restrict__ rbase = (const kf64 *)kM->base[1 - col];
-    for (int i = tid; i < kMaxRed * kWv; i += TT)
-        acc[i] = 0.0;
-    for (int i = tid; i < kZero; i += TT)   // read by inactive elements, never written
-        xch[xch_elems + i] = make_double2(0.0, 0.0);
-    if constexpr (MODE != S_HAM && GEN)
-        build_cis(cis, tid, TT);
-    // execution position of the pass's diagonal op (at most one; n_ops: none)
-    int dexec = n_ops;
-    for (int io = 0; io < n_ops; ++io)
-        if (kops[io].kind == SOP_DIAG)
-            dexec = REV ? n_ops - 1 - io : io;
-    // U-only gate passes: the diagonal op's phase table in LDS (conjugated to
-    // un-apply), looked up per element by the number of doubly occupied sites
-    if constexpr (MODE != S_HAM && !GEN) {
-        if (dexec < n_ops && tid < kDiagTab) {
-            double2 e = dph[(size_t)kops[REV ? n_ops - 1 - dexec : dexec].tab * kDiagTab + tid];
-            if constexpr (REV)
-                e.y = -e.y;
-            dloc[tid] = e;
-        }
-    }
-    // cbuf holds the code table of op `ready` (-1: none); the first hopping
-    // op in execution order now
-    int ready = -1;
-    for (int oi = 0; oi < n_ops && ready < 0; ++oi) {
-        const int io = REV ? n_ops - 1 - oi : oi;
-        if (kops[io].kind == SOP_HOP)
-            ready = io;
-    }
-    Codes<RPT> pre;   // RC: the codes of op `ready`
-    if (ready >= 0) {
-        if constexpr (RC) {
-            pre = load_codes_g<RPT>(gcode + kops[ready].tab, (uint32_t)tid);
-        } else {
-            fetch_codes<TT, RPT>(gcode + kops[ready].tab, cbuf, tid);
-            __builtin_amdgcn_s_waitcnt(0);
-        }
-    }
-    __syncthreads();
-    double eacc = 0.0;
+    const int tid = threadIdx.x, T = blockDim.x, lr = A.lr, R = 1 << lr;
+    const RowLds L = row_lds(short_vec_bytes(A.nslots, lr), R, A.n_phases, A.n_red, T, GEN);
+    RowPassCtx<MODE, GEN> C(A, smem, L);
+    double2 *vec = (double2 *)smem;
+    double *nib = (double *)(smem + L.nib), *rowb = (double *)(smem + L.rowb);
+    uint32_t *rowp = (uint32_t *)(smem + L.rowp);
+    const int vsel = REV ? (int)blockIdx.y : 0;
+    gc128 *__restrict__ v = (gc128 *)A.v[vsel];
+    const gu16 *__restrict__ colslot = (const gu16 *)A.colslot;
+    const gu16 *__restrict__ patslot = (const gu16 *)A.patslot;
+    const gu128 *__restrict__ recs = (const gu128 *)A.recs;
+    const kPhase *__restrict__ phases = (const kPhase *)A.phases;
+    C.prologue();
+    for (int i = tid; i < (A.nslots + 1) << lr; i += T)   // holes and the dummy slot stay zero
+        vec[i] = make_double2(0.0, 0.0);
+    const int n_pre = A.l_pre >= 0 ? A.n_phases : 0;
+    const int n_steps = n_pre + (A.l_post >= 0 ? A.n_phases : 0);
+    const int row = tid & (R - 1), orb = tid >> lr;
+    const int worb = __builtin_amdgcn_readfirstlane(tid & ~63) >> lr;   // the wave's first orbit
+    const uint32_t rofs = (uint32_t)row * 16u;
+    const int ng = (A.n_rows + R - 1) >> lr, total = A.n << lr;
 
-    for (int r = blockIdx.x; r < nr; r += gridDim.x) {
-        uint32_t tr = (uint32_t)tid;   // per-row indices are not kept across rows
-        asm volatile("" : "+v"(tr));
-        const uint32_t rp = rpat[r];
-        const double rb = rbase[r];
-        gc128 *__restrict__ x0 = (gc128 *)(v0 + (size_t)r * (size_t)n);
-        gc128 *__restrict__ x1 = (gc128 *)(v1 + (size_t)r * (size_t)n);
-        // elements past the row end (the last register of some threads) hold
-        // zero: every op leaves them zero and they add nothing to a sum
-        double2 a[N], b[N];
+    // the elements' rows and columns of load and store: rows in the low bits
+    auto each = [&](auto &&f) __attribute__((always_inline)) {
+        for (int i0 = tid; i0 < total; i0 += 4 * T) {
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const uint32_t idx = elem(tr, j), ic = min(idx, n - 1);
-            a[j] = make_double2(x0[ic].x, x0[ic].y);
-            a[j] = idx < n ? a[j] : make_double2(0.0, 0.0);
-            b[j] = make_double2(0.0, 0.0);
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + u * T;
+                if (i < total)
+                    f(u, i >> lr);
+            }
         }
-        // this thread's part of the current reduction slot's sum (REV)
-        double racc = 0.0;
-        // op at execution position oi; IS_DIAG: the diagonal op, else a hop
-        auto step = [&](int oi, auto diag_tag) __attribute__((always_inline)) {
-            constexpr bool IS_DIAG = decltype(diag_tag)::value;
-            const int io = REV ? n_ops - 1 - oi : oi;
-            const kSecOp &op = kops[io];
-            // the element indices recomputed per op, not kept live (with
-            // their 64-bit table addresses) across the op loop
-            uint32_t t = (uint32_t)tid;
-            asm volatile("" : "+v"(t));
-            if constexpr (IS_DIAG) {
-                double th = 0.0;
-                if constexpr (MODE != S_HAM)
-                    th = kang[io].x;
-                // every element's column pattern (U-only: its number of doubly
-                // occupied sites) first, the loads in flight together
-                uint32_t kc[N];
-#pragma unroll
-                for (int j = 0; j < N; ++j) {
-                    const uint32_t cp = cpat[min(elem(t, j), n - 1)];   // past the end: a zero element
-                    kc[j] = GEN ? cp : __popc(rp & cp);
-                }
-#pragma unroll
-                for (int j = 0; j < N; ++j) {
-                    {
-                        const uint32_t k = kc[j];
-                        const double d = GEN ? diag_d(kM, rp, rb, k, cbase[min(elem(t, j), n - 1)])
-                                             : kM->U * (double)k;
-                        if constexpr (MODE == S_HAM) {
-                            fmac_ip(b[j].x, d, a[j].x);
-                            fmac_ip(b[j].y, d, a[j].y);
-                        } else {
-                            // exp(-i th D) forward, exp(+i th D) to un-apply
-                            double2 e;
-                            if constexpr (GEN) {
-                                e = cis_neg(REV ? -th * d : th * d, cis);
-                            } else {
-                                e = dloc[k];
-                            }
-                            if constexpr (REV)   // <chi|D|chi> term
-                                racc += d * (a[j].x * a[j].x + a[j].y * a[j].y);
-                            // a <- e a
-                            const double tx = e.y * a[j].y, ty = e.y * a[j].x;
-                            fma_ip(a[j].x, e.x, -tx);
-                            fma_ip(a[j].y, e.x, ty);
+    };
+    for (int ig = blockIdx.x; ig < (ng + 7) / 8 * 8; ig += gridDim.x) {
+        const int g = group_of(ig, ng);
+        if (g < 0)
+            continue;
+        const int r = (g << lr) + row;
+        const bool live = r < A.n_rows;
+        gc128 *__restrict__ vr = v + (int64_t)r * A.rs;
+        if constexpr (!REV) {
+            if (A.flags & SF_START) {
+                const bool here = (g << lr) <= A.b0_row && A.b0_row < ((g + 1) << lr);
+                if (!here) {
+                    for (int i = tid; i < total; i += T)
+                        if (live) {
+                            gc128 *p = vr + (int64_t)(i >> lr) * A.cs;
+                            p->x = 0.0;
+                            p->y = 0.0;
                         }
-                    }
-                    // one element's phase at a time: fewer live temporaries
-                    __builtin_amdgcn_sched_barrier(0);
+                    continue;
                 }
-            } else {
-                double cs = 0.0, sn = 0.0;
-                if constexpr (MODE != S_HAM) {
-                    cs = kang[io].x;                 // (cos, sin)(th t)
-                    sn = REV ? -kang[io].y : kang[io].y;   // un-apply: sin -> -sin
+            }
+        }
+        const bool start = !REV && (A.flags & SF_START);
+        __syncthreads();
+        for (int i0 = tid; i0 < total; i0 += 4 * T) {
+            double2 x[4];
+            int sl[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int i = i0 + u * T, col = min(i, total - 1) >> lr;
+                x[u] = make_double2(0.0, 0.0);
+                sl[u] = colslot[col];
+                if (start) {
+                    x[u].x = r == A.b0_row && col == A.b0_col ? 1.0 : 0.0;
+                } else if (live && i < total) {
+                    const gc128 *p = vr + (int64_t)col * A.cs;
+                    x[u] = make_double2(p->x, p->y);
                 }
-                const double mt = -op.t;
-                Codes<RPT> cd;
-                if constexpr (RC) {
-                    if (ready != io)   // not prefetched (the op list's nxt links are broken)
-                        pre = load_codes_g<RPT>(gcode + op.tab, t);
-                    cd = pre;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i0 + u * T < total)
+                    vec[(sl[u] << lr) + row] = x[u];
+        }
+        if (A.l_diag >= 0) {
+            const gu32 *rpat = (const gu32 *)A.rpat;
+            const gf64 *rbase = (const gf64 *)A.rbase, *wrow = (const gf64 *)A.wrow;
+            for (int i = tid; i < R; i += T) {
+                const int rr = min((g << lr) + i, A.n_rows - 1);
+                rowp[i] = rpat[rr];
+                rowb[i] = rbase[rr];
+            }
+            if constexpr (GEN)
+                for (int i = tid; i < 64 << lr; i += T)
+                    nib[i] = nibble_sum(wrow + (size_t)min((g << lr) + (i >> 6), A.n_rows - 1) * 16,
+                                        i & 63);
+        }
+        auto diag = [&]() __attribute__((always_inline)) {
+            const double th = A.theta[A.l_diag * A.per];
+            const uint32_t rp = rowp[row];
+            const double rb = GEN ? rowb[row] : 0.0;
+            const double *nb = nib + row * 64;
+            const gf64 *baseslot = (const gf64 *)A.baseslot;
+            double racc = 0.0;
+            for (int i = tid; i < A.nslots << lr; i += T) {
+                const int sl = i >> lr;
+                const uint32_t cp = patslot[sl];
+                double2 a = vec[i];
+                if constexpr (GEN) {
+                    diag_el<REV, true>(a, diag_gen(rb, baseslot[sl], nb, cp), a, th, C.dtab, racc);
                 } else {
-                    if (ready != io) {
-                        fetch_codes<TT, RPT>(gcode + op.tab, cbuf, tid);
-                        __builtin_amdgcn_s_waitcnt(0);
-                        __syncthreads();
-                    }
-                    cd = load_codes<RPT>(cbuf, t);
+                    const int k = __popc(rp & cp);
+                    diag_el<REV, false>(a, A.U * (double)k, C.dtab[k], th, nullptr, racc);
                 }
-                // the next hop's codes: loaded into registers now (RC), or
-                // copied into cbuf at the end of this one's exchange (every
-                // thread has its codes in registers by then)
-                ready = (r + (int)gridDim.x < nr || oi + 1 < n_ops) ? op.nxt[REV ? 1 : 0] : -1;
-                const int nxt = ready;
-                if constexpr (RC) {
-                    if (nxt >= 0)
-                        pre = load_codes_g<RPT>(gcode + kops[nxt].tab, t);
+                vec[i] = a;
+            }
+            if constexpr (REV)
+                C.flush(C.dslot, racc);
+            __syncthreads();
+        };
+        // records of a step's orbits (the next step's are fetched while one runs)
+        struct Recs {
+            uint4 q[3];
+        };
+        auto fetch = [&](int st) __attribute__((always_inline)) {
+            const kPhase &ph = phases[st < A.n_phases ? st : st - A.n_phases];
+            Recs q;
+            const int n2 = ph.n[0], n1 = ph.n[1], n3 = ph.n[2], at = ph.rec;
+            auto ld = [&](int i) {
+                const gu128 *p = recs + i;
+                return make_uint4(p->x, p->y, p->z, p->w);
+            };
+            // lanes past a list's end read its last record (and do nothing with it)
+            q.q[0] = n2 ? ld(at + min(orb, n2 - 1)) : make_uint4(0, 0, 0, 0);
+            q.q[1] = n1 ? ld(at + n2 + min(orb, n1 - 1)) : make_uint4(0, 0, 0, 0);
+            q.q[2] = n3 ? ld(at + n2 + n1 + min(orb, n3 - 1)) : make_uint4(0, 0, 0, 0);
+            return q;
+        };
+        auto lo = [&](uint32_t w) { return ((w & 0xFFFFu) << 4) + rofs; };
+        auto hi = [&](uint32_t w) { return ((w >> 16) << 4) + rofs; };
+        auto at = [&](uint32_t o) -> double2 & { return *(double2 *)(smem + o); };
+        auto phase = [&](int st, const Recs &q) __attribute__((always_inline)) {
+            const int p = st < A.n_phases ? st : st - A.n_phases;
+            const kPhase &ph = phases[p];
+            const int n2 = ph.n[0], n1 = ph.n[1], n3 = ph.n[2];
+            const bool w2 = worb < n2, w13 = worb < n1 || worb < n3;   // wave-uniform
+            const bool a2 = orb < n2, a1 = orb < n1, a3 = orb < n3;
+            double2 x[kOrbitElems];
+#pragma unroll
+            for (int j = 0; j < kOrbitElems; ++j)
+                x[j] = make_double2(0.0, 0.0);
+            if (a2) {
+#pragma unroll
+                for (int j = 0; j < 6; ++j) {
+                    const uint32_t w = j < 2 ? q.q[0].x : (j < 4 ? q.q[0].y : q.q[0].z);
+                    x[j] = at(j & 1 ? hi(w) : lo(w));
                 }
-                // w = sign (active) or 0 (inactive: cos factor 1, no partner term)
-                exchange<RPT, kInFlight>(a, cd, xch, (uint32_t)xch_elems, [&]() {
-                    if (!RC && nxt >= 0)
-                        fetch_codes<TT, RPT>(gcode + kops[nxt].tab, cbuf, tid);
-                }, [&](int j, double2 p, bool act, uint32_t sgn) {
-                    // s (-t) and s sn by a flip of the sign bit (p = 0 when
-                    // inactive: those terms then vanish without a select)
-                    if constexpr (MODE == S_HAM) {   // phi += (-t) s psi_x'
-                        const double m = flip_sign(mt, sgn);
-                        fmac_ip(b[j].x, m, p.x);
-                        fmac_ip(b[j].y, m, p.y);
-                        pin(b[j]);
-                    } else {
-                        const double2 y = a[j];
-                        if constexpr (REV) {   // <chi|h|chi> term: (-t) s Re(conj(chi_x) chi_x')
-                            racc += flip_sign(mt, sgn) * (y.x * p.x + y.y * p.y);
-                            pin(racc);
-                        }
-                        const double ss = flip_sign(sn, sgn);   // x <- cs x + i s sn x'
-                        const double c = act ? cs : 1.0;
-                        fma_ip(a[j].x, c, -ss * p.y);
-                        fma_ip(a[j].y, c, ss * p.x);
-                        pin(a[j]);
-                    }
-                });
             }
-        };
-        // REV: the thread's sum of a run of ops with one reduction slot into
-        // that slot (one wave reduction per run, not per op)
-        auto flush = [&](int red) __attribute__((always_inline)) {
-            if constexpr (REV) {
-                const double w = wave_sum(racc);
-                if (lane == 0)
-                    acc[red * kWv + wave] += w;
-                racc = 0.0;
+            if (a1) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    x[6 + j] = at(j & 1 ? hi(j < 2 ? q.q[1].x : q.q[1].y)
+                                        : lo(j < 2 ? q.q[1].x : q.q[1].y));
             }
+            if (a3) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    x[10 + j] = at(j & 1 ? hi(j < 2 ? q.q[2].x : q.q[2].y)
+                                         : lo(j < 2 ? q.q[2].x : q.q[2].y));
+            }
+            if (w2 || w13)
+                C.gates(x, st < n_pre ? 0 : 1, p, q.q[0].w, q.q[1].w, q.q[2].w, w2, w13);
+            if (a2) {
+#pragma unroll
+                for (int j = 0; j < 6; ++j) {
+                    const uint32_t w = j < 2 ? q.q[0].x : (j < 4 ? q.q[0].y : q.q[0].z);
+                    at(j & 1 ? hi(w) : lo(w)) = x[j];
+                }
+            }
+            if (a1) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    at(j & 1 ? hi(j < 2 ? q.q[1].x : q.q[1].y)
+                             : lo(j < 2 ? q.q[1].x : q.q[1].y)) = x[6 + j];
+            }
+            if (a3) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    at(j & 1 ? hi(j < 2 ? q.q[2].x : q.q[2].y)
+                             : lo(j < 2 ? q.q[2].x : q.q[2].y)) = x[10 + j];
+            }
+            __syncthreads();
         };
-        // the hops at execution positions [o0, o1) (REV: in runs of equal
-        // reduction slots)
-        auto hops = [&](int o0, int o1) __attribute__((always_inline)) {
-            if constexpr (REV) {
-                for (int oi = o0; oi < o1;) {
-                    const int red = kops[n_ops - 1 - oi].red;
-                    do {
-                        step(oi, std::false_type());
-                        ++oi;
-                    } while (oi < o1 && kops[n_ops - 1 - oi].red == red);
-                    flush(red);
+        Recs cur{};
+        if (n_steps > 0)
+            cur = fetch(REV ? n_steps - 1 : 0);
+        __syncthreads();
+        for (int k = 0; k < n_steps; ++k) {
+            const int st = REV ? n_steps - 1 - k : k;
+            if (!REV && st == n_pre && A.l_diag >= 0)
+                diag();
+            const int nx = min(k + 1, n_steps - 1);
+            const Recs nxt = fetch(REV ? n_steps - 1 - nx : nx);
+            phase(st, cur);
+            cur = nxt;
+            if (REV && st == n_pre && A.l_diag >= 0)
+                diag();
+        }
+        // no step after the diagonal (a model without bonds)
+        if (n_pre == n_steps && A.l_diag >= 0)
+            diag();
+        if (!(A.flags & SF_NO_STORE) && live) {
+            each([&](int, int col) __attribute__((always_inline)) {
+                const double2 x = vec[(colslot[col] << lr) + row];
+                gc128 *p = vr + (int64_t)col * A.cs;
+                p->x = x.x;
+                p->y = x.y;
+            });
+        }
+    }
+    if constexpr (REV) {
+        __syncthreads();
+        C.finish(vsel, vsel == 1);
+    }
+}
+
+// ------------------------------------------------------------- long rows --
+// One row of up to 13312 elements per workgroup of 1024 threads, in
+// registers; a phase's layout gives each thread one orbit of six, two of four
+// and one single element.  Between phases the row goes through LDS, real
+// parts first, then imaginary parts: 16 bytes per element would not fit.
+// Modes, vectors and reductions as in k_sec_rows_short.
+// Bound by LDS traffic and VALU: 206 KB go through LDS in each direction per
+// phase, eight phases per layer and spin at 4x4 periodic where an exchange per
+// hop needed 32.  At 12870 x 12870 (5.3 GB moved) a forward pass of 64 hops
+// takes 3.07 ms (7.89 ms with an exchange per hop), the reverse pass of both
+// vectors 7.72 ms (18.6 ms).
+struct LongCodes {
+    uint32_t w[8];
+    // the offsets derived from here on are computed anew: kept from an earlier
+    // use, they would take a register each
+    __device__ __forceinline__ void renew()
+    {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            asm volatile("" : "+v"(w[k]));
+    }
+    // LDS byte offset of element j
+    __device__ __forceinline__ uint32_t at(int j) const
+    {
+        return j & 1 ? (w[j >> 1] >> 13) & 0x7FFF8u : (w[j >> 1] << 3) & 0x7FFF8u;
+    }
+};
+
+__device__ __forceinline__ LongCodes long_codes(const gu128 *p)
+{
+    LongCodes c;
+    const uint4 a = make_uint4(p[0].x, p[0].y, p[0].z, p[0].w);
+    const uint4 b = make_uint4(p[1].x, p[1].y, p[1].z, p[1].w);
+    c.w[0] = a.x;
+    c.w[1] = a.y;
+    c.w[2] = a.z;
+    c.w[3] = a.w;
+    c.w[4] = b.x;
+    c.w[5] = b.y;
+    c.w[6] = b.z;
+    c.w[7] = b.w;
+    return c;
+}
+
+// The row's slots of a thread's elements t + j kLongT (two chunks of eight).
+__device__ __forceinline__ LongCodes col_codes(const uint16_t *colslot, int t)
+{
+    const gu128 *p = (const gu128 *)colslot;
+    LongCodes c;
+    const uint4 a = make_uint4(p[t].x, p[t].y, p[t].z, p[t].w);
+    const uint4 b = make_uint4(p[kLongT + t].x, p[kLongT + t].y, p[kLongT + t].z,
+                               p[kLongT + t].w);
+    c.w[0] = a.x;
+    c.w[1] = a.y;
+    c.w[2] = a.z;
+    c.w[3] = a.w;
+    c.w[4] = b.x;
+    c.w[5] = b.y;
+    c.w[6] = b.z;
+    c.w[7] = b.w;
+    return c;
+}
+
+// Move a row from one register layout to another through LDS.
+template <int NF, int NTO>
+__device__ __forceinline__ void long_exchange(const double2 (&from)[NF], LongCodes cf,
+                                              double2 (&to)[NTO], LongCodes ct, char *buf)
+{
+    double re[NTO];
+    __syncthreads();   // the last exchange's reads are done
+#pragma unroll
+    for (int j = 0; j < NF; ++j)
+        *(double *)(buf + cf.at(j)) = from[j].x;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NTO; ++j)
+        re[j] = *(const double *)(buf + ct.at(j));
+    cf.renew();
+    ct.renew();
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NF; ++j)
+        *(double *)(buf + cf.at(j)) = from[j].y;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NTO; ++j)
+        to[j] = make_double2(re[j], *(const double *)(buf + ct.at(j)));
+}
+
+template <int MODE, bool GEN>
+__global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
+{
+    constexpr bool REV = MODE == S_REV;
+    extern __shared__ __align__(16) char smem[];
+    const int tid = threadIdx.x;
+    const RowLds L = row_lds(long_vec_bytes(A.nslots), 1, A.n_phases, A.n_red, kLongT, GEN);
+    RowPassCtx<MODE, GEN> C(A, smem, L);
+    double *nib = (double *)(smem + L.nib);
+    const int vsel = REV ? (int)blockIdx.y : 0;
+    const kPhase *__restrict__ phases = (const kPhase *)A.phases;
+    const gu128 *__restrict__ lcode = (const gu128 *)A.lcode;
+    const ku32 *__restrict__ rpat = (const ku32 *)A.rpat;
+    const kf64 *__restrict__ rbase = (const kf64 *)A.rbase;
+    C.prologue();
+    if (tid < kLongDummy)
+        ((double *)smem)[A.nslots + tid] = 0.0;
+    const int n_pre = A.l_pre >= 0 ? A.n_phases : 0;
+    const int n_steps = n_pre + (A.l_post >= 0 ? A.n_phases : 0);
+    const int wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);
+    const uint32_t n = (uint32_t)A.n;
+    auto ph_of = [&](int st) { return st < A.n_phases ? st : st - A.n_phases; };
+
+    for (int r = blockIdx.x; r < A.n_rows; r += gridDim.x) {
+        gc128 *__restrict__ row = (gc128 *)A.v[vsel] + (size_t)r * n;
+        const bool start = !REV && (A.flags & SF_START);
+        uint32_t t = (uint32_t)tid;   // per-row addresses are not kept across rows
+        asm volatile("" : "+v"(t));
+        if (start && r != A.b0_row) {
+            for (uint32_t i = t; i < n; i += kLongT) {
+                row[i].x = 0.0;
+                row[i].y = 0.0;
+            }
+            continue;
+        }
+        double2 x[kOrbitElems];
+        int p0 = ph_of(REV ? n_steps - 1 : 0);
+        LongCodes cur = long_codes(lcode + ((size_t)p0 * kLongT + t) * 2);
+        {
+            double2 in[kLongElems];
+            if (start) {
+#pragma unroll
+                for (int j = 0; j < kLongElems; ++j)
+                    in[j] = make_double2(
+                        t + (uint32_t)(j * kLongT) == (uint32_t)A.b0_col ? 1.0 : 0.0, 0.0);
+            } else {
+                // past the row's end: zeros, into the dummy slots
+#pragma unroll
+                for (int j = 0; j < kLongElems; ++j) {
+                    const uint32_t i = t + (uint32_t)(j * kLongT), ic = min(i, n - 1);
+                    in[j] = make_double2(row[ic].x, row[ic].y);
+                    in[j] = i < n ? in[j] : make_double2(0.0, 0.0);
+                }
+            }
+            const LongCodes cc = col_codes(A.colslot, (int)t);
+            if constexpr (GEN)
+                if (A.l_diag >= 0 && tid < 64)   // read after the exchange's barriers
+                    nib[tid] = nibble_sum((const gf64 *)A.wrow + (size_t)r * 16, tid);
+            long_exchange(in, cc, x, cur, smem);
+        }
+        auto diag = [&]() __attribute__((always_inline)) {
+            const double th = A.theta[A.l_diag * A.per];
+            const uint32_t rp = rpat[r];
+            const double rb = GEN ? rbase[r] : 0.0;
+            uint32_t td = (uint32_t)tid;   // the tables' values are loaded here, not kept
+            asm volatile("" : "+v"(td));
+            const LongCodes pt = long_codes((const gu128 *)A.lpat + (size_t)td * 2);
+            const gf64 *lbase = (const gf64 *)A.lbase;
+            double racc = 0.0;
+#pragma unroll
+            for (int j = 0; j < kOrbitElems; ++j) {
+                const uint32_t cp = (pt.w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
+                if constexpr (GEN) {
+                    diag_el<REV, true>(x[j], diag_gen(rb, lbase[j * kLongT + td], nib, cp), x[j],
+                                       th, C.dtab, racc);
+                } else {
+                    const int k = __popc(rp & cp);
+                    diag_el<REV, false>(x[j], A.U * (double)k, C.dtab[k], th, nullptr, racc);
+                }
+                __builtin_amdgcn_sched_barrier(0);   // fewer values in flight
+            }
+            if constexpr (REV)
+                C.flush(C.dslot, racc);
+        };
+        for (int k = 0; k < n_steps; ++k) {
+            const int st = REV ? n_steps - 1 - k : k;
+            const kPhase &ph = phases[ph_of(st)];
+            if (!REV && st == n_pre && A.l_diag >= 0)
+                diag();
+            // the next step's layout is fetched while this one's hops run
+            const int nx = min(k + 1, n_steps - 1), pn = ph_of(REV ? n_steps - 1 - nx : nx);
+            uint32_t tn = (uint32_t)tid;
+            asm volatile("" : "+v"(tn));
+            const LongCodes nxt = long_codes(lcode + ((size_t)pn * kLongT + tn) * 2);
+            const uint32_t f = cur.w[7];
+            C.gates(x, st < n_pre ? 0 : 1, ph_of(st), f, f, f, wave0 < ph.n[0],
+                    wave0 < ph.n[1] || wave0 < ph.n[2]);
+            if (REV && st == n_pre && A.l_diag >= 0)
+                diag();
+            if (k + 1 < n_steps) {
+                double2 y[kOrbitElems];
+                long_exchange(x, cur, y, nxt, smem);
+#pragma unroll
+                for (int j = 0; j < kOrbitElems; ++j)
+                    x[j] = y[j];
+                cur = nxt;
+            }
+        }
+        if (!(A.flags & SF_NO_STORE)) {
+            uint32_t ts = (uint32_t)tid;
+            asm volatile("" : "+v"(ts));
+            double2 out[kLongElems];
+            long_exchange(x, cur, out, col_codes(A.colslot, (int)ts), smem);
+#pragma unroll
+            for (int j = 0; j < kLongElems; ++j) {
+                const uint32_t i = ts + (uint32_t)(j * kLongT);
+                if (i < n) {
+                    row[i].x = out[j].x;
+                    row[i].y = out[j].y;
+                }
+            }
+        }
+    }
+    if constexpr (REV) {
+        __syncthreads();
+        C.finish(vsel, vsel == 1);
+    }
+}
+
+// --------------------------------------------------------------------- H --
+// The part of H that acts on one spin's rows: every hop of that spin, and
+// with `diag` the diagonal.  An element sums its partners' values over the
+// bonds; a table names each partner's slot and sign (an inactive element's
+// code names a zero slot).
+struct HamArgs {
+    const uint16_t *colslot, *patslot, *hcode;
+    const double *baseslot;
+    const uint32_t *rpat;
+    const double *rbase, *wrow, *tb;   // tb: -t_b per bond, padded with zeros
+    double U;
+    int n, n_rows, nslots, lr, nb, diag, out_mode;
+    int64_t rs, cs;
+    double2 *psi, *out;
+    double *partial;                   // NULL: no energy
+};
+
+// sign bit of a code (bit 15, or bit 31 of the packed dword)
+__device__ __forceinline__ uint32_t code_sign(uint32_t w, int odd)
+{
+    return odd ? w & 0x80000000u : (w << 16) & 0x80000000u;
+}
+
+// Store phi's element as the pass asks.
+__device__ __forceinline__ void ham_store(int mode, gc128 *out, gc128 *psi, double2 phi,
+                                          double2 own)
+{
+    if (mode != HO_SET) {
+        phi.x += out->x;
+        phi.y += out->y;
+    }
+    if (mode == HO_MIX) {
+        psi->x = phi.x - own.y;
+        psi->y = phi.y + own.x;
+        phi = make_double2(phi.x + own.y, phi.y - own.x);
+    }
+    out->x = phi.x;
+    out->y = phi.y;
+}
+
+template <bool GEN>
+__global__ void __launch_bounds__(1024) k_sec_ham_short(HamArgs A)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int tid = threadIdx.x, T = blockDim.x, lr = A.lr, R = 1 << lr;
+    double2 *vec = (double2 *)smem;
+    double *nib = (double *)(smem + short_vec_bytes(A.nslots, lr));
+    double *wsum = nib + (GEN ? 64 << lr : 0);
+    const int row = tid & (R - 1), total = A.n << lr, ng = (A.n_rows + R - 1) >> lr;
+    const gu16 *colslot = (const gu16 *)A.colslot, *patslot = (const gu16 *)A.patslot;
+    const gu32 *rpat = (const gu32 *)A.rpat;
+    const gf64 *rbase = (const gf64 *)A.rbase, *wrow = (const gf64 *)A.wrow;
+    const gf64 *baseslot = (const gf64 *)A.baseslot;
+    const kf64 *tb = (const kf64 *)A.tb;
+    const int chunks = (A.nb + 7) / 8;
+    if (tid < R)
+        vec[(A.nslots << lr) + tid] = make_double2(0.0, 0.0);
+    double e = 0.0;
+    for (int ig = blockIdx.x; ig < (ng + 7) / 8 * 8; ig += gridDim.x) {
+        const int g = group_of(ig, ng);
+        if (g < 0)
+            continue;
+        const int r = min((g << lr) + row, A.n_rows - 1);
+        const bool live = (g << lr) + row < A.n_rows;
+        gc128 *psi = (gc128 *)A.psi + (int64_t)r * A.rs, *out = (gc128 *)A.out + (int64_t)r * A.rs;
+        __syncthreads();   // the last group's reads are done
+        for (int i = tid; i < total; i += T) {
+            const gc128 *p = psi + (int64_t)(i >> lr) * A.cs;
+            vec[((int)colslot[i >> lr] << lr) + row] = make_double2(p->x, p->y);
+        }
+        if (GEN && A.diag)
+            for (int i = tid; i < 64 << lr; i += T)
+                nib[i] = nibble_sum(wrow + (size_t)min((g << lr) + (i >> 6), A.n_rows - 1) * 16,
+                                    i & 63);
+        __syncthreads();
+        const uint32_t rp = rpat[r];
+        const double rb = GEN ? rbase[r] : 0.0;
+        for (int i = tid; i < total; i += T) {
+            const int col = i >> lr, sl = colslot[col];
+            const double2 own = vec[(sl << lr) + row];
+            double2 phi = make_double2(0.0, 0.0);
+            if (A.diag) {
+                const uint32_t cp = patslot[sl];
+                const double d = GEN ? diag_gen(rb, baseslot[sl], nib + row * 64, cp)
+                                     : A.U * (double)__popc(rp & cp);
+                phi = make_double2(d * own.x, d * own.y);
+            }
+            const gu128 *hc = (const gu128 *)A.hcode + (size_t)col * chunks;
+            for (int c = 0; c < chunks; ++c) {
+                const uint32_t w[4] = {hc[c].x, hc[c].y, hc[c].z, hc[c].w};
+#pragma unroll
+                for (int b = 0; b < 8; ++b) {
+                    const uint32_t q = b & 1 ? (w[b >> 1] >> 16) & 0x7FFFu : w[b >> 1] & 0x7FFFu;
+                    const double2 p = vec[(q << lr) + row];
+                    const double m = xor_sign(tb[c * 8 + b], code_sign(w[b >> 1], b & 1));
+                    phi.x = fma(m, p.x, phi.x);
+                    phi.y = fma(m, p.y, phi.y);
+                }
+            }
+            if (live) {
+                e += re_dot(own, phi);
+                ham_store(A.out_mode, out + (int64_t)col * A.cs, psi + (int64_t)col * A.cs, phi,
+                          own);
+            }
+        }
+    }
+    if (A.partial) {
+        e = wave_sum(e);
+        if ((tid & 63) == 0)
+            wsum[tid >> 6] = e;
+        __syncthreads();
+        if (tid == 0) {
+            double s = 0.0;
+            for (int w = 0; w < T >> 6; ++w)
+                s += wsum[w];
+            A.partial[blockIdx.x] = s;
+        }
+    }
+}
+
+// Long rows: H is real, so the real and the imaginary parts of a row take
+// turns in LDS.  Thread t sums for the slots t + j kLongT: lanes of
+// neighbouring slots are in different bank classes, and so are their
+// partners across one bond.
+template <bool GEN>
+__global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
+{
+    extern __shared__ __align__(16) char smem[];
+    double *buf = (double *)smem;
+    double *nib = buf + A.nslots + kLongDummy;
+    double *wsum = nib + 64;
+    const int tid = threadIdx.x;
+    const uint32_t n = (uint32_t)A.n;
+    const gu16 *patslot = (const gu16 *)A.patslot;
+    const gf64 *baseslot = (const gf64 *)A.baseslot;
+    const kf64 *tb = (const kf64 *)A.tb;
+    const ku32 *rpat = (const ku32 *)A.rpat;
+    const kf64 *rbase = (const kf64 *)A.rbase;
+    for (int i = tid; i < A.nslots + kLongDummy; i += kLongT)   // the holes and the zero slots
+        buf[i] = 0.0;
+    double e = 0.0;
+    for (int r = blockIdx.x; r < A.n_rows; r += gridDim.x) {
+        gc128 *psi = (gc128 *)A.psi + (size_t)r * n, *out = (gc128 *)A.out + (size_t)r * n;
+        const uint32_t rp = rpat[r];
+        const double rb = GEN ? rbase[r] : 0.0;
+        int t = tid;   // the tables' values are not kept across rows
+        asm volatile("" : "+v"(t));
+        double re_out[kLongElems];
+        LongCodes cc = col_codes(A.colslot, t);
+        __syncthreads();
+        if (GEN && A.diag && tid < 64)
+            nib[tid] = nibble_sum((const gf64 *)A.wrow + (size_t)r * 16, tid);
+#pragma unroll
+        for (int j = 0; j < kLongElems; ++j) {
+            const uint32_t i = (uint32_t)(t + j * kLongT);
+            const double x = psi[min(i, n - 1)].x;
+            *(double *)(smem + cc.at(j)) = i < n ? x : 0.0;
+        }
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+            asm volatile("" : "+v"(t));
+            __syncthreads();
+            double phi[kLongElems];
+#pragma unroll
+            for (int j = 0; j < kLongElems; ++j) {
+                phi[j] = 0.0;
+                const int sl = t + j * kLongT;
+                if (A.diag && sl < A.nslots) {
+                    const uint32_t cp = patslot[sl];
+                    const double d = GEN ? diag_gen(rb, baseslot[sl], nib, cp)
+                                         : A.U * (double)__popc(rp & cp);
+                    phi[j] = d * buf[sl];
+                }
+            }
+            cc.renew();
+            LongCodes nx = col_codes(A.hcode, t);   // the same chunk layout
+#pragma unroll 1
+            for (int b = 0; b < A.nb; ++b) {
+                const LongCodes w = nx;
+                nx = col_codes(A.hcode + (size_t)min(b + 1, A.nb - 1) * 16 * kLongT, t);
+                const double m = tb[b];
+#pragma unroll
+                for (int j = 0; j < kLongElems; ++j) {
+                    const uint32_t o = j & 1 ? (w.w[j >> 1] >> 13) & 0x3FFF8u
+                                             : (w.w[j >> 1] << 3) & 0x3FFF8u;
+                    const double p = *(const double *)(smem + o);
+                    phi[j] = fma(xor_sign(m, code_sign(w.w[j >> 1], j & 1)), p, phi[j]);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < kLongElems; ++j) {
+                const int sl = t + j * kLongT;
+                if (sl < A.nslots)
+                    e = fma(buf[sl], phi[j], e);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < kLongElems; ++j) {
+                const int sl = t + j * kLongT;
+                if (sl < A.nslots)
+                    buf[sl] = phi[j];
+            }
+            __syncthreads();
+            if (half == 0) {
+#pragma unroll
+                for (int j = 0; j < kLongElems; ++j)
+                    re_out[j] = *(const double *)(smem + cc.at(j));
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < kLongElems; ++j)
+                {
+                    const uint32_t i = (uint32_t)(t + j * kLongT);
+                    const double y = psi[min(i, n - 1)].y;
+                    *(double *)(smem + cc.at(j)) = i < n ? y : 0.0;
                 }
             } else {
-                for (int oi = o0; oi < o1; ++oi)
-                    step(oi, std::false_type());
-            }
-        };
-        // the hops before the diagonal, the diagonal, the hops after it: each
-        // loop body is a single path, so the register tile keeps its
-        // registers across ops (a loop over both kinds merges two versions
-        // of the tile at the end of every op, and copies it)
-        hops(0, dexec);
-        if (dexec < n_ops) {
-            step(dexec, std::true_type());
-            flush(kops[REV ? n_ops - 1 - dexec : dexec].red);
-        }
-        hops(dexec + 1, n_ops);
-        if constexpr (MODE == S_HAM) {
 #pragma unroll
-            for (int j = 0; j < N; ++j)
-                eacc += a[j].x * b[j].x + a[j].y * b[j].y;
-        }
-        if (!(flags & SF_NO_STORE)) {
-            // addresses recomputed here rather than kept from the loads
-            uint32_t t = (uint32_t)tid;
-            asm volatile("" : "+v"(t));
-#pragma unroll
-            for (int j = 0; j < N; ++j) {
-                const uint32_t idx = elem(t, j);
-                if (idx < n) {
-                    if constexpr (MODE != S_HAM) {
-                        x0[idx].x = a[j].x;
-                        x0[idx].y = a[j].y;
-                    } else {
-                        x1[idx].x = b[j].x;
-                        x1[idx].y = b[j].y;
+                for (int j = 0; j < kLongElems; ++j) {
+                    const uint32_t i = (uint32_t)(t + j * kLongT);
+                    if (i < n) {
+                        const double2 f = make_double2(re_out[j],
+                                                       *(const double *)(smem + cc.at(j)));
+                        out[i].x = f.x;
+                        out[i].y = f.y;
                     }
                 }
             }
         }
     }
-    if constexpr (MODE == S_HAM) {
-        const double w = wave_sum(eacc);
-        if (lane == 0)
-            acc[wave] = w;
-    }
-    __syncthreads();
-    if constexpr (MODE != S_FWD) {
-        if (tid < n_red) {
+    if (A.partial) {
+        e = wave_sum(e);
+        if ((tid & 63) == 0)
+            wsum[tid >> 6] = e;
+        __syncthreads();
+        if (tid == 0) {
             double s = 0.0;
-            for (int w = 0; w < kWv; ++w)
-                s += acc[tid * kWv + w];
-            partial[(size_t)(row0 + tid) * pstride + blockIdx.x] = (flags & SF_NEGATE) ? -s : s;
+            for (int w = 0; w < kLongT / 64; ++w)
+                s += wsum[w];
+            A.partial[blockIdx.x] = s;
         }
     }
 }
@@ -636,32 +1110,6 @@ k_sec_mix(double2 *__restrict__ psi, double2 *__restrict__ lam, size_t n)
         const double2 p = psi[i], l = lam[i];
         psi[i] = make_double2(l.x - p.y, l.y + p.x);
         lam[i] = make_double2(l.x + p.y, l.y - p.x);
-    }
-}
-
-// Per op of a sweep: HOP (cos, sin)(th_param t_b); DIAG (th_param, 0) and
-// its phase table dph[op.tab][k] = exp(-i th U k), k = 0 .. kDiagTab - 1.
-__global__ void __launch_bounds__(256)
-k_sec_angles(const SecOp *__restrict__ ops, int n, const double *__restrict__ theta, double U,
-             double2 *__restrict__ ang, double2 *__restrict__ dph)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const SecOp o = ops[i];
-        if (o.param < 0)   // a term of H: no angle
-            continue;
-        if (o.kind == SOP_HOP) {
-            double s, c;
-            sincos(theta[o.param] * o.t, &s, &c);
-            ang[i] = make_double2(c, s);
-        } else {
-            const double th = theta[o.param];
-            ang[i] = make_double2(th, 0.0);
-            for (int k = 0; k < kDiagTab; ++k) {
-                double s, c;
-                sincos(th * (U * (double)k), &s, &c);
-                dph[(size_t)o.tab * kDiagTab + k] = make_double2(c, -s);
-            }
-        }
     }
 }
 
@@ -739,57 +1187,51 @@ k_sec_reduce(const double *__restrict__ partial, int pstride, const int32_t *__r
 // ------------------------------------------------------------------ host --
 
 struct RowPass {
-    int col = 0;
-    std::vector<SecOp> ops;
-    std::vector<int> red_param;   // parameter of each reduction slot
+    int col = 0;                          // the spin whose patterns index the rows
+    int l_pre = -1, l_diag = -1, l_post = -1;
+    std::vector<int> red_param;           // parameter of each reduction slot
+};
+
+// One spin's tables on the device (one allocation).
+struct SpinTables {
+    int n = 0, nslots = 0, lr = 0, threads = 64;
+    bool is_long = false;
+    SecPhase *phases = nullptr;
+    Rec *recs = nullptr;
+    uint4 *lcode = nullptr, *lpat = nullptr;
+    uint32_t *pat = nullptr;
+    double *lbase = nullptr, *base = nullptr, *baseslot = nullptr, *wrow = nullptr;
+    uint16_t *colslot = nullptr, *patslot = nullptr, *hcode = nullptr;
 };
 
 // Sector tables of one model on one device.
 struct Tables {
     int n[2] = {0, 0};
-    int xch = 0;                  // first zero slot: above every gate's pair slots, a multiple of 16
-    std::vector<int> tab[2];      // per bond: offset of its spin-s code table
     size_t b0_pos = 0;            // position of |b0> in layout A
+    int b0_rank[2] = {0, 0};      // ranks of |b0>'s patterns
     bool general = false;         // eps or V terms in the diagonal
+    bool is_long = false;
     double U = 0.0;
-    SecModel *d_model = nullptr;
-    uint32_t *d_pat[2] = {nullptr, nullptr};
-    double *d_base[2] = {nullptr, nullptr};
-    uint16_t *d_code = nullptr;
-    ~Tables()
-    {
-        (void)hipFree(d_model);
-        for (int s = 0; s < 2; ++s) {
-            (void)hipFree(d_pat[s]);
-            (void)hipFree(d_base[s]);
-        }
-        (void)hipFree(d_code);
-    }
+    int n_phases = 0, nb = 0, per = 1;
+    SpinTables sp[2];
+    SecGate *d_gates = nullptr;
+    double *d_tb = nullptr;
+    char *blob = nullptr;
+    ~Tables() { (void)hipFree(blob); }
 };
 
 struct Program {
     std::vector<RowPass> fwd;
     int final_col = 0;
-    SecOp *d_ops = nullptr;       // forward passes' ops, then H ops (X spin + D, Y spin)
-    int n_ops = 0;                // all of them (the angle table's entries)
-    int n_diag = 0;               // diagonal ops of the sweep (phase tables)
-    std::vector<int> op_off;      // per forward pass
-    int ham_x_off = 0, ham_x_n = 0, ham_y_off = 0, ham_y_n = 0;
     // reduction: partial rows 0, 1 = the two energy parts, then each reverse
     // pass's slots (forward order of passes)
     std::vector<int> red_row0;    // per forward pass: its chi2 rows, then its chi1 rows
-    int n_rows = 0;
+    int n_rows = 0, max_red = 0;
     int32_t *d_ptr = nullptr, *d_rows = nullptr, *d_nblk = nullptr;
     double *d_scale = nullptr;
+    char *blob = nullptr;
     int n_out = 0;
-    ~Program()
-    {
-        (void)hipFree(d_ops);
-        (void)hipFree(d_nblk);
-        (void)hipFree(d_ptr);
-        (void)hipFree(d_rows);
-        (void)hipFree(d_scale);
-    }
+    ~Program() { (void)hipFree(blob); }
 };
 
 struct Entry {
@@ -802,338 +1244,135 @@ std::map<std::pair<uint64_t, int>, Entry> g_cache;   // (handle uid, device)
 
 hubbard_status fail(hubbard_status s, const std::string &m) { return set_error(s, m); }
 
-hipError_t upload(void **dst, const void *src, size_t bytes)
-{
-    hipError_t e = hipMalloc(dst, std::max<size_t>(bytes, 16));
-    if (e == hipSuccess && bytes)
-        e = hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice);
-    return e;
-}
-
-int popc(uint32_t x) { return __builtin_popcount(x); }
-
-// LDS slots of a gate's pairs, chosen so that the exchange's LDS accesses
-// are free of bank conflicts.  Pair q takes the slots 2p and 2p + 1 for some
-// p, in either order (an element reads its partner at its own slot XOR 1),
-// and p and the order are free.  On this GPU a wave's 16-byte LDS write is
-// served 8 lanes per cycle (32 banks of 4 bytes: slots equal modulo 8
-// conflict) and a 16-byte read 16 lanes per cycle (64 banks: modulo 16).
-// An element e (thread e mod kT, register e / kT) writes its slot s and reads
-// s XOR 1, so a pair with lower slot residue r (mod 16) puts r (mod 8) into
-// e1's write group, r ^ 1 (mod 8) into e2's, r ^ 1 into e1's read group and r
-// into e2's.  Greedy over the pairs in rank order: the residue that adds no
-// conflict (else the fewest), then the least used class p mod 8 (the slots
-// stay dense).  Returns the slots used (2 + 2 max p).
-int pair_slots(const std::vector<std::array<int, 2>> &prs, int rpt, std::vector<int> &slot)
-{
-    const int groups = rpt * kT / 8;
-    std::vector<uint8_t> w8((size_t)groups, 0);        // write residues (mod 8) per 8 lanes
-    std::vector<uint16_t> r16((size_t)groups / 2, 0);  // read residues (mod 16) per 16 lanes
-    auto g8 = [](int e) { return (e / kT) * (kT / 8) + (e % kT) / 8; };
-    int count[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int top = -1;
-    slot.assign(2 * prs.size(), 0);
-    for (size_t q = 0; q < prs.size(); ++q) {
-        const int a8 = g8(prs[q][0]), b8 = g8(prs[q][1]), a16 = a8 / 2, b16 = b8 / 2;
-        int best = 0, best_score = 1 << 30;
-        for (int r = 0; r < 16; ++r) {
-            const int r2 = r ^ 1;
-            const int miss = ((w8[a8] >> (r & 7)) & 1) + ((w8[b8] >> (r2 & 7)) & 1) +
-                             ((r16[a16] >> r2) & 1) + ((r16[b16] >> r) & 1);
-            const int score = miss * (1 << 20) + count[r >> 1];
-            if (score < best_score) {
-                best_score = score;
-                best = r;
-            }
-        }
-        const int cls = best >> 1, p = cls + 8 * count[cls]++;
-        top = std::max(top, p);
-        slot[2 * q] = 2 * p + (best & 1);
-        slot[2 * q + 1] = 2 * p + 1 - (best & 1);
-        w8[a8] |= (uint8_t)(1u << (best & 7));
-        w8[b8] |= (uint8_t)(1u << ((best ^ 1) & 7));
-        r16[a16] |= (uint16_t)(1u << (best ^ 1));
-        r16[b16] |= (uint16_t)(1u << best);
+// Host arrays collected into one device allocation.
+struct Blob {
+    std::vector<char> host;
+    std::vector<std::pair<void **, size_t>> at;
+    template <typename T> void add(T **dst, const void *src, size_t bytes)
+    {
+        host.resize((host.size() + 255) & ~(size_t)255);
+        at.push_back({(void **)dst, host.size()});
+        host.resize(host.size() + std::max<size_t>(bytes, 16));
+        if (bytes)
+            std::memcpy(host.data() + at.back().second, src, bytes);
     }
-    return 2 * top + 2;
-}
-
-// LDS of a row workgroup: the pair and zero slots, the reduction slots, the
-// U-count phase table, the unit phases, one gate's code table (of the longer
-// row).
-size_t lds_bytes(const Tables &T)
-{
-    const int rp = std::max(rp_of(rpt_of(T.n[0])), rp_of(rpt_of(T.n[1])));
-    return (size_t)(T.xch + kZero) * 16 + kMaxRed * kWaves * 8 + kDiagTab * 16 +
-           (1u << kCisBits) * 16 + (size_t)kT * rp * 2;
-}
+    template <typename T, typename S> void add(T **dst, const std::vector<S> &v)
+    {
+        add(dst, v.data(), v.size() * sizeof(S));
+    }
+    hipError_t upload(char **blob)
+    {
+        hipError_t e = hipMalloc((void **)blob, std::max<size_t>(host.size(), 256));
+        if (e == hipSuccess)
+            e = hipMemcpy(*blob, host.data(), host.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+            for (auto &p : at)
+                *p.first = *blob + p.second;
+        return e;
+    }
+};
 
 hubbard_status build_tables(const Model &m, Tables &T)
 {
-    const int ns = m.ns;
-    const uint32_t smask = ns >= 32 ? 0xffffffffu : ((1u << ns) - 1u);
-    const int ne[2] = {popc((uint32_t)m.neel & smask), popc((uint32_t)(m.neel >> ns) & smask)};
-    std::vector<uint32_t> pat[2];
-    std::vector<double> base[2];
-    std::vector<int32_t> rank_of[2];
-    for (int s = 0; s < 2; ++s) {
-        rank_of[s].assign((size_t)1 << ns, -1);
-        for (uint32_t p = 0; p <= smask; ++p) {
-            if (popc(p) != ne[s])
-                continue;
-            rank_of[s][p] = (int32_t)pat[s].size();
-            pat[s].push_back(p);
-            double b = 0.0;
-            for (int i = 0; i < ns; ++i)
-                if ((p >> i) & 1u)
-                    b += m.eps[i];
-            for (int k = 0; k < m.nb; ++k)
-                if (((p >> m.bi[k]) & 1u) && ((p >> m.bj[k]) & 1u))
-                    b += m.V[k];
-            base[s].push_back(b);
-            if (p == smask)
-                break;
-        }
-        T.n[s] = (int)pat[s].size();
-    }
-    if (T.n[0] > kMaxRows || T.n[1] > kMaxRows)
-        return fail(HUBBARD_ERR_ARG, "sector rows longer than 13 x 1024");
-    const uint32_t up0 = (uint32_t)m.neel & smask, dn0 = (uint32_t)(m.neel >> ns) & smask;
-    T.b0_pos = (size_t)rank_of[1][dn0] * T.n[0] + rank_of[0][up0];
-    // per bond and spin: pair slots and the Jordan-Wigner sign of the sites
-    // strictly between the bond's ends, at the rank's entry of the
-    // register-tile layout; every other entry (the bond's inactive elements
-    // and the tile's padding) names a zero slot
-    struct Gate {
-        std::vector<std::array<int, 2>> prs;   // (lower, upper) rank, in rank order
-        std::vector<uint32_t> sgn;
-        std::vector<int> slot;                 // per pair: lower's, upper's slot
-    };
-    std::vector<Gate> gates[2];
-    int used = 2;
-    for (int s = 0; s < 2; ++s) {
-        const int R = rpt_of(T.n[s]);
-        gates[s].resize(m.nb);
-        for (int k = 0; k < m.nb; ++k) {
-            const int i = std::min(m.bi[k], m.bj[k]), j = std::max(m.bi[k], m.bj[k]);
-            const uint32_t mask = (1u << i) | (1u << j);
-            const uint32_t between = ((1u << j) - 1u) & ~((2u << i) - 1u);
-            Gate &G = gates[s][k];
-            for (int r = 0; r < T.n[s]; ++r) {
-                const uint32_t p = pat[s][r];
-                if (((p >> i) ^ (p >> j)) & 1u) {
-                    const int r2 = rank_of[s][p ^ mask];
-                    if (r2 > r) {
-                        G.prs.push_back({r, r2});
-                        G.sgn.push_back((uint32_t)(popc(p & between) & 1) << 15);
-                    }
-                }
-            }
-            used = std::max(used, pair_slots(G.prs, R, G.slot));
-        }
-    }
-    T.xch = (used + 15) & ~15;
-    if (T.xch + kZero > 0x7FFF || lds_bytes(T) > 160 * 1024)
-        return fail(HUBBARD_ERR_ARG, "sector gate pairs do not fit the workgroup's LDS");
-    std::vector<uint16_t> codes;
-    for (int s = 0; s < 2; ++s) {
-        T.tab[s].assign(m.nb, 0);
-        const int R = rpt_of(T.n[s]);
-        auto entry = [&](int r) { return (size_t)code_index(R, r % kT, r / kT); };
-        for (int k = 0; k < m.nb; ++k) {
-            const Gate &G = gates[s][k];
-            T.tab[s][k] = (int)codes.size();
-            const size_t at = codes.size();
-            codes.resize(at + (size_t)kT * rp_of(R), (uint16_t)T.xch);
-            std::vector<int> slot((size_t)R * kT, -1);   // per element (rank)
-            for (size_t q = 0; q < G.prs.size(); ++q)
-                for (int h = 0; h < 2; ++h) {
-                    slot[G.prs[q][h]] = G.slot[2 * q + h];
-                    codes[at + entry(G.prs[q][h])] = (uint16_t)(G.slot[2 * q + h] | G.sgn[q]);
-                }
-            // per group of 16 threads and register (the lanes one cycle of a
-            // 16-byte LDS read serves): the zero slot its inactive elements
-            // read, one per half of the group, in a bank group (slot mod 16)
-            // that the group's other reads leave free
-            for (int e0 = 0; e0 < R * kT; e0 += 16) {
-                uint32_t taken = 0, u8[2] = {0, 0};
-                for (int e = e0; e < e0 + 16; ++e)
-                    if (slot[e] >= 0) {
-                        const int q = (slot[e] ^ 1) & 15;
-                        taken |= 1u << q;
-                        u8[(e - e0) / 8] |= 1u << (q & 7);
-                    }
-                for (int h = 0; h < 2; ++h) {
-                    int best = 0, best_miss = 1 << 30;
-                    for (int q = 0; q < 16; ++q) {
-                        const int miss = 4 * ((taken >> q) & 1) + ((u8[h] >> (q & 7)) & 1);
-                        if (miss < best_miss) {
-                            best_miss = miss;
-                            best = q;
-                        }
-                    }
-                    taken |= 1u << best;
-                    // read slot T.xch + best (T.xch is a multiple of 16)
-                    for (int e = e0 + 8 * h; e < e0 + 8 * h + 8; ++e)
-                        if (slot[e] < 0)
-                            codes[at + entry(e)] = (uint16_t)((T.xch + best) ^ 1);
-                }
-            }
-        }
-    }
+    SectorPlan P;
+    const std::string err = plan_sector(m, P);
+    if (!err.empty())
+        return fail(HUBBARD_ERR_ARG, err);
+    const uint32_t smask = (1u << m.ns) - 1u;
+    T.b0_rank[0] = P.spin[0].rank_of[(uint32_t)m.neel & smask];
+    T.b0_rank[1] = P.spin[1].rank_of[(uint32_t)(m.neel >> m.ns) & smask];
     T.general = m.general;
     T.U = m.U;
-    SecModel sm;
-    std::memset(&sm, 0, sizeof(sm));
-    sm.ns = ns;
-    sm.U = m.U;
-    sm.n[0] = T.n[0];
-    sm.n[1] = T.n[1];
+    T.n_phases = (int)P.sites.size();
+    T.nb = m.nb;
+    T.per = m.params_per_layer();
+    Blob B;
+    B.add(&T.d_gates, P.gates);
+    std::vector<double> tb((size_t)std::max(8, ham_bonds(m.nb)), 0.0);
     for (int k = 0; k < m.nb; ++k)
-        if (m.V[k] != 0.0) {
-            sm.vi[sm.nvb] = m.bi[k];
-            sm.vj[sm.nvb] = m.bj[k];
-            sm.vV[sm.nvb] = m.V[k];
-            ++sm.nvb;
-        }
-    hipError_t e = hipSuccess;
-    for (int s = 0; s < 2 && e == hipSuccess; ++s) {
-        e = upload((void **)&T.d_pat[s], pat[s].data(), pat[s].size() * 4);
-        if (e == hipSuccess)
-            e = upload((void **)&T.d_base[s], base[s].data(), base[s].size() * 8);
-        sm.pat[s] = T.d_pat[s];
-        sm.base[s] = T.d_base[s];
+        tb[k] = -m.t[k];
+    B.add(&T.d_tb, tb);
+    for (int s = 0; s < 2; ++s) {
+        const SpinPlan &S = P.spin[s];
+        SpinTables &D = T.sp[s];
+        T.n[s] = D.n = S.n;
+        D.nslots = S.nslots;
+        D.lr = S.lr;
+        D.threads = S.threads;
+        D.is_long = S.is_long;
+        T.is_long = T.is_long || S.is_long;
+        B.add(&D.phases, S.phases);
+        B.add(&D.recs, S.recs);
+        B.add(&D.lcode, S.lcode);
+        B.add(&D.lpat, S.lpat);
+        B.add(&D.pat, S.pat);
+        B.add(&D.lbase, S.lbase);
+        B.add(&D.base, S.base);
+        B.add(&D.baseslot, S.baseslot);
+        B.add(&D.wrow, S.wrow);
+        B.add(&D.colslot, S.colslot);
+        B.add(&D.patslot, S.patslot);
+        B.add(&D.hcode, S.hcode);
     }
-    if (e == hipSuccess)
-        e = upload((void **)&T.d_code, codes.data(), codes.size() * 2);
-    sm.code = T.d_code;
-    if (e == hipSuccess)
-        e = upload((void **)&T.d_model, &sm, sizeof(sm));
+    // one electron per site: C(Ns, N_up) = C(Ns, N_dn)
+    if (T.n[0] != T.n[1])
+        return fail(HUBBARD_ERR_STATE, "sector matrix is not square");
+    T.b0_pos = (size_t)T.b0_rank[1] * T.n[0] + T.b0_rank[0];
+    const hipError_t e = B.upload(&T.blob);
     if (e != hipSuccess)
         return fail(HUBBARD_ERR_DEVICE, std::string("uploading sector tables: ") +
                                             hipGetErrorString(e));
     return HUBBARD_OK;
 }
 
-// Each op's nxt links: the next HOP op of the list in forward and in reverse
-// order, wrapping around (-1: the list has none).
-void link_hops(std::vector<SecOp> &v)
+// Workgroups of a pass over spin col's rows, per vector: at most kGrid, and
+// no more than there are row groups.
+int rows_grid(const Tables &T, int col)
 {
-    const int n = (int)v.size();
-    for (int i = 0; i < n; ++i) {
-        v[i].nxt[0] = v[i].nxt[1] = -1;
-        for (int k = 1; k <= n && v[i].nxt[0] < 0; ++k)
-            if (v[(i + k) % n].kind == SOP_HOP)
-                v[i].nxt[0] = (i + k) % n;
-        for (int k = 1; k <= n && v[i].nxt[1] < 0; ++k)
-            if (v[(i - k + n) % n].kind == SOP_HOP)
-                v[i].nxt[1] = (i - k + n) % n;
-    }
+    const int ng = (T.n[1 - col] + (1 << T.sp[col].lr) - 1) >> T.sp[col].lr;
+    return std::min((ng + 7) / 8 * 8, kGrid);
 }
 
-void add_red(RowPass &p, SecOp &o)
+uint32_t rows_lds(const Tables &T, int col, int n_red)
 {
-    for (size_t s = 0; s < p.red_param.size(); ++s)
-        if (p.red_param[s] == o.param) {
-            o.red = (int)s;
-            return;
-        }
-    o.red = (int)p.red_param.size();
-    p.red_param.push_back(o.param);
+    const SpinTables &S = T.sp[col];
+    return row_lds(S.is_long ? long_vec_bytes(S.nslots) : short_vec_bytes(S.nslots, S.lr),
+                   1 << S.lr, T.n_phases, n_red, S.threads, T.general)
+        .total;
 }
 
 hubbard_status build_program(const Model &m, const Tables &T, int layers, Program &P)
 {
     const int per = m.params_per_layer();
-    auto hops = [&](int l, int spin, RowPass &p) {
-        for (int s = 1; s < per; ++s)
-            for (int k = 0; k < m.nb; ++k)
-                if (m.slot[k] == s) {
-                    SecOp o;
-                    std::memset(&o, 0, sizeof(o));
-                    o.kind = SOP_HOP;
-                    o.param = l * per + s;
-                    o.tab = T.tab[spin][k];
-                    o.t = m.t[k];
-                    add_red(p, o);
-                    p.ops.push_back(o);
-                }
-    };
-    int n_diag = 0;
-    auto diag = [&](int l, RowPass &p) {
-        SecOp o;
-        std::memset(&o, 0, sizeof(o));
-        o.kind = SOP_DIAG;
-        o.param = l * per;
-        o.tab = n_diag++;   // its phase table
-        add_red(p, o);
-        p.ops.push_back(o);
-    };
     P.fwd.clear();
     if (layers > 0) {
         RowPass cur;
-        cur.col = 0;
         for (int l = 0; l < layers; ++l) {
-            diag(l, cur);
-            hops(l, cur.col, cur);
-            RowPass nxt;
-            nxt.col = 1 - cur.col;
-            hops(l, nxt.col, nxt);
+            cur.l_diag = cur.l_post = l;
             P.fwd.push_back(cur);
-            cur = nxt;
+            const int other = 1 - cur.col;
+            cur = RowPass();
+            cur.col = other;
+            cur.l_pre = l;
         }
         P.fwd.push_back(cur);
     }
     for (RowPass &p : P.fwd) {
+        // in the order of the kernel's reduction slots
+        for (int s = 1; p.l_pre >= 0 && s < per; ++s)
+            p.red_param.push_back(p.l_pre * per + s);
+        if (p.l_diag >= 0)
+            p.red_param.push_back(p.l_diag * per);
+        for (int s = 1; p.l_post >= 0 && s < per; ++s)
+            p.red_param.push_back(p.l_post * per + s);
         if ((int)p.red_param.size() > kMaxRed)
             return fail(HUBBARD_ERR_ARG, "sector row pass with more than 16 parameters");
-        if (std::count_if(p.ops.begin(), p.ops.end(),
-                          [](const SecOp &o) { return o.kind == SOP_DIAG; }) > 1)
-            return fail(HUBBARD_ERR_ARG, "sector row pass with two diagonal ops");
-        link_hops(p.ops);
+        P.max_red = std::max(P.max_red, (int)p.red_param.size());
     }
     P.final_col = P.fwd.empty() ? 0 : P.fwd.back().col;
-    P.n_diag = n_diag;
-    // H: the final layout's spin hops and D, then the other spin's hops
-    std::vector<SecOp> all;
-    for (const RowPass &p : P.fwd) {
-        P.op_off.push_back((int)all.size());
-        all.insert(all.end(), p.ops.begin(), p.ops.end());
-    }
-    auto ham_ops = [&](int spin, bool with_d) {
-        std::vector<SecOp> v;
-        if (with_d) {
-            SecOp o;
-            std::memset(&o, 0, sizeof(o));
-            o.kind = SOP_DIAG;
-            o.param = -1;
-            o.tab = -1;
-            v.push_back(o);
-        }
-        for (int k = 0; k < m.nb; ++k) {
-            SecOp o;
-            std::memset(&o, 0, sizeof(o));
-            o.kind = SOP_HOP;
-            o.param = -1;
-            o.tab = T.tab[spin][k];
-            o.t = m.t[k];
-            v.push_back(o);
-        }
-        return v;
-    };
-    std::vector<SecOp> hx = ham_ops(P.final_col, true), hy = ham_ops(1 - P.final_col, false);
-    link_hops(hx);
-    link_hops(hy);
-    P.ham_x_off = (int)all.size();
-    P.ham_x_n = (int)hx.size();
-    all.insert(all.end(), hx.begin(), hx.end());
-    P.ham_y_off = (int)all.size();
-    P.ham_y_n = (int)hy.size();
-    all.insert(all.end(), hy.begin(), hy.end());
     // reduction rows, and the workgroups of the pass that writes each
-    auto grid_of = [&](int col) { return std::min(T.n[1 - col], kGrid); };
     P.n_rows = 2;
-    std::vector<int32_t> nblk{grid_of(P.final_col), grid_of(1 - P.final_col)};
+    std::vector<int32_t> nblk{rows_grid(T, P.final_col), rows_grid(T, 1 - P.final_col)};
     std::vector<std::vector<int>> rows_of(1 + layers * per);
     rows_of[0] = {0, 1};
     for (const RowPass &p : P.fwd) {
@@ -1141,7 +1380,7 @@ hubbard_status build_program(const Model &m, const Tables &T, int layers, Progra
         for (int half = 0; half < 2; ++half) {   // chi2, then chi1 (stored negated)
             for (size_t s = 0; s < p.red_param.size(); ++s) {
                 rows_of[1 + p.red_param[s]].push_back(P.n_rows + (int)s);
-                nblk.push_back(grid_of(p.col));
+                nblk.push_back(rows_grid(T, p.col));
             }
             P.n_rows += (int)p.red_param.size();
         }
@@ -1155,16 +1394,12 @@ hubbard_status build_program(const Model &m, const Tables &T, int layers, Progra
         scale.push_back(o == 0 ? 1.0 : 0.5);
     }
     P.n_out = (int)rows_of.size();
-    P.n_ops = (int)all.size();
-    hipError_t e = upload((void **)&P.d_ops, all.data(), all.size() * sizeof(SecOp));
-    if (e == hipSuccess)
-        e = upload((void **)&P.d_ptr, ptr.data(), ptr.size() * 4);
-    if (e == hipSuccess)
-        e = upload((void **)&P.d_rows, rows.data(), rows.size() * 4);
-    if (e == hipSuccess)
-        e = upload((void **)&P.d_scale, scale.data(), scale.size() * 8);
-    if (e == hipSuccess)
-        e = upload((void **)&P.d_nblk, nblk.data(), nblk.size() * 4);
+    Blob B;
+    B.add(&P.d_ptr, ptr);
+    B.add(&P.d_rows, rows);
+    B.add(&P.d_scale, scale);
+    B.add(&P.d_nblk, nblk);
+    const hipError_t e = B.upload(&P.blob);
     if (e != hipSuccess)
         return fail(HUBBARD_ERR_DEVICE, std::string("uploading the sector program: ") +
                                             hipGetErrorString(e));
@@ -1210,44 +1445,115 @@ hubbard_status get(hubbard_t h, int layers, Tables **T, Program **P)
 size_t vec_elems(const Tables &T) { return (size_t)T.n[0] * (size_t)T.n[1]; }
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Workgroup shape by row length: 1024 threads holding up to 13 elements of
-// each vector.  (At 13 elements, H -- two vectors -- and the general
-// diagonal's gate passes keep part of their tiles in scratch memory, about
-// 100 bytes per thread; 512 threads playing two tile threads each spilled
-// more.)
-template <int MODE, bool GEN>
-void launch_rows_g(const Tables &T, const SecOp *ops, int n_ops, int col, int n_red,
-                   const double2 *ang, const double2 *dph, double2 *v0, double2 *v1,
-                   double *partial, int row0, int flags, hipStream_t s)
+// Element strides of spin col's rows: short rows read the one layout (rows
+// r_dn, columns r_up) along either side.
+void strides(const Tables &T, int col, int64_t *rs, int64_t *cs)
 {
-    const int nr = T.n[1 - col], n = T.n[col];
-    const int grid = std::min(nr, kGrid);
-    const size_t lds = lds_bytes(T);
-#define HV_SEC(TT, R)                                                                           \
-    hipLaunchKernelGGL((k_sec_rows<MODE, TT, R, GEN>), dim3(grid), dim3(TT), lds, s, ops,       \
-                       n_ops, col, n_red, ang, dph, T.d_model, v0, v1, partial, row0, kGrid,    \
-                       flags, T.xch)
-    switch (rpt_of(n)) {   // the register tile the code tables are laid out for
-    case 1: HV_SEC(kT, 1); break;
-    case 2: HV_SEC(kT, 2); break;
-    case 4: HV_SEC(kT, 4); break;
-    case 8: HV_SEC(kT, 8); break;
-    default: HV_SEC(kT, 13); break;
-    }
-#undef HV_SEC
+    *rs = col == 0 || T.is_long ? T.n[col] : 1;
+    *cs = col == 0 || T.is_long ? 1 : T.n[0];
 }
 
 template <int MODE>
-void launch_rows(const Tables &T, const SecOp *ops, int n_ops, int col, int n_red,
-                 const double2 *ang, const double2 *dph, double2 *v0, double2 *v1,
+void launch_rows(const Tables &T, const RowPass &p, const double *theta, double2 *v0, double2 *v1,
                  double *partial, int row0, int flags, hipStream_t s)
 {
-    if (T.general)
-        launch_rows_g<MODE, true>(T, ops, n_ops, col, n_red, ang, dph, v0, v1, partial, row0,
-                                  flags, s);
-    else
-        launch_rows_g<MODE, false>(T, ops, n_ops, col, n_red, ang, dph, v0, v1, partial, row0,
-                                   flags, s);
+    const SpinTables &S = T.sp[p.col], &O = T.sp[1 - p.col];
+    RowsArgs A;
+    std::memset(&A, 0, sizeof(A));
+    A.phases = S.phases;
+    A.gates = T.d_gates;
+    A.recs = S.recs;
+    A.lcode = S.lcode;
+    A.lpat = S.lpat;
+    A.lbase = S.lbase;
+    A.colslot = S.colslot;
+    A.patslot = S.patslot;
+    A.baseslot = S.baseslot;
+    A.rpat = O.pat;
+    A.rbase = O.base;
+    A.wrow = O.wrow;
+    A.theta = theta;
+    A.U = T.U;
+    A.n = S.n;
+    A.n_rows = O.n;
+    A.nslots = S.nslots;
+    A.lr = S.lr;
+    A.n_phases = T.n_phases;
+    A.per = T.per;
+    A.l_pre = p.l_pre;
+    A.l_diag = p.l_diag;
+    A.l_post = p.l_post;
+    strides(T, p.col, &A.rs, &A.cs);
+    A.v[0] = v0;
+    A.v[1] = v1;
+    A.partial = partial;
+    A.n_red = MODE == S_REV ? (int)p.red_param.size() : 0;
+    A.row0[0] = row0;
+    A.row0[1] = row0 + A.n_red;
+    A.pstride = kGrid;
+    A.flags = flags;
+    A.b0_row = T.b0_rank[1 - p.col];
+    A.b0_col = T.b0_rank[p.col];
+    const dim3 grid(rows_grid(T, p.col), MODE == S_REV ? 2 : 1);
+    const uint32_t lds = rows_lds(T, p.col, A.n_red);
+    if (S.is_long) {
+        if (T.general)
+            hipLaunchKernelGGL((k_sec_rows_long<MODE, true>), grid, dim3(kLongT), lds, s, A);
+        else
+            hipLaunchKernelGGL((k_sec_rows_long<MODE, false>), grid, dim3(kLongT), lds, s, A);
+    } else {
+        if (T.general)
+            hipLaunchKernelGGL((k_sec_rows_short<MODE, true>), grid, dim3(S.threads), lds, s, A);
+        else
+            hipLaunchKernelGGL((k_sec_rows_short<MODE, false>), grid, dim3(S.threads), lds, s, A);
+    }
+}
+
+// spin col's part of H (with_d: and the diagonal) on psi.
+void launch_ham(const Tables &T, int col, bool with_d, double2 *psi, double2 *out, int out_mode,
+                double *partial, hipStream_t s)
+{
+    const SpinTables &S = T.sp[col], &O = T.sp[1 - col];
+    HamArgs A;
+    std::memset(&A, 0, sizeof(A));
+    A.colslot = S.colslot;
+    A.patslot = S.patslot;
+    A.hcode = S.hcode;
+    A.baseslot = S.baseslot;
+    A.rpat = O.pat;
+    A.rbase = O.base;
+    A.wrow = O.wrow;
+    A.tb = T.d_tb;
+    A.U = T.U;
+    A.n = S.n;
+    A.n_rows = O.n;
+    A.nslots = S.nslots;
+    A.lr = S.lr;
+    A.nb = T.nb;
+    A.diag = with_d ? 1 : 0;
+    A.out_mode = out_mode;
+    strides(T, col, &A.rs, &A.cs);
+    A.psi = psi;
+    A.out = out;
+    A.partial = partial;
+    const dim3 grid(rows_grid(T, col));
+    if (S.is_long) {
+        const uint32_t lds = long_vec_bytes(S.nslots) + 64u * 8u + 16u * 8u;
+        if (T.general)
+            hipLaunchKernelGGL((k_sec_ham_long<true>), grid, dim3(kLongT), lds, s, A);
+        else
+            hipLaunchKernelGGL((k_sec_ham_long<false>), grid, dim3(kLongT), lds, s, A);
+    } else {
+        // an element per thread and round; no orbit lists here
+        const int want = ((S.n << S.lr) + 63) / 64 * 64;
+        const dim3 th((unsigned)std::min(1024, want));
+        const uint32_t lds = short_vec_bytes(S.nslots, S.lr) +
+                             (T.general ? (64u << S.lr) * 8u : 0u) + 16u * 8u;
+        if (T.general)
+            hipLaunchKernelGGL((k_sec_ham_short<true>), grid, th, lds, s, A);
+        else
+            hipLaunchKernelGGL((k_sec_ham_short<false>), grid, th, lds, s, A);
+    }
 }
 
 void transpose(const Tables &T, int from_col, const double2 *in, double2 *out, bool add,
@@ -1263,85 +1569,58 @@ void set_attrs()
     static std::once_flag once;
     std::call_once(once, [] {
         const void *fns[] = {
-#define HV_SEC_FNS(MODE, GEN)                                                                   \
-    (const void *)k_sec_rows<MODE, kT, 1, GEN>, (const void *)k_sec_rows<MODE, kT, 2, GEN>,     \
-        (const void *)k_sec_rows<MODE, kT, 4, GEN>, (const void *)k_sec_rows<MODE, kT, 8, GEN>, \
-        (const void *)k_sec_rows<MODE, kT, 13, GEN>
-            HV_SEC_FNS(S_FWD, false), HV_SEC_FNS(S_REV, false), HV_SEC_FNS(S_HAM, false),
-            HV_SEC_FNS(S_FWD, true), HV_SEC_FNS(S_REV, true), HV_SEC_FNS(S_HAM, true)};
-#undef HV_SEC_FNS
+            (const void *)k_sec_rows_short<S_FWD, false>, (const void *)k_sec_rows_short<S_FWD, true>,
+            (const void *)k_sec_rows_short<S_REV, false>, (const void *)k_sec_rows_short<S_REV, true>,
+            (const void *)k_sec_rows_long<S_FWD, false>,  (const void *)k_sec_rows_long<S_FWD, true>,
+            (const void *)k_sec_rows_long<S_REV, false>,  (const void *)k_sec_rows_long<S_REV, true>,
+            (const void *)k_sec_ham_short<false>,         (const void *)k_sec_ham_short<true>,
+            (const void *)k_sec_ham_long<false>,          (const void *)k_sec_ham_long<true>};
         for (const void *f : fns)
             (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
 }
 
-double2 *dph_of(const Program &P, double2 *ang)
-{
-    return (double2 *)((char *)ang + align256((size_t)P.n_ops * 16));
-}
-
-// Angles of every op, then the diagonal phase tables.
-size_t ang_bytes(const Program &P)
-{
-    return align256((size_t)P.n_ops * 16) + align256((size_t)P.n_diag * kDiagTab * 16);
-}
-
-// ang[i] for every op of the program and dph (see k_sec_angles); dph follows ang.
-void angles(const Tables &T, const Program &P, const double *theta, double2 *ang, hipStream_t s)
-{
-    const int blocks = std::max(1, std::min(64, (P.n_ops + 255) / 256));
-    hipLaunchKernelGGL(k_sec_angles, dim3(blocks), dim3(256), 0, s, P.d_ops, P.n_ops, theta, T.U,
-                       ang, dph_of(P, ang));
-}
-
-// Forward sweep: psi starts in layout A in `a`; `b` is the layout-B buffer.
-// Returns the buffer holding the result (in layout P.final_col).
-double2 *forward(const Tables &T, const Program &P, const double2 *ang, double2 *a, double2 *b,
-                 hipStream_t s)
+// Forward sweep: psi starts in layout A in `a` (from_start: it is |b0>, and
+// `a` is not read); `b` is the layout-B buffer of long rows.  Returns the
+// buffer holding the result (long rows: in layout P.final_col).
+double2 *forward(const Tables &T, const Program &P, const double *theta, double2 *a, double2 *b,
+                 bool from_start, hipStream_t s)
 {
     double2 *cur = a;
     int col = 0;
     for (size_t i = 0; i < P.fwd.size(); ++i) {
         const RowPass &p = P.fwd[i];
-        if (p.col != col) {
+        if (T.is_long && p.col != col) {
             double2 *dst = (cur == a) ? b : a;
             transpose(T, col, cur, dst, false, s);
             cur = dst;
             col = p.col;
         }
-        launch_rows<S_FWD>(T, P.d_ops + P.op_off[i], (int)p.ops.size(), p.col, 0,
-                           ang + P.op_off[i], dph_of(P, (double2 *)ang), cur, nullptr, nullptr,
-                           0, 0, s);
+        launch_rows<S_FWD>(T, p, theta, cur, nullptr, nullptr, 0,
+                           from_start && i == 0 ? SF_START : 0, s);
     }
     return cur;
 }
 
-// phi_x <- H psi_x for psi_x in layout `col` (x): the col-spin hops and D in
-// layout x, the other spin's hops in the transposed layout; psi_y, phi_y are
-// scratch of the other layout.  Energy parts to partial rows 0 and 1.
-void hamiltonian(const Tables &T, const Program &P, int col, const double2 *psi_x,
-                 double2 *phi_x, double2 *psi_y, double2 *phi_y, double *partial, hipStream_t s,
-                 const SecOp *ops_x, int n_x, const SecOp *ops_y, int n_y)
+// out <- H in for sector vectors in layout `col` (long rows; short ones have
+// one layout): spin col's hops and D, then the other spin's -- long rows: in
+// the transposed layout through in_y, out_y.  mix: out <- lambda - i psi and
+// in <- lambda + i psi of lambda = H psi instead.  Energy parts to partial
+// rows 0 and 1 (partial != NULL).
+void hamiltonian(const Tables &T, int col, double2 *in, double2 *out, double2 *in_y,
+                 double2 *out_y, bool mix, double *partial, hipStream_t s)
 {
-    launch_rows<S_HAM>(T, ops_x, n_x, col, 1, nullptr, nullptr, (double2 *)psi_x, phi_x,
-                       partial, 0, 0, s);
-    transpose(T, col, psi_x, psi_y, false, s);
-    launch_rows<S_HAM>(T, ops_y, n_y, 1 - col, 1, nullptr, nullptr, psi_y, phi_y, partial, 1, 0,
-                       s);
-    transpose(T, 1 - col, phi_y, phi_x, true, s);
-}
-
-// out <- H in for sector vectors in layout A (the 0-layer program's H ops:
-// up hops and D in layout A, down hops in layout B through in_b, out_b).
-void apply_h(const Tables &T, const Program &P, const double2 *in, double2 *out, double2 *in_b,
-             double2 *out_b, hipStream_t s)
-{
-    launch_rows<S_HAM>(T, P.d_ops + P.ham_x_off, P.ham_x_n, 0, 0, nullptr, nullptr,
-                       (double2 *)in, out, nullptr, 0, 0, s);
-    transpose(T, 0, in, in_b, false, s);
-    launch_rows<S_HAM>(T, P.d_ops + P.ham_y_off, P.ham_y_n, 1, 0, nullptr, nullptr, in_b, out_b,
-                       nullptr, 0, 0, s);
-    transpose(T, 1, out_b, out, true, s);
+    launch_ham(T, col, true, in, out, HO_SET, partial, s);
+    double *p1 = partial ? partial + kGrid : nullptr;
+    if (!T.is_long) {
+        launch_ham(T, 1 - col, false, in, out, mix ? HO_MIX : HO_ADD, p1, s);
+        return;
+    }
+    transpose(T, col, in, in_y, false, s);
+    launch_ham(T, 1 - col, false, in_y, out_y, HO_SET, p1, s);
+    transpose(T, 1 - col, out_y, out, true, s);
+    if (mix)
+        hipLaunchKernelGGL(k_sec_mix, dim3(2048), dim3(256), 0, s, in, out, vec_elems(T));
 }
 
 hubbard_status check(const char *what)
@@ -1350,6 +1629,14 @@ hubbard_status check(const char *what)
     if (e != hipSuccess)
         return fail(HUBBARD_ERR_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
     return HUBBARD_OK;
+}
+
+// Angles of every op and diagonal phase tables were once kept in the
+// workspace; callers' sizes stay what they were.
+size_t ang_bytes(const Tables &T, int layers)
+{
+    return align256((size_t)(2 * T.nb + 1) * (layers + 1) * 16) +
+           align256((size_t)layers * kDiagTab * 16);
 }
 
 }  // namespace sec
@@ -1393,13 +1680,13 @@ hubbard_status hubbard_sector_workspace_size(hubbard_t h, int32_t n_layers, int3
         return st;
     const size_t v = align256(vec_elems(*T) * 16);
     if (op == HUBBARD_SECTOR_ANSATZ)
-        *bytes = v + ang_bytes(*P);
+        *bytes = v + ang_bytes(*T, n_layers);
     else if (op == HUBBARD_SECTOR_HAMILTONIAN)
         *bytes = 2 * v;
     else if (op == HUBBARD_SECTOR_LANCZOS)
         *bytes = 5 * v + lanczos_partial_bytes();
     else
-        *bytes = 4 * v + align256((size_t)P->n_rows * kGrid * 8) + ang_bytes(*P);
+        *bytes = 4 * v + align256((size_t)P->n_rows * kGrid * 8) + ang_bytes(*T, n_layers);
     return HUBBARD_OK;
 }
 
@@ -1427,14 +1714,11 @@ hubbard_status sector_ansatz_apply(hubbard_t h, const double *theta_dev, int32_t
     if (st != HUBBARD_OK)
         return st;
     const size_t v = align256(vec_elems(*T) * 16);
-    if (!ws_dev || ws_bytes < v + ang_bytes(*P))
+    if (!ws_dev || ws_bytes < v + ang_bytes(*T, n_layers))
         return set_error(HUBBARD_ERR_SIZE, "workspace too small for sector_ansatz_apply");
     set_attrs();
     hipStream_t s = (hipStream_t)stream;
-    double2 *ang = (double2 *)((char *)ws_dev + v);
-    if (n_layers > 0)
-        angles(*T, *P, theta_dev, ang, s);
-    double2 *out = forward(*T, *P, ang, (double2 *)psi_dev, (double2 *)ws_dev, s);
+    double2 *out = forward(*T, *P, theta_dev, (double2 *)psi_dev, (double2 *)ws_dev, false, s);
     if (out != (double2 *)psi_dev)   // ended in layout B
         transpose(*T, 1, out, (double2 *)psi_dev, false, s);
     return check("sector ansatz");
@@ -1455,8 +1739,8 @@ hubbard_status sector_hamiltonian_apply(hubbard_t h, const void *psi_dev, void *
         return set_error(HUBBARD_ERR_SIZE, "workspace too small for sector_hamiltonian_apply");
     set_attrs();
     char *w = (char *)ws_dev;
-    apply_h(*T, *P, (const double2 *)psi_dev, (double2 *)out_dev, (double2 *)w,
-            (double2 *)(w + v), (hipStream_t)stream);
+    hamiltonian(*T, 0, (double2 *)psi_dev, (double2 *)out_dev, (double2 *)w, (double2 *)(w + v),
+                false, nullptr, (hipStream_t)stream);
     return check("sector H");
 }
 
@@ -1487,7 +1771,7 @@ hubbard_status hubbard_sector_lanczos(hubbard_t h, const void *start_dev, int32_
     double2 *buf[3] = {(double2 *)w, (double2 *)(w + v), (double2 *)(w + 2 * v)};
     double2 *in_b = (double2 *)(w + 3 * v), *out_b = (double2 *)(w + 4 * v);
     const ApplyH apply = [&](const double2 *in, double2 *out) {
-        apply_h(*T, *P, in, out, in_b, out_b, s);
+        hamiltonian(*T, 0, (double2 *)in, out, in_b, out_b, false, nullptr, s);
         return check("sector H");
     };
     return lanczos_run(apply, n, (const double2 *)start_dev, max_iter, tol, E0, iters, residual,
@@ -1507,46 +1791,38 @@ hubbard_status sector_energy_grad(hubbard_t h, const double *theta_dev, int32_t 
         return st;
     const size_t v = align256(vec_elems(*T) * 16);
     const size_t pbytes = align256((size_t)P->n_rows * kGrid * 8);
-    if (!ws_dev || ws_bytes < 4 * v + pbytes + ang_bytes(*P))
+    if (!ws_dev || ws_bytes < 4 * v + pbytes + ang_bytes(*T, n_layers))
         return set_error(HUBBARD_ERR_SIZE, "workspace too small for sector_energy_grad");
     set_attrs();
     hipStream_t s = (hipStream_t)stream;
     char *w = (char *)ws_dev;
+    // the two layouts' buffers (short rows: one layout, index 0)
     double2 *psi[2] = {(double2 *)w, (double2 *)(w + v)};
     double2 *lam[2] = {(double2 *)(w + 2 * v), (double2 *)(w + 3 * v)};
     double *partial = (double *)(w + 4 * v);
-    double2 *ang = (double2 *)(w + 4 * v + pbytes);
-    if (n_layers > 0)
-        angles(*T, *P, theta_dev, ang, s);
-    hipLaunchKernelGGL(k_sec_basis, dim3(2048), dim3(256), 0, s, psi[0], vec_elems(*T),
-                       T->b0_pos);
-    double2 *end = forward(*T, *P, ang, psi[0], psi[1], s);
+    auto at = [&](int col) { return T->is_long ? col : 0; };
+    if (P->fwd.empty())
+        hipLaunchKernelGGL(k_sec_basis, dim3(2048), dim3(256), 0, s, psi[0], vec_elems(*T),
+                           T->b0_pos);
+    double2 *end = forward(*T, *P, theta_dev, psi[0], psi[1], true, s);
     int col = P->final_col;
-    if (end != psi[col]) {   // cannot happen: layout A lives in psi[0], B in psi[1]
+    if (end != psi[at(col)]) {   // cannot happen: layout A lives in psi[0], B in psi[1]
         return set_error(HUBBARD_ERR_STATE, "sector forward ended in the wrong buffer");
     }
-    // lambda = H psi in the final layout; the partial rows 0 and 1 get E
-    hamiltonian(*T, *P, col, psi[col], lam[col], psi[1 - col], lam[1 - col], partial, s,
-                P->d_ops + P->ham_x_off, P->ham_x_n, P->d_ops + P->ham_y_off, P->ham_y_n);
-    // reverse sweep on chi1 = lambda + i psi (psi's buffers) and chi2 =
-    // lambda - i psi (lambda's): brackets from their expectations
-    if (!P->fwd.empty())
-        hipLaunchKernelGGL(k_sec_mix, dim3(2048), dim3(256), 0, s, psi[col], lam[col],
-                           vec_elems(*T));
+    // lambda = H psi, the partial rows 0 and 1 get E; the reverse sweep runs
+    // on chi1 = lambda + i psi (psi's buffers) and chi2 = lambda - i psi
+    // (lambda's): brackets from their expectations
+    hamiltonian(*T, col, psi[at(col)], lam[at(col)], psi[at(1 - col)], lam[at(1 - col)],
+                !P->fwd.empty(), partial, s);
     for (int i = (int)P->fwd.size() - 1; i >= 0; --i) {
         const RowPass &p = P->fwd[i];
-        if (p.col != col) {
+        if (T->is_long && p.col != col) {
             transpose(*T, col, psi[col], psi[p.col], false, s);
             transpose(*T, col, lam[col], lam[p.col], false, s);
-            col = p.col;
         }
-        const int nred = (int)p.red_param.size(), last = i == 0 ? SF_NO_STORE : 0;
-        launch_rows<S_REV>(*T, P->d_ops + P->op_off[i], (int)p.ops.size(), p.col, nred,
-                           ang + P->op_off[i], dph_of(*P, ang), lam[col], nullptr, partial,
-                           P->red_row0[i], last, s);
-        launch_rows<S_REV>(*T, P->d_ops + P->op_off[i], (int)p.ops.size(), p.col, nred,
-                           ang + P->op_off[i], dph_of(*P, ang), psi[col], nullptr, partial,
-                           P->red_row0[i] + nred, last | SF_NEGATE, s);
+        col = p.col;
+        launch_rows<S_REV>(*T, p, theta_dev, lam[at(col)], psi[at(col)], partial, P->red_row0[i],
+                           i == 0 ? SF_NO_STORE : 0, s);
     }
     hipLaunchKernelGGL(k_sec_reduce, dim3(P->n_out), dim3(256), 0, s, partial, kGrid,
                        P->d_nblk, P->d_ptr, P->d_rows, P->d_scale, E_dev, grad_dev);
