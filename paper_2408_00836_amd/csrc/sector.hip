@@ -66,7 +66,9 @@ constexpr int kMaxRed = 16;               // reduction slots of one row pass
 constexpr int kGrid = 1024;               // at most this many workgroups write partials
 
 enum { S_FWD = 0, S_REV = 1 };
-enum { SF_NO_STORE = 1, SF_START = 2 };
+// SF_TURN (long rows): the result goes, transposed, to the other layout's
+// buffer; with SF_BOTH also to its own place.
+enum { SF_NO_STORE = 1, SF_START = 2, SF_TURN = 4, SF_BOTH = 8 };
 // What a pass of H does with its part phi of H psi: out <- phi, out <- out +
 // phi, or lambda = out + phi and then psi <- lambda + i psi, out <- lambda -
 // i psi (the reverse sweep's two vectors).
@@ -106,6 +108,7 @@ struct RowsArgs {
                                  // diagonal and of the hops after it (-1: none)
     int64_t rs, cs;              // element (row, col) at row rs + col cs
     double2 *v[2];
+    double2 *t[2];               // long rows, SF_TURN: the transposed result
     double *partial;
     int row0[2];                 // first partial row of each vector
     int n_red, pstride, flags;
@@ -653,18 +656,30 @@ __global__ void __launch_bounds__(1024) k_sec_rows_short(RowsArgs A)
 // vectors 7.72 ms (18.6 ms).
 struct LongCodes {
     uint32_t w[8];
-    // the offsets derived from here on are computed anew: kept from an earlier
-    // use, they would take a register each
+    // LDS byte offset of element j
+    __device__ __forceinline__ uint32_t at(int j) const
+    {
+        return j & 1 ? (w[j >> 1] >> 13) & 0x7FFF8u : (w[j >> 1] << 3) & 0x7FFF8u;
+    }
     __device__ __forceinline__ void renew()
     {
 #pragma unroll
         for (int k = 0; k < 8; ++k)
             asm volatile("" : "+v"(w[k]));
     }
-    // LDS byte offset of element j
-    __device__ __forceinline__ uint32_t at(int j) const
+};
+
+// LDS byte offsets of a layout's N elements, unpacked once for the real and
+// the imaginary parts (kept through the hops instead, they spilled).
+template <int N> struct LongAddr {
+    uint32_t a[N];
+    __device__ __forceinline__ explicit LongAddr(const LongCodes &c)
     {
-        return j & 1 ? (w[j >> 1] >> 13) & 0x7FFF8u : (w[j >> 1] << 3) & 0x7FFF8u;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            a[j] = c.at(j);
+            asm volatile("" : "+v"(a[j]));
+        }
     }
 };
 
@@ -705,28 +720,29 @@ __device__ __forceinline__ LongCodes col_codes(const uint16_t *colslot, int t)
 
 // Move a row from one register layout to another through LDS.
 template <int NF, int NTO>
-__device__ __forceinline__ void long_exchange(const double2 (&from)[NF], LongCodes cf,
-                                              double2 (&to)[NTO], LongCodes ct, char *buf)
+__device__ __forceinline__ void long_exchange(const double2 (&from)[NF], const LongCodes &fcodes,
+                                              double2 (&to)[NTO], const LongCodes &tcodes,
+                                              char *buf)
 {
     double re[NTO];
+    const LongAddr<NF> cf(fcodes);
     __syncthreads();   // the last exchange's reads are done
 #pragma unroll
     for (int j = 0; j < NF; ++j)
-        *(double *)(buf + cf.at(j)) = from[j].x;
+        *(double *)(buf + cf.a[j]) = from[j].x;
+    const LongAddr<NTO> ct(tcodes);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < NTO; ++j)
-        re[j] = *(const double *)(buf + ct.at(j));
-    cf.renew();
-    ct.renew();
+        re[j] = *(const double *)(buf + ct.a[j]);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < NF; ++j)
-        *(double *)(buf + cf.at(j)) = from[j].y;
+        *(double *)(buf + cf.a[j]) = from[j].y;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < NTO; ++j)
-        to[j] = make_double2(re[j], *(const double *)(buf + ct.at(j)));
+        to[j] = make_double2(re[j], *(const double *)(buf + ct.a[j]));
 }
 
 template <int MODE, bool GEN>
@@ -752,16 +768,28 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
     const uint32_t n = (uint32_t)A.n;
     auto ph_of = [&](int st) { return st < A.n_phases ? st : st - A.n_phases; };
 
-    for (int r = blockIdx.x; r < A.n_rows; r += gridDim.x) {
+    for (int ig = blockIdx.x; ig < (A.n_rows + 7) / 8 * 8; ig += gridDim.x) {
+        const int r = group_of(ig, A.n_rows);
+        if (r < 0)
+            continue;
         gc128 *__restrict__ row = (gc128 *)A.v[vsel] + (size_t)r * n;
         const bool start = !REV && (A.flags & SF_START);
+        auto put = [&](uint32_t i, double2 v) __attribute__((always_inline)) {
+            if (!(A.flags & SF_TURN) || (A.flags & SF_BOTH)) {
+                row[i].x = v.x;
+                row[i].y = v.y;
+            }
+            if (A.flags & SF_TURN) {
+                gc128 *p = (gc128 *)A.t[vsel] + (size_t)i * A.n_rows + r;
+                p->x = v.x;
+                p->y = v.y;
+            }
+        };
         uint32_t t = (uint32_t)tid;   // per-row addresses are not kept across rows
         asm volatile("" : "+v"(t));
         if (start && r != A.b0_row) {
-            for (uint32_t i = t; i < n; i += kLongT) {
-                row[i].x = 0.0;
-                row[i].y = 0.0;
-            }
+            for (uint32_t i = t; i < n; i += kLongT)
+                put(i, make_double2(0.0, 0.0));
             continue;
         }
         double2 x[kOrbitElems];
@@ -818,23 +846,23 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
             const kPhase &ph = phases[ph_of(st)];
             if (!REV && st == n_pre && A.l_diag >= 0)
                 diag();
-            // the next step's layout is fetched while this one's hops run
-            const int nx = min(k + 1, n_steps - 1), pn = ph_of(REV ? n_steps - 1 - nx : nx);
-            uint32_t tn = (uint32_t)tid;
-            asm volatile("" : "+v"(tn));
-            const LongCodes nxt = long_codes(lcode + ((size_t)pn * kLongT + tn) * 2);
             const uint32_t f = cur.w[7];
             C.gates(x, st < n_pre ? 0 : 1, ph_of(st), f, f, f, wave0 < ph.n[0],
                     wave0 < ph.n[1] || wave0 < ph.n[2]);
             if (REV && st == n_pre && A.l_diag >= 0)
                 diag();
             if (k + 1 < n_steps) {
+                // the next layout: wanted once the real parts are written
+                const int pn = ph_of(REV ? st - 1 : st + 1);
+                uint32_t tn = (uint32_t)tid;
+                asm volatile("" : "+v"(tn));
+                const LongCodes nxt = long_codes(lcode + ((size_t)pn * kLongT + tn) * 2);
                 double2 y[kOrbitElems];
                 long_exchange(x, cur, y, nxt, smem);
+                cur = nxt;
 #pragma unroll
                 for (int j = 0; j < kOrbitElems; ++j)
                     x[j] = y[j];
-                cur = nxt;
             }
         }
         if (!(A.flags & SF_NO_STORE)) {
@@ -845,10 +873,8 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
 #pragma unroll
             for (int j = 0; j < kLongElems; ++j) {
                 const uint32_t i = ts + (uint32_t)(j * kLongT);
-                if (i < n) {
-                    row[i].x = out[j].x;
-                    row[i].y = out[j].y;
-                }
+                if (i < n)
+                    put(i, out[j]);
             }
         }
     }
@@ -869,7 +895,7 @@ struct HamArgs {
     const uint32_t *rpat;
     const double *rbase, *wrow, *tb;   // tb: -t_b per bond, padded with zeros
     double U;
-    int n, n_rows, nslots, lr, nb, diag, out_mode;
+    int n, n_rows, nslots, lr, nb, diag, out_mode, turn;   // turn (long rows): out is transposed
     int64_t rs, cs;
     double2 *psi, *out;
     double *partial;                   // NULL: no energy
@@ -999,8 +1025,11 @@ __global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
     for (int i = tid; i < A.nslots + kLongDummy; i += kLongT)   // the holes and the zero slots
         buf[i] = 0.0;
     double e = 0.0;
-    for (int r = blockIdx.x; r < A.n_rows; r += gridDim.x) {
-        gc128 *psi = (gc128 *)A.psi + (size_t)r * n, *out = (gc128 *)A.out + (size_t)r * n;
+    for (int ig = blockIdx.x; ig < (A.n_rows + 7) / 8 * 8; ig += gridDim.x) {
+        const int r = group_of(ig, A.n_rows);
+        if (r < 0)
+            continue;
+        gc128 *psi = (gc128 *)A.psi + (size_t)r * n;
         const uint32_t rp = rpat[r];
         const double rb = GEN ? rbase[r] : 0.0;
         int t = tid;   // the tables' values are not kept across rows
@@ -1080,8 +1109,12 @@ __global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
                     if (i < n) {
                         const double2 f = make_double2(re_out[j],
                                                        *(const double *)(smem + cc.at(j)));
-                        out[i].x = f.x;
-                        out[i].y = f.y;
+                        gc128 *o = (gc128 *)A.out +
+                                   (A.turn ? (size_t)i * A.n_rows + r : (size_t)r * n + i);
+                        double2 own = make_double2(0.0, 0.0);
+                        if (A.out_mode == HO_MIX)
+                            own = make_double2(psi[i].x, psi[i].y);
+                        ham_store(A.out_mode, o, psi + i, f, own);
                     }
                 }
             }
@@ -1101,24 +1134,12 @@ __global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
     }
 }
 
-// chi1 <- lambda + i psi in psi's place, chi2 <- lambda - i psi in lambda's.
-__global__ void __launch_bounds__(256)
-k_sec_mix(double2 *__restrict__ psi, double2 *__restrict__ lam, size_t n)
-{
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (size_t)gridDim.x * blockDim.x) {
-        const double2 p = psi[i], l = lam[i];
-        psi[i] = make_double2(l.x - p.y, l.y + p.x);
-        lam[i] = make_double2(l.x + p.y, l.y - p.x);
-    }
-}
-
-// out[c nr + r] = in[r nc + c] (add: out += that), through 64 x 64 LDS tiles
+// out[c nr + r] = in[r nc + c], through 64 x 64 LDS tiles
 // (1 KB row segments; 32 x 32 tiles reached 3.7 TB/s at 12870 x 12870, these
 // 4.6 TB/s).
 constexpr int kTrTile = 64, kTrThreads = 512;
 __global__ void __launch_bounds__(kTrThreads)
-k_sec_transpose(const double2 *__restrict__ in, double2 *__restrict__ out, int nr, int nc, int add)
+k_sec_transpose(const double2 *__restrict__ in, double2 *__restrict__ out, int nr, int nc)
 {
     constexpr int RW = kTrThreads / kTrTile;   // tile rows per sweep of the threads
     __shared__ double2 tile[kTrTile][kTrTile + 1];
@@ -1133,14 +1154,7 @@ k_sec_transpose(const double2 *__restrict__ in, double2 *__restrict__ out, int n
     for (int k = ty; k < kTrTile; k += RW) {
         const int c = c0 + k, r = r0 + tx;
         if (r < nr && c < nc) {
-            double2 v = tile[tx][k];
-            double2 *o = out + (size_t)c * nr + r;
-            if (add) {
-                const double2 w = *o;
-                v.x += w.x;
-                v.y += w.y;
-            }
-            *o = v;
+            out[(size_t)c * nr + r] = tile[tx][k];
         }
     }
 }
@@ -1329,6 +1343,8 @@ hubbard_status build_tables(const Model &m, Tables &T)
 // no more than there are row groups.
 int rows_grid(const Tables &T, int col)
 {
+    if (T.is_long)   // one workgroup per CU
+        return 256;
     const int ng = (T.n[1 - col] + (1 << T.sp[col].lr) - 1) >> T.sp[col].lr;
     return std::min((ng + 7) / 8 * 8, kGrid);
 }
@@ -1455,7 +1471,8 @@ void strides(const Tables &T, int col, int64_t *rs, int64_t *cs)
 
 template <int MODE>
 void launch_rows(const Tables &T, const RowPass &p, const double *theta, double2 *v0, double2 *v1,
-                 double *partial, int row0, int flags, hipStream_t s)
+                 double *partial, int row0, int flags, hipStream_t s, double2 *t0 = nullptr,
+                 double2 *t1 = nullptr)
 {
     const SpinTables &S = T.sp[p.col], &O = T.sp[1 - p.col];
     RowsArgs A;
@@ -1486,6 +1503,8 @@ void launch_rows(const Tables &T, const RowPass &p, const double *theta, double2
     strides(T, p.col, &A.rs, &A.cs);
     A.v[0] = v0;
     A.v[1] = v1;
+    A.t[0] = t0;
+    A.t[1] = t1;
     A.partial = partial;
     A.n_red = MODE == S_REV ? (int)p.red_param.size() : 0;
     A.row0[0] = row0;
@@ -1511,7 +1530,7 @@ void launch_rows(const Tables &T, const RowPass &p, const double *theta, double2
 
 // spin col's part of H (with_d: and the diagonal) on psi.
 void launch_ham(const Tables &T, int col, bool with_d, double2 *psi, double2 *out, int out_mode,
-                double *partial, hipStream_t s)
+                bool turn, double *partial, hipStream_t s)
 {
     const SpinTables &S = T.sp[col], &O = T.sp[1 - col];
     HamArgs A;
@@ -1532,6 +1551,7 @@ void launch_ham(const Tables &T, int col, bool with_d, double2 *psi, double2 *ou
     A.nb = T.nb;
     A.diag = with_d ? 1 : 0;
     A.out_mode = out_mode;
+    A.turn = turn ? 1 : 0;
     strides(T, col, &A.rs, &A.cs);
     A.psi = psi;
     A.out = out;
@@ -1556,12 +1576,11 @@ void launch_ham(const Tables &T, int col, bool with_d, double2 *psi, double2 *ou
     }
 }
 
-void transpose(const Tables &T, int from_col, const double2 *in, double2 *out, bool add,
-               hipStream_t s)
+void transpose(const Tables &T, int from_col, const double2 *in, double2 *out, hipStream_t s)
 {
     const int nr = T.n[1 - from_col], nc = T.n[from_col];
     hipLaunchKernelGGL(k_sec_transpose, dim3((nc + kTrTile - 1) / kTrTile, (nr + kTrTile - 1) / kTrTile),
-                       dim3(kTrThreads), 0, s, in, out, nr, nc, add ? 1 : 0);
+                       dim3(kTrThreads), 0, s, in, out, nr, nc);
 }
 
 void set_attrs()
@@ -1582,45 +1601,36 @@ void set_attrs()
 
 // Forward sweep: psi starts in layout A in `a` (from_start: it is |b0>, and
 // `a` is not read); `b` is the layout-B buffer of long rows.  Returns the
-// buffer holding the result (long rows: in layout P.final_col).
+// buffer holding the result (long rows: in layout P.final_col; both: in both
+// layouts).
 double2 *forward(const Tables &T, const Program &P, const double *theta, double2 *a, double2 *b,
-                 bool from_start, hipStream_t s)
+                 bool from_start, bool both, hipStream_t s)
 {
     double2 *cur = a;
-    int col = 0;
     for (size_t i = 0; i < P.fwd.size(); ++i) {
-        const RowPass &p = P.fwd[i];
-        if (T.is_long && p.col != col) {
-            double2 *dst = (cur == a) ? b : a;
-            transpose(T, col, cur, dst, false, s);
-            cur = dst;
-            col = p.col;
-        }
-        launch_rows<S_FWD>(T, p, theta, cur, nullptr, nullptr, 0,
-                           from_start && i == 0 ? SF_START : 0, s);
+        const bool last = i + 1 == P.fwd.size();
+        double2 *other = (cur == a) ? b : a;
+        int flags = from_start && i == 0 ? SF_START : 0;
+        if (T.is_long && (!last || both))
+            flags |= SF_TURN | (last ? SF_BOTH : 0);
+        launch_rows<S_FWD>(T, P.fwd[i], theta, cur, nullptr, nullptr, 0, flags, s, other);
+        if (T.is_long && !last)
+            cur = other;
     }
     return cur;
 }
 
 // out <- H in for sector vectors in layout `col` (long rows; short ones have
-// one layout): spin col's hops and D, then the other spin's -- long rows: in
-// the transposed layout through in_y, out_y.  mix: out <- lambda - i psi and
-// in <- lambda + i psi of lambda = H psi instead.  Energy parts to partial
-// rows 0 and 1 (partial != NULL).
-void hamiltonian(const Tables &T, int col, double2 *in, double2 *out, double2 *in_y,
-                 double2 *out_y, bool mix, double *partial, hipStream_t s)
+// one layout).  Long rows: in_y is `in` in the other layout, where the other
+// spin's hops act; their part comes back transposed.  mix: out <- lambda - i
+// psi and in <- lambda + i psi of lambda = H psi instead.  Energy parts to
+// partial rows 0 and 1 (partial != NULL).
+void hamiltonian(const Tables &T, int col, double2 *in, double2 *out, double2 *in_y, bool mix,
+                 double *partial, hipStream_t s)
 {
-    launch_ham(T, col, true, in, out, HO_SET, partial, s);
     double *p1 = partial ? partial + kGrid : nullptr;
-    if (!T.is_long) {
-        launch_ham(T, 1 - col, false, in, out, mix ? HO_MIX : HO_ADD, p1, s);
-        return;
-    }
-    transpose(T, col, in, in_y, false, s);
-    launch_ham(T, 1 - col, false, in_y, out_y, HO_SET, p1, s);
-    transpose(T, 1 - col, out_y, out, true, s);
-    if (mix)
-        hipLaunchKernelGGL(k_sec_mix, dim3(2048), dim3(256), 0, s, in, out, vec_elems(T));
+    launch_ham(T, 1 - col, false, T.is_long ? in_y : in, out, HO_SET, T.is_long, p1, s);
+    launch_ham(T, col, true, in, out, mix ? HO_MIX : HO_ADD, false, partial, s);
 }
 
 hubbard_status check(const char *what)
@@ -1718,9 +1728,9 @@ hubbard_status sector_ansatz_apply(hubbard_t h, const double *theta_dev, int32_t
         return set_error(HUBBARD_ERR_SIZE, "workspace too small for sector_ansatz_apply");
     set_attrs();
     hipStream_t s = (hipStream_t)stream;
-    double2 *out = forward(*T, *P, theta_dev, (double2 *)psi_dev, (double2 *)ws_dev, false, s);
+    double2 *out = forward(*T, *P, theta_dev, (double2 *)psi_dev, (double2 *)ws_dev, false, false, s);
     if (out != (double2 *)psi_dev)   // ended in layout B
-        transpose(*T, 1, out, (double2 *)psi_dev, false, s);
+        transpose(*T, 1, out, (double2 *)psi_dev, s);
     return check("sector ansatz");
 }
 
@@ -1738,9 +1748,10 @@ hubbard_status sector_hamiltonian_apply(hubbard_t h, const void *psi_dev, void *
     if (!ws_dev || ws_bytes < 2 * v)
         return set_error(HUBBARD_ERR_SIZE, "workspace too small for sector_hamiltonian_apply");
     set_attrs();
-    char *w = (char *)ws_dev;
-    hamiltonian(*T, 0, (double2 *)psi_dev, (double2 *)out_dev, (double2 *)w, (double2 *)(w + v),
-                false, nullptr, (hipStream_t)stream);
+    if (T->is_long)
+        transpose(*T, 0, (const double2 *)psi_dev, (double2 *)ws_dev, (hipStream_t)stream);
+    hamiltonian(*T, 0, (double2 *)psi_dev, (double2 *)out_dev, (double2 *)ws_dev, false, nullptr,
+                (hipStream_t)stream);
     return check("sector H");
 }
 
@@ -1769,9 +1780,11 @@ hubbard_status hubbard_sector_lanczos(hubbard_t h, const void *start_dev, int32_
     hipStream_t s = (hipStream_t)stream;
     char *w = (char *)ws_dev;
     double2 *buf[3] = {(double2 *)w, (double2 *)(w + v), (double2 *)(w + 2 * v)};
-    double2 *in_b = (double2 *)(w + 3 * v), *out_b = (double2 *)(w + 4 * v);
+    double2 *in_b = (double2 *)(w + 3 * v);
     const ApplyH apply = [&](const double2 *in, double2 *out) {
-        hamiltonian(*T, 0, (double2 *)in, out, in_b, out_b, false, nullptr, s);
+        if (T->is_long)
+            transpose(*T, 0, in, in_b, s);
+        hamiltonian(*T, 0, (double2 *)in, out, in_b, false, nullptr, s);
         return check("sector H");
     };
     return lanczos_run(apply, n, (const double2 *)start_dev, max_iter, tol, E0, iters, residual,
@@ -1801,10 +1814,13 @@ hubbard_status sector_energy_grad(hubbard_t h, const double *theta_dev, int32_t 
     double2 *lam[2] = {(double2 *)(w + 2 * v), (double2 *)(w + 3 * v)};
     double *partial = (double *)(w + 4 * v);
     auto at = [&](int col) { return T->is_long ? col : 0; };
-    if (P->fwd.empty())
+    if (P->fwd.empty()) {
         hipLaunchKernelGGL(k_sec_basis, dim3(2048), dim3(256), 0, s, psi[0], vec_elems(*T),
                            T->b0_pos);
-    double2 *end = forward(*T, *P, theta_dev, psi[0], psi[1], true, s);
+        if (T->is_long)
+            transpose(*T, 0, psi[0], psi[1], s);
+    }
+    double2 *end = forward(*T, *P, theta_dev, psi[0], psi[1], true, true, s);
     int col = P->final_col;
     if (end != psi[at(col)]) {   // cannot happen: layout A lives in psi[0], B in psi[1]
         return set_error(HUBBARD_ERR_STATE, "sector forward ended in the wrong buffer");
@@ -1812,17 +1828,14 @@ hubbard_status sector_energy_grad(hubbard_t h, const double *theta_dev, int32_t 
     // lambda = H psi, the partial rows 0 and 1 get E; the reverse sweep runs
     // on chi1 = lambda + i psi (psi's buffers) and chi2 = lambda - i psi
     // (lambda's): brackets from their expectations
-    hamiltonian(*T, col, psi[at(col)], lam[at(col)], psi[at(1 - col)], lam[at(1 - col)],
-                !P->fwd.empty(), partial, s);
+    hamiltonian(*T, col, psi[at(col)], lam[at(col)], psi[at(1 - col)], !P->fwd.empty(), partial,
+                s);
     for (int i = (int)P->fwd.size() - 1; i >= 0; --i) {
         const RowPass &p = P->fwd[i];
-        if (T->is_long && p.col != col) {
-            transpose(*T, col, psi[col], psi[p.col], false, s);
-            transpose(*T, col, lam[col], lam[p.col], false, s);
-        }
         col = p.col;
         launch_rows<S_REV>(*T, p, theta_dev, lam[at(col)], psi[at(col)], partial, P->red_row0[i],
-                           i == 0 ? SF_NO_STORE : 0, s);
+                           i == 0 ? SF_NO_STORE : (T->is_long ? SF_TURN : 0), s, lam[at(1 - col)],
+                           psi[at(1 - col)]);
     }
     hipLaunchKernelGGL(k_sec_reduce, dim3(P->n_out), dim3(256), 0, s, partial, kGrid,
                        P->d_nblk, P->d_ptr, P->d_rows, P->d_scale, E_dev, grad_dev);
