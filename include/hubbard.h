@@ -211,7 +211,11 @@ hubbard_status hamiltonian_apply(hubbard_t h, const void *psi_dev, void *out_dev
 /* Eq. (4): E_dev[0] <- <psi(theta)|H|psi(theta)> with psi(theta) prepared
  * from the start state |b0> in the workspace (the workspace's contents on
  * entry are not read).  ws_dev must hold
- * hubbard_workspace_size(..., HUBBARD_OP_ENERGY) bytes (HUBBARD_ERR_SIZE). */
+ * hubbard_workspace_size(..., HUBBARD_OP_ENERGY) bytes (HUBBARD_ERR_SIZE).
+ * The HVA circuit is evaluated on the particle-number sector of |b0> (below:
+ * every other amplitude is zero throughout), as energy_grad and
+ * energy_grad_batch do; the NP circuit, a model the sector form refuses, and
+ * any handle under hubbard_set_timing on the full vector. */
 hubbard_status energy(hubbard_t h, const double *theta_dev, int32_t n_layers,
                       double *E_dev, void *ws_dev, size_t ws_bytes, void *stream);
 
@@ -221,7 +225,9 @@ hubbard_status energy(hubbard_t h, const double *theta_dev, int32_t n_layers,
  * that un-applies the gates to psi and lambda = H psi in the workspace.
  * ws_dev must hold hubbard_workspace_size(..., HUBBARD_OP_ENERGY_GRAD); its
  * contents on entry are not read, and on return they are scratch (psi and
- * lambda are kept there in a layout of the library's own). */
+ * lambda are kept there in a layout of the library's own).  The first call
+ * per handle, device and layer count uploads the full vector's plan and the
+ * sector's tables. */
 hubbard_status energy_grad(hubbard_t h, const double *theta_dev, int32_t n_layers,
                            double *E_dev, double *grad_dev, void *ws_dev,
                            size_t ws_bytes, void *stream);
@@ -353,7 +359,11 @@ hubbard_status energy_grad_noalloc(hubbard_t h, const double *theta_dev, int32_t
 
 /* Batched energy and gradient of many independent instances (different
  * lattices, sizes, U, disorder, V and layer counts; each its own parameters)
- * with no host work per call: a fixed sequence of launches on `stream` --
+ * with no host work per call: a fixed sequence of launches on `stream`.
+ * Instances that all run the HVA circuit in rows of at most 6500 sector
+ * amplitudes (up to 15 sites) are evaluated on their sectors, pass by pass,
+ * each with energy_grad's results bit for bit.  Any other batch runs on the
+ * full vectors:
  * for each position j of the forward, H and reverse schedules, launches that
  * run pass j of every instance that has one (two: passes whose tiles fill the
  * workgroup's registers exactly, and the others; a large instance's tiles
@@ -416,11 +426,11 @@ hubbard_status energy_grad_batch(const hubbard_t *hs, int32_t n, const double *t
  * there).  HVA circuit only: a handle switched to the NP ansatz (whose
  * on-site gates change N_up and N_dn) gives HUBBARD_ERR_STATE.
  * Layout: each spin's gates act along the rows of the matrix whose columns
- * that spin indexes; between runs of gates of the two spins the state is
- * transposed through LDS tiles (a workspace copy).  All calls are
+ * that spin indexes; rows of more than 6500 amplitudes (16 sites) are stored
+ * transposed between the passes of the two spins.  All calls are
  * asynchronous on `stream`; the first call per handle, device and layer
- * count builds and uploads the sector's tables (pair slots and
- * Jordan-Wigner signs per gate and rank: 4 bytes x ranks x bonds x 2). */
+ * count builds and uploads the sector's tables (slots and Jordan-Wigner
+ * signs of every row element: up to a few MiB). */
 enum {
     HUBBARD_SECTOR_ANSATZ = 0,        /* sector_ansatz_apply: one sector vector */
     HUBBARD_SECTOR_ENERGY_GRAD = 1,   /* sector_energy_grad: four vectors + partial sums */

@@ -86,7 +86,8 @@ void hubbard_lbfgs_destroy(hubbard_lbfgs_t L);
  * keeps (at most 16). */
 hubbard_status hubbard_batch_cached(int32_t *count);
 
-/* Phase timing.  When enabled, every later call records HIP events on its own
+/* Phase timing.  When enabled, every later call runs on the full vector (the
+ * pass kernels are what is timed) and records HIP events on its own
  * stream around its phases: the forward passes, the H (or expectation)
  * passes and the reverse passes.  hubbard_phase_ms waits for the last
  * recorded event and returns the phase durations of the most recent call in

@@ -51,6 +51,23 @@ hubbard_status lanczos_run(const ApplyH &apply, uint64_t n, const double2 *start
                            double *residual, double2 *gs_dev, double2 *const buf[3],
                            double2 *partial, hipStream_t s);
 size_t lanczos_partial_bytes();
+// sector.hip: evaluations from |b0> on its particle-number sector
+size_t sector_eval_bytes(hubbard_t h, int layers, bool grad);
+size_t sector_eval_ready(hubbard_t h, int layers);
+hubbard_status sector_eval(hubbard_t h, int layers, const double *theta, double *E, double *grad,
+                           void *ws, hipStream_t s);
+struct SectorBatch;
+size_t sector_batch_bound(const hubbard_t *hs, int n, const int32_t *layers);
+SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
+                                const int64_t *toff, const int32_t *layers, char *ws, int lanes,
+                                hubbard_status *st);
+void sector_batch_free(SectorBatch *b);
+bool sector_batch_uses(const SectorBatch *b, int lane);
+void sector_batch_launch(const SectorBatch *b, const hipStream_t *lane);
+void sector_batch_reduction(const SectorBatch *b, const int32_t **seg_ptr,
+                            const int64_t **seg_off, const int32_t **seg_cnt,
+                            const double **scale, const int64_t **out_idx, int *n_out,
+                            size_t *partial_at);
 }  // namespace hv
 
 using namespace hv;
@@ -898,6 +915,26 @@ VecLayout grad_layout(const hubbard_model *h)
     return vl;
 }
 
+// Whether energy and energy_grad evaluate on the sector of |b0> instead of
+// the full vector.  The HVA circuit keeps (N_up, N_dn), so the results are
+// the same and all but C(Ns, N_up) C(Ns, N_dn) of the 2^n amplitudes stay
+// zero.  The sector form won at every size measured (full vector / sector
+// form, one evaluation): 8 qubits 75 / 41 us, 16 qubits 486 / 219 us, 24
+// qubits with the general diagonal 16.2 / 1.03 ms, 28 qubits 92.9 / 4.2 ms.  The full vector remains for the NP
+// ansatz, for models whose sector plan is refused, for a workspace too small
+// for the sector's vectors, and under hubbard_set_timing, which times the
+// full vector's pass kernels.
+bool sector_route(hubbard_model *h, int layers, bool grad, size_t ws_bytes)
+{
+    if (h->m.ansatz != 0 || h->timing)
+        return false;
+    const std::string err = g_err;   // a refusal is no error of this call
+    const size_t need = sector_eval_bytes(h, layers, grad);
+    if (need == 0)
+        g_err = err;
+    return need != 0 && need <= ws_bytes;
+}
+
 // Phase marks: 0 before the forward passes, 1 after them, 2 after the H or
 // expectation passes, 3 after the reverse passes.
 void mark(hubbard_model *h, int i, hipStream_t s)
@@ -1142,6 +1179,10 @@ hubbard_status batch_layout(const hubbard_t *hs, int n, const int64_t *toff,
         L.seg_ptr.push_back((int32_t)L.seg_off.size());
     }
     L.ws_bytes = L.partial_at + align256(std::max<size_t>(L.n_partial, 1) * sizeof(double));
+    std::vector<int32_t> layers(n);
+    for (int i = 0; i < n; ++i)
+        layers[i] = progs[i]->layers;
+    L.ws_bytes = std::max(L.ws_bytes, sector_batch_bound(hs, n, layers.data()));
     return HUBBARD_OK;
 }
 
@@ -1167,6 +1208,7 @@ hubbard_status batch_host_programs(const hubbard_t *hs, int n, const int32_t *la
 
 struct BatchProgram {
     BatchLayout L;
+    SectorBatch *sector = nullptr;   // the batch on the instances' sectors, if it has that form
     std::vector<uint64_t> uids;   // handles whose device tables the instances point into
     uint64_t last_use = 0;        // cache clock of the last call
     DevInstance *d_inst = nullptr;
@@ -1182,6 +1224,7 @@ struct BatchProgram {
     hipEvent_t fork = nullptr, join[kBatchLanes] = {};
     ~BatchProgram()
     {
+        sector_batch_free(sector);
         if (fork)
             (void)hipEventDestroy(fork);
         for (int l = 1; l < kBatchLanes; ++l) {
@@ -1241,6 +1284,20 @@ void evict_batches_of(uint64_t uid)
     });
 }
 
+// Streams and events of the lanes 1.. that a batch's launches use.
+template <typename Pred> hubbard_status make_lanes(BatchProgram &bp, Pred used)
+{
+    for (int l = 1; l < kBatchLanes; ++l) {
+        if (!used(l))
+            continue;
+        if ((!bp.fork && hipEventCreateWithFlags(&bp.fork, hipEventDisableTiming) != hipSuccess) ||
+            hipStreamCreateWithFlags(&bp.lane_s[l], hipStreamNonBlocking) != hipSuccess ||
+            hipEventCreateWithFlags(&bp.join[l], hipEventDisableTiming) != hipSuccess)
+            return fail(HUBBARD_ERR_DEVICE, "creating the batch lane streams");
+    }
+    return HUBBARD_OK;
+}
+
 hubbard_status build_batch(const hubbard_t *hs, int n, const double *theta, const int64_t *toff,
                            const int32_t *layers, char *ws, const BatchConfig &cfg,
                            BatchProgram &bp)
@@ -1252,6 +1309,34 @@ hubbard_status build_batch(const hubbard_t *hs, int n, const double *theta, cons
     for (int i = 0; i < n; ++i)
         if (std::find(bp.uids.begin(), bp.uids.end(), hs[i]->uid) == bp.uids.end())
             bp.uids.push_back(hs[i]->uid);
+    // On the instances' sectors, by the rule of energy_grad: 256 uneven
+    // instances of 8 to 20 qubits take 12.9 ms on the full vectors (each
+    // launch listed below) and 1.68 ms on the sectors.  Only the workspace
+    // size comes from the full vectors' layout then.
+    bool timing = false;
+    for (int i = 0; i < n; ++i)
+        timing = timing || hs[i]->timing;
+    if (!timing) {
+        const std::string err = g_err;
+        hubbard_status st = HUBBARD_OK;
+        bp.sector = sector_batch_build(hs, n, theta, toff, layers, ws, cfg.lanes, &st);
+        if (st == HUBBARD_ERR_DEVICE || st == HUBBARD_ERR_NOMEM)
+            return st;
+        g_err = err;
+    }
+    if (bp.sector) {
+        std::vector<std::unique_ptr<Program>> own;
+        std::vector<const Program *> host;
+        hubbard_status st = batch_host_programs(hs, n, layers, own, host);
+        if (st == HUBBARD_OK)
+            st = batch_layout(hs, n, toff, host, cfg, bp.L);
+        if (st != HUBBARD_OK)
+            return st;
+        const size_t ws_bytes = bp.L.ws_bytes;
+        bp.L = BatchLayout();
+        bp.L.ws_bytes = ws_bytes;
+        return make_lanes(bp, [&bp](int l) { return sector_batch_uses(bp.sector, l); });
+    }
     // the instances' device programs (cached per handle, device and layer count)
     std::vector<const Program *> progs(n);
     std::vector<DevInstance> insts(n);
@@ -1274,17 +1359,12 @@ hubbard_status build_batch(const hubbard_t *hs, int n, const double *theta, cons
     hubbard_status st = batch_layout(hs, n, toff, progs, cfg, bp.L);
     if (st != HUBBARD_OK)
         return st;
-    bool used[kBatchLanes] = {};
-    for (const BatchLaunch &bl : bp.L.launches)
-        used[bl.lane] = true;
-    for (int l = 1; l < kBatchLanes; ++l) {
-        if (!used[l])
-            continue;
-        if ((!bp.fork && hipEventCreateWithFlags(&bp.fork, hipEventDisableTiming) != hipSuccess) ||
-            hipStreamCreateWithFlags(&bp.lane_s[l], hipStreamNonBlocking) != hipSuccess ||
-            hipEventCreateWithFlags(&bp.join[l], hipEventDisableTiming) != hipSuccess)
-            return fail(HUBBARD_ERR_DEVICE, "creating the batch lane streams");
-    }
+    st = make_lanes(bp, [&bp](int l) {
+        return std::any_of(bp.L.launches.begin(), bp.L.launches.end(),
+                           [l](const BatchLaunch &bl) { return bl.lane == l; });
+    });
+    if (st != HUBBARD_OK)
+        return st;
     for (int i = 0; i < n; ++i) {
         insts[i].psi = ws + bp.L.voff[i];
         insts[i].lam = ws + bp.L.voff[i] + align256(vec_bytes(hs[i]));
@@ -1534,6 +1614,11 @@ hubbard_status energy(hubbard_t h, const double *theta_dev, int32_t n_layers, do
     if (ws_bytes < vb + pr->partial_bytes)
         return fail(HUBBARD_ERR_SIZE, "workspace too small for energy");
     hipStream_t s = (hipStream_t)stream;
+    if (sector_route(h, n_layers, false, ws_bytes)) {
+        h->ev_used = 0;
+        h->kmode.clear();
+        return sector_eval(h, n_layers, theta_dev, E_dev, nullptr, ws_dev, s);
+    }
     double2 *psi = (double2 *)ws_dev;
     double *partial = (double *)((char *)ws_dev + vb);
     // the first forward pass starts from |b0> itself (no init pass)
@@ -1672,6 +1757,12 @@ hubbard_status energy_grad_noalloc(hubbard_t h, const double *theta_dev, int32_t
     hubbard_status st = scratch_address(dev, &base);
     if (st != HUBBARD_OK)
         return st;
+    if (h->m.ansatz == 0 && !h->timing) {
+        const size_t need_s = sector_eval_ready(h, n_layers);
+        if (need_s != 0 && need_s <= kScratchBytes)
+            return sector_eval(h, n_layers, theta_dev, E_dev, grad_dev, base,
+                               (hipStream_t)stream);
+    }
     double2 *psi = (double2 *)base;
     double2 *lam = (double2 *)(base + kScratchVecBytes);
     double *partial = (double *)(base + 2 * kScratchVecBytes);
@@ -1679,8 +1770,15 @@ hubbard_status energy_grad_noalloc(hubbard_t h, const double *theta_dev, int32_t
                          VecLayout(), (hipStream_t)stream);
 }
 
-hubbard_status energy_grad(hubbard_t h, const double *theta_dev, int32_t n_layers, double *E_dev,
-                           double *grad_dev, void *ws_dev, size_t ws_bytes, void *stream)
+}  // extern "C"
+
+namespace {
+
+// energy_grad; sector: on the sector of |b0> where that applies (the
+// autotuner times the full vector's schedules).
+hubbard_status energy_grad_on(hubbard_t h, const double *theta_dev, int32_t n_layers,
+                              double *E_dev, double *grad_dev, void *ws_dev, size_t ws_bytes,
+                              void *stream, bool sector)
 {
     if (!h || !E_dev || !ws_dev || n_layers < 0 || (n_layers > 0 && (!theta_dev || !grad_dev)))
         return fail(HUBBARD_ERR_ARG, "bad arguments to energy_grad");
@@ -1693,6 +1791,11 @@ hubbard_status energy_grad(hubbard_t h, const double *theta_dev, int32_t n_layer
     if (ws_bytes < 2 * vb + pr->partial_bytes)
         return fail(HUBBARD_ERR_SIZE, "workspace too small for energy_grad");
     hipStream_t s = (hipStream_t)stream;
+    if (sector && sector_route(h, n_layers, true, ws_bytes)) {
+        h->ev_used = 0;
+        h->kmode.clear();
+        return sector_eval(h, n_layers, theta_dev, E_dev, grad_dev, ws_dev, s);
+    }
     // psi and lambda share the first 2 vb bytes (layout of grad_layout)
     const VecLayout vl = grad_layout(h);
     double2 *psi = (double2 *)ws_dev;
@@ -1700,6 +1803,17 @@ hubbard_status energy_grad(hubbard_t h, const double *theta_dev, int32_t n_layer
                                        : psi + ((size_t)1 << vl.ilv);
     double *partial = (double *)((char *)ws_dev + 2 * vb);
     return grad_sequence(h, h, *pr, *ds, theta_dev, E_dev, grad_dev, psi, lam, partial, vl, s);
+}
+
+}  // namespace
+
+extern "C" {
+
+hubbard_status energy_grad(hubbard_t h, const double *theta_dev, int32_t n_layers, double *E_dev,
+                           double *grad_dev, void *ws_dev, size_t ws_bytes, void *stream)
+{
+    return energy_grad_on(h, theta_dev, n_layers, E_dev, grad_dev, ws_dev, ws_bytes, stream,
+                          true);
 }
 
 hubbard_status hubbard_batch_workspace_size(const hubbard_t *hs, int32_t n,
@@ -1742,7 +1856,8 @@ hubbard_status energy_grad_batch(const hubbard_t *hs, int32_t n, const double *t
                       std::to_string((uintptr_t)ws_dev) + ":" + std::to_string(cfg.items) + "." +
                       std::to_string(cfg.lanes);
     for (int i = 0; i < n; ++i)
-        key += ":" + std::to_string(hs[i]->uid) + "." + std::to_string(hs[i]->gen) + "/" +
+        key += (hs[i]->timing ? ":t" : ":") + std::to_string(hs[i]->uid) + "." +
+               std::to_string(hs[i]->gen) + "/" +
                std::to_string(n_layers[i]) + "/" + std::to_string(theta_off[i]);
     hipStream_t s = (hipStream_t)stream;
     BatchProgram *bp = nullptr;
@@ -1780,6 +1895,12 @@ hubbard_status energy_grad_batch(const hubbard_t *hs, int32_t n, const double *t
     for (int l = 1; l < kBatchLanes; ++l)
         if (bp->lane_s[l] && hipStreamWaitEvent(bp->lane_s[l], bp->fork, 0) != hipSuccess)
             return fail(HUBBARD_ERR_DEVICE, "forking the batch lane streams");
+    if (bp->sector) {
+        hipStream_t lane[kBatchLanes];
+        for (int l = 0; l < kBatchLanes; ++l)
+            lane[l] = l == 0 ? s : bp->lane_s[l];
+        sector_batch_launch(bp->sector, lane);
+    }
     for (const BatchLaunch &bl : L.launches) {
         const DevWork *w = bp->d_work + bl.item0;
         hipStream_t ls = bl.lane == 0 ? s : bp->lane_s[bl.lane];
@@ -1823,9 +1944,18 @@ hubbard_status energy_grad_batch(const hubbard_t *hs, int32_t n, const double *t
         if (bp->lane_s[l] && (hipEventRecord(bp->join[l], bp->lane_s[l]) != hipSuccess ||
                               hipStreamWaitEvent(s, bp->join[l], 0) != hipSuccess))
             return fail(HUBBARD_ERR_DEVICE, "joining the batch lane streams");
-    hipLaunchKernelGGL(k_reduce_seg, dim3((unsigned)L.scale.size()), dim3(256), 0, s, partial,
-                       bp->d_seg_ptr, bp->d_seg_off, bp->d_seg_cnt, bp->d_scale, bp->d_out_idx, n,
-                       E_dev, grad_dev);
+    const int32_t *seg_ptr = bp->d_seg_ptr, *seg_cnt = bp->d_seg_cnt;
+    const int64_t *seg_off = bp->d_seg_off, *out_idx = bp->d_out_idx;
+    const double *scale = bp->d_scale;
+    int n_out = (int)L.scale.size();
+    if (bp->sector) {
+        size_t at = 0;
+        sector_batch_reduction(bp->sector, &seg_ptr, &seg_off, &seg_cnt, &scale, &out_idx, &n_out,
+                               &at);
+        partial = (double *)((char *)ws_dev + at);
+    }
+    hipLaunchKernelGGL(k_reduce_seg, dim3((unsigned)n_out), dim3(256), 0, s, partial, seg_ptr,
+                       seg_off, seg_cnt, scale, out_idx, n, E_dev, grad_dev);
     return check_launch("batch");
 }
 
@@ -1968,13 +2098,13 @@ hubbard_status hubbard_tune(hubbard_t h, int32_t n_layers, const double *theta_d
         if (hubbard_workspace_size(h, n_layers, HUBBARD_OP_ENERGY_GRAD, &need) != HUBBARD_OK ||
             need > ws_bytes)
             continue;
-        if ((st = energy_grad(h, theta_dev, n_layers, E, g, ws_dev, ws_bytes, stream)) !=
+        if ((st = energy_grad_on(h, theta_dev, n_layers, E, g, ws_dev, ws_bytes, stream, false)) !=
             HUBBARD_OK)
             break;   // (also plans and uploads this configuration)
         float ms = 1e30f;
         for (int r = 0; r < reps; ++r) {
             (void)hipEventRecord(e0, s);
-            energy_grad(h, theta_dev, n_layers, E, g, ws_dev, ws_bytes, stream);
+            energy_grad_on(h, theta_dev, n_layers, E, g, ws_dev, ws_bytes, stream, false);
             (void)hipEventRecord(e1, s);
             float t = 0.0f;
             if (hipEventSynchronize(e1) != hipSuccess ||

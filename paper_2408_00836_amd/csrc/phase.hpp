@@ -20,14 +20,15 @@ __device__ __forceinline__ double flip_sign(double x, uint32_t bit)
 // significant bits, exact for |k| < 2^17), the phase of k h from the LDS
 // table cis[k mod 2^kCisBits] = (cos kh, sin kh), and cos r, sin r by their
 // Taylor series (|r| <= pi / 2^kCisBits, truncation below 1e-19).
-__device__ __forceinline__ double2 cis_neg(double x, const double2 *cis)
+// dx: a correction added to x, far below it (its rounding).
+__device__ __forceinline__ double2 cis_neg(double x, const double2 *cis, double dx = 0.0)
 {
     constexpr double kInvH = 0x1.45f306dc9c883p+5;    // 2^kCisBits / (2 pi), kCisBits = 8
     constexpr double kHHi = 0x1.921fb54440000p-6;     // 2 pi / 2^kCisBits, leading part
     constexpr double kHLo = 0x1.68c234c4c6629p-45;    // remainder
     const double k = rint(x * kInvH);
     double r = fma(-k, kHHi, x);
-    r = fma(-k, kHLo, r);
+    r = fma(-k, kHLo, r) + dx;
     const double2 t = cis[(int)k & ((1 << kCisBits) - 1)];
     const double r2 = r * r;
     const double c = fma(r2, fma(r2, fma(r2, -1.0 / 720.0, 1.0 / 24.0), -0.5), 1.0);

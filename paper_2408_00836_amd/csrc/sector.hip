@@ -31,6 +31,7 @@
 
 #include <algorithm>
 #include <array>
+#include <cmath>
 #include <cstring>
 #include <functional>
 #include <map>
@@ -70,9 +71,9 @@ enum { S_FWD = 0, S_REV = 1 };
 // buffer; with SF_BOTH also to its own place.
 enum { SF_NO_STORE = 1, SF_START = 2, SF_TURN = 4, SF_BOTH = 8 };
 // What a pass of H does with its part phi of H psi: out <- phi, out <- out +
-// phi, or lambda = out + phi and then psi <- lambda + i psi, out <- lambda -
-// i psi (the reverse sweep's two vectors).
-enum { HO_SET = 0, HO_ADD = 1, HO_MIX = 2 };
+// phi, lambda = out + phi and then psi <- lambda / m + i m psi, out <- lambda
+// / m - i m psi (the reverse sweep's two vectors), or only the energy.
+enum { HO_SET = 0, HO_ADD = 1, HO_MIX = 2, HO_NONE = 3 };
 
 typedef __attribute__((address_space(1))) double2 gc128;
 typedef const __attribute__((address_space(1))) uint16_t gu16;
@@ -113,6 +114,7 @@ struct RowsArgs {
     int row0[2];                 // first partial row of each vector
     int n_red, pstride, flags;
     int b0_row, b0_col;
+    int grid;                    // workgroups of the pass (per vector)
 };
 
 // x from another lane of the same 16-lane row (DPP control CTRL), both
@@ -247,15 +249,15 @@ __host__ __device__ inline uint32_t long_vec_bytes(int nslots)
 
 // Work common to both row kernels.  A pass's steps: the phases of the hops
 // before the diagonal, then those of the hops after it.
-template <int MODE, bool GEN>
+template <int MODE, bool GEN, typename AT>
 struct RowPassCtx {
     static constexpr bool REV = MODE == S_REV;
-    const RowsArgs &A;
+    const AT &A;
     double2 *ang, *dtab;
     double *acc;
     int tid, T, dslot, post_slot;
 
-    __device__ RowPassCtx(const RowsArgs &a, char *smem, const RowLds &L)
+    __device__ RowPassCtx(const AT &a, char *smem, const RowLds &L)
         : A(a), ang((double2 *)(smem + L.ang)), dtab((double2 *)(smem + L.dtab)),
           acc((double *)(smem + L.acc)), tid(threadIdx.x), T(blockDim.x)
     {
@@ -272,9 +274,11 @@ struct RowPassCtx {
             const int run = i >= n_gates ? 1 : 0, layer = run ? A.l_post : A.l_pre;
             if (layer < 0)
                 continue;
-            const SecGate &g = A.gates[i - run * n_gates];
+            const gf64 *theta = (const gf64 *)A.theta;
+            const __attribute__((address_space(1))) SecGate &g =
+                ((const __attribute__((address_space(1))) SecGate *)A.gates)[i - run * n_gates];
             double s, c;
-            sincos(A.theta[layer * A.per + g.slot] * g.t, &s, &c);
+            sincos(theta[layer * A.per + g.slot] * g.t, &s, &c);
             ang[i] = make_double2(c, REV ? -s : s);
         }
         if (A.l_diag >= 0) {
@@ -347,7 +351,7 @@ struct RowPassCtx {
         }
     }
     // the workgroup's partial sums (after a barrier)
-    __device__ void finish(int vsel, bool negate)
+    __device__ void finish(int bid, int vsel, bool negate)
     {
         const int lane = tid & 63, wave = tid >> 6, R = T / 4;
         for (int r = wave; r < A.n_red; r += T >> 6) {
@@ -356,17 +360,28 @@ struct RowPassCtx {
                 s += acc[r * R + i];
             s = wave_sum(s);
             if (lane == 0)
-                A.partial[(size_t)(A.row0[vsel] + r) * A.pstride + blockIdx.x] = negate ? -s : s;
+                A.partial[(size_t)(A.row0[vsel] + r) * A.pstride + bid] = negate ? -s : s;
         }
     }
 };
 
 // D's value of an element from its row's nibble sums: the row's and the
-// pattern's own terms and the coupling sum_j p_j w_j.
+// pattern's own terms and the coupling sum_j p_j w_j.  err: the last sum's
+// rounding (the phase exp(-i th D) needs it: D is large against pi).
+__device__ __forceinline__ double diag_gen(double rb, double cb, const double *nib, uint32_t cp,
+                                           double &err)
+{
+    const double a = rb + cb;
+    const double b = (nib[cp & 15u] + nib[16 + ((cp >> 4) & 15u)]) +
+                     (nib[32 + ((cp >> 8) & 15u)] + nib[48 + (cp >> 12)]);
+    const double d = a + b, t = d - a;
+    err = (a - (d - t)) + (b - t);
+    return d;
+}
 __device__ __forceinline__ double diag_gen(double rb, double cb, const double *nib, uint32_t cp)
 {
-    return (rb + cb) + ((nib[cp & 15u] + nib[16 + ((cp >> 4) & 15u)]) +
-                        (nib[32 + ((cp >> 8) & 15u)] + nib[48 + (cp >> 12)]));
+    double err;
+    return diag_gen(rb, cb, nib, cp, err);
 }
 
 __device__ __forceinline__ double nibble_sum(const gf64 *w, int e)
@@ -382,11 +397,13 @@ __device__ __forceinline__ double nibble_sum(const gf64 *w, int e)
 // The diagonal on one element: exp(-i th D) forward, the bracket D |a|^2 and
 // exp(+i th D) in reverse.
 template <bool REV, bool GEN>
-__device__ __forceinline__ void diag_el(double2 &a, double d, double2 ph, double th,
+__device__ __forceinline__ void diag_el(double2 &a, double d, double err, double2 ph, double th,
                                         const double2 *cis, double &racc)
 {
-    if constexpr (GEN)
-        ph = cis_neg(REV ? -th * d : th * d, cis);
+    if constexpr (GEN) {
+        const double t = REV ? -th : th, x = t * d;
+        ph = cis_neg(x, cis, fma(t, d, -x) + t * err);
+    }
     if constexpr (REV)
         racc = fma(d, fma(a.x, a.x, a.y * a.y), racc);
     a = make_double2(fma(ph.x, a.x, -ph.y * a.y), fma(ph.x, a.y, ph.y * a.x));
@@ -415,23 +432,23 @@ __device__ __forceinline__ int group_of(int i, int n)
 // to 0.283 ms.
 //   S_FWD: v[0] <- ops applied.  SF_START: the input is |b0>, not read; the
 //          rows without it are zero.
-//   S_REV: blockIdx.y picks chi2 = v[0] or chi1 = v[1]; the ops un-applied in
+//   S_REV: vsel picks chi2 = v[0] or chi1 = v[1]; the ops un-applied in
 //          reverse order, <chi|G|chi> of every hop and of D before its
 //          un-application added to its reduction slot (chi1's negated).  The
 //          bracket Im <lambda|G|psi> is (<chi2|G|chi2> - <chi1|G|chi1>) / 4
-//          with chi1, chi2 = lambda +- i psi.
-template <int MODE, bool GEN>
-__global__ void __launch_bounds__(1024) k_sec_rows_short(RowsArgs A)
+//          with chi1, chi2 = lambda / m +- i m psi for any m: one near the
+//          square root of |lambda| / |psi| keeps the difference's rounding
+//          as small as the bracket's own.
+template <int MODE, bool GEN, typename AT>
+__device__ __forceinline__ void rows_short(const AT &A, int bid, int vsel, char *smem)
 {
     constexpr bool REV = MODE == S_REV;
-    extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, T = blockDim.x, lr = A.lr, R = 1 << lr;
     const RowLds L = row_lds(short_vec_bytes(A.nslots, lr), R, A.n_phases, A.n_red, T, GEN);
-    RowPassCtx<MODE, GEN> C(A, smem, L);
+    RowPassCtx<MODE, GEN, AT> C(A, smem, L);
     double2 *vec = (double2 *)smem;
     double *nib = (double *)(smem + L.nib), *rowb = (double *)(smem + L.rowb);
     uint32_t *rowp = (uint32_t *)(smem + L.rowp);
-    const int vsel = REV ? (int)blockIdx.y : 0;
     gc128 *__restrict__ v = (gc128 *)A.v[vsel];
     const gu16 *__restrict__ colslot = (const gu16 *)A.colslot;
     const gu16 *__restrict__ patslot = (const gu16 *)A.patslot;
@@ -458,7 +475,7 @@ __global__ void __launch_bounds__(1024) k_sec_rows_short(RowsArgs A)
             }
         }
     };
-    for (int ig = blockIdx.x; ig < (ng + 7) / 8 * 8; ig += gridDim.x) {
+    for (int ig = bid; ig < (ng + 7) / 8 * 8; ig += A.grid) {
         const int g = group_of(ig, ng);
         if (g < 0)
             continue;
@@ -526,10 +543,12 @@ __global__ void __launch_bounds__(1024) k_sec_rows_short(RowsArgs A)
                 const uint32_t cp = patslot[sl];
                 double2 a = vec[i];
                 if constexpr (GEN) {
-                    diag_el<REV, true>(a, diag_gen(rb, baseslot[sl], nb, cp), a, th, C.dtab, racc);
+                    double err;
+                    const double d = diag_gen(rb, baseslot[sl], nb, cp, err);
+                    diag_el<REV, true>(a, d, err, a, th, C.dtab, racc);
                 } else {
                     const int k = __popc(rp & cp);
-                    diag_el<REV, false>(a, A.U * (double)k, C.dtab[k], th, nullptr, racc);
+                    diag_el<REV, false>(a, A.U * (double)k, 0.0, C.dtab[k], th, nullptr, racc);
                 }
                 vec[i] = a;
             }
@@ -639,8 +658,31 @@ __global__ void __launch_bounds__(1024) k_sec_rows_short(RowsArgs A)
     }
     if constexpr (REV) {
         __syncthreads();
-        C.finish(vsel, vsel == 1);
+        C.finish(bid, vsel, vsel == 1);
     }
+}
+
+template <int MODE, bool GEN>
+__global__ void __launch_bounds__(1024) k_sec_rows_short(RowsArgs A)
+{
+    extern __shared__ __align__(16) char smem[];
+    rows_short<MODE, GEN>(A, (int)blockIdx.x, MODE == S_REV ? (int)blockIdx.y : 0, smem);
+}
+
+// A batch's pass: every workgroup runs one workgroup's part of one instance's
+// pass, the same work in the same order as that instance's own launch.
+struct SecWork {
+    int32_t args, bid, vsel, pad;
+};
+typedef const __attribute__((address_space(4))) RowsArgs kRowsArgs;
+
+template <int MODE, bool GEN>
+__global__ void __launch_bounds__(1024)
+k_sec_rows_batch(const RowsArgs *__restrict__ args, const SecWork *__restrict__ work)
+{
+    extern __shared__ __align__(16) char smem[];
+    const SecWork w = work[blockIdx.x];
+    rows_short<MODE, GEN>(((kRowsArgs *)args)[w.args], w.bid, w.vsel, smem);
 }
 
 // ------------------------------------------------------------- long rows --
@@ -752,7 +794,7 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
     extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x;
     const RowLds L = row_lds(long_vec_bytes(A.nslots), 1, A.n_phases, A.n_red, kLongT, GEN);
-    RowPassCtx<MODE, GEN> C(A, smem, L);
+    RowPassCtx<MODE, GEN, RowsArgs> C(A, smem, L);
     double *nib = (double *)(smem + L.nib);
     const int vsel = REV ? (int)blockIdx.y : 0;
     const kPhase *__restrict__ phases = (const kPhase *)A.phases;
@@ -768,7 +810,7 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
     const uint32_t n = (uint32_t)A.n;
     auto ph_of = [&](int st) { return st < A.n_phases ? st : st - A.n_phases; };
 
-    for (int ig = blockIdx.x; ig < (A.n_rows + 7) / 8 * 8; ig += gridDim.x) {
+    for (int ig = blockIdx.x; ig < (A.n_rows + 7) / 8 * 8; ig += A.grid) {
         const int r = group_of(ig, A.n_rows);
         if (r < 0)
             continue;
@@ -830,11 +872,12 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
             for (int j = 0; j < kOrbitElems; ++j) {
                 const uint32_t cp = (pt.w[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
                 if constexpr (GEN) {
-                    diag_el<REV, true>(x[j], diag_gen(rb, lbase[j * kLongT + td], nib, cp), x[j],
-                                       th, C.dtab, racc);
+                    double err;
+                    const double d = diag_gen(rb, lbase[j * kLongT + td], nib, cp, err);
+                    diag_el<REV, true>(x[j], d, err, x[j], th, C.dtab, racc);
                 } else {
                     const int k = __popc(rp & cp);
-                    diag_el<REV, false>(x[j], A.U * (double)k, C.dtab[k], th, nullptr, racc);
+                    diag_el<REV, false>(x[j], A.U * (double)k, 0.0, C.dtab[k], th, nullptr, racc);
                 }
                 __builtin_amdgcn_sched_barrier(0);   // fewer values in flight
             }
@@ -880,7 +923,7 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
     }
     if constexpr (REV) {
         __syncthreads();
-        C.finish(vsel, vsel == 1);
+        C.finish((int)blockIdx.x, vsel, vsel == 1);
     }
 }
 
@@ -898,7 +941,9 @@ struct HamArgs {
     int n, n_rows, nslots, lr, nb, diag, out_mode, turn;   // turn (long rows): out is transposed
     int64_t rs, cs;
     double2 *psi, *out;
+    double mix;                        // HO_MIX: m, a power of two
     double *partial;                   // NULL: no energy
+    int grid;
 };
 
 // sign bit of a code (bit 15, or bit 31 of the packed dword)
@@ -908,14 +953,19 @@ __device__ __forceinline__ uint32_t code_sign(uint32_t w, int odd)
 }
 
 // Store phi's element as the pass asks.
-__device__ __forceinline__ void ham_store(int mode, gc128 *out, gc128 *psi, double2 phi,
+__device__ __forceinline__ void ham_store(int mode, double m, gc128 *out, gc128 *psi, double2 phi,
                                           double2 own)
 {
+    if (mode == HO_NONE)
+        return;
     if (mode != HO_SET) {
         phi.x += out->x;
         phi.y += out->y;
     }
     if (mode == HO_MIX) {
+        const double im = 1.0 / m;   // exact
+        phi = make_double2(phi.x * im, phi.y * im);
+        own = make_double2(own.x * m, own.y * m);
         psi->x = phi.x - own.y;
         psi->y = phi.y + own.x;
         phi = make_double2(phi.x + own.y, phi.y - own.x);
@@ -924,10 +974,9 @@ __device__ __forceinline__ void ham_store(int mode, gc128 *out, gc128 *psi, doub
     out->y = phi.y;
 }
 
-template <bool GEN>
-__global__ void __launch_bounds__(1024) k_sec_ham_short(HamArgs A)
+template <bool GEN, typename AT>
+__device__ __forceinline__ void ham_short(const AT &A, int bid, char *smem)
 {
-    extern __shared__ __align__(16) char smem[];
     const int tid = threadIdx.x, T = blockDim.x, lr = A.lr, R = 1 << lr;
     double2 *vec = (double2 *)smem;
     double *nib = (double *)(smem + short_vec_bytes(A.nslots, lr));
@@ -942,7 +991,7 @@ __global__ void __launch_bounds__(1024) k_sec_ham_short(HamArgs A)
     if (tid < R)
         vec[(A.nslots << lr) + tid] = make_double2(0.0, 0.0);
     double e = 0.0;
-    for (int ig = blockIdx.x; ig < (ng + 7) / 8 * 8; ig += gridDim.x) {
+    for (int ig = bid; ig < (ng + 7) / 8 * 8; ig += A.grid) {
         const int g = group_of(ig, ng);
         if (g < 0)
             continue;
@@ -985,7 +1034,7 @@ __global__ void __launch_bounds__(1024) k_sec_ham_short(HamArgs A)
             }
             if (live) {
                 e += re_dot(own, phi);
-                ham_store(A.out_mode, out + (int64_t)col * A.cs, psi + (int64_t)col * A.cs, phi,
+                ham_store(A.out_mode, A.mix, out + (int64_t)col * A.cs, psi + (int64_t)col * A.cs, phi,
                           own);
             }
         }
@@ -999,9 +1048,26 @@ __global__ void __launch_bounds__(1024) k_sec_ham_short(HamArgs A)
             double s = 0.0;
             for (int w = 0; w < T >> 6; ++w)
                 s += wsum[w];
-            A.partial[blockIdx.x] = s;
+            A.partial[bid] = s;
         }
     }
+}
+
+template <bool GEN>
+__global__ void __launch_bounds__(1024) k_sec_ham_short(HamArgs A)
+{
+    extern __shared__ __align__(16) char smem[];
+    ham_short<GEN>(A, (int)blockIdx.x, smem);
+}
+
+typedef const __attribute__((address_space(4))) HamArgs kHamArgs;
+template <bool GEN>
+__global__ void __launch_bounds__(1024)
+k_sec_ham_batch(const HamArgs *__restrict__ args, const SecWork *__restrict__ work)
+{
+    extern __shared__ __align__(16) char smem[];
+    const SecWork w = work[blockIdx.x];
+    ham_short<GEN>(((kHamArgs *)args)[w.args], w.bid, smem);
 }
 
 // Long rows: H is real, so the real and the imaginary parts of a row take
@@ -1025,7 +1091,7 @@ __global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
     for (int i = tid; i < A.nslots + kLongDummy; i += kLongT)   // the holes and the zero slots
         buf[i] = 0.0;
     double e = 0.0;
-    for (int ig = blockIdx.x; ig < (A.n_rows + 7) / 8 * 8; ig += gridDim.x) {
+    for (int ig = blockIdx.x; ig < (A.n_rows + 7) / 8 * 8; ig += A.grid) {
         const int r = group_of(ig, A.n_rows);
         if (r < 0)
             continue;
@@ -1114,7 +1180,7 @@ __global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
                         double2 own = make_double2(0.0, 0.0);
                         if (A.out_mode == HO_MIX)
                             own = make_double2(psi[i].x, psi[i].y);
-                        ham_store(A.out_mode, o, psi + i, f, own);
+                        ham_store(A.out_mode, A.mix, o, psi + i, f, own);
                     }
                 }
             }
@@ -1225,7 +1291,7 @@ struct Tables {
     int b0_rank[2] = {0, 0};      // ranks of |b0>'s patterns
     bool general = false;         // eps or V terms in the diagonal
     bool is_long = false;
-    double U = 0.0;
+    double U = 0.0, mix = 1.0;
     int n_phases = 0, nb = 0, per = 1;
     SpinTables sp[2];
     SecGate *d_gates = nullptr;
@@ -1300,6 +1366,19 @@ hubbard_status build_tables(const Model &m, Tables &T)
     T.n_phases = (int)P.sites.size();
     T.nb = m.nb;
     T.per = m.params_per_layer();
+    // m = 2^k near sqrt |H psi|: an evenly filled state's hops give |H psi|^2
+    // a term t^2 per bond (both spins) and its diagonal a mean value
+    double hop2 = 0.0, mean = 0.25 * m.U * m.ns;
+    for (int k = 0; k < m.nb; ++k) {
+        hop2 += m.t[k] * m.t[k];
+        mean += m.V[k];
+    }
+    for (int i = 0; i < m.ns; ++i)
+        mean += m.eps[i];
+    const double norm = std::sqrt(hop2 + mean * mean);
+    T.mix = norm > 0.0 && std::isfinite(norm)
+                ? std::ldexp(1.0, std::max(-64, std::min(64, (int)std::lround(0.5 * std::log2(norm)))))
+                : 1.0;
     Blob B;
     B.add(&T.d_gates, P.gates);
     std::vector<double> tb((size_t)std::max(8, ham_bonds(m.nb)), 0.0);
@@ -1469,10 +1548,11 @@ void strides(const Tables &T, int col, int64_t *rs, int64_t *cs)
     *cs = col == 0 || T.is_long ? 1 : T.n[0];
 }
 
-template <int MODE>
-void launch_rows(const Tables &T, const RowPass &p, const double *theta, double2 *v0, double2 *v1,
-                 double *partial, int row0, int flags, hipStream_t s, double2 *t0 = nullptr,
-                 double2 *t1 = nullptr)
+// Arguments of pass p (reverse: of its two vectors) on v0 (and v1); its
+// partial rows start at row0, pstride entries each.
+RowsArgs rows_args(const Tables &T, const RowPass &p, bool rev, const double *theta, double2 *v0,
+                   double2 *v1, double *partial, int row0, int pstride, int flags, double2 *t0,
+                   double2 *t1)
 {
     const SpinTables &S = T.sp[p.col], &O = T.sp[1 - p.col];
     RowsArgs A;
@@ -1506,14 +1586,26 @@ void launch_rows(const Tables &T, const RowPass &p, const double *theta, double2
     A.t[0] = t0;
     A.t[1] = t1;
     A.partial = partial;
-    A.n_red = MODE == S_REV ? (int)p.red_param.size() : 0;
+    A.n_red = rev ? (int)p.red_param.size() : 0;
     A.row0[0] = row0;
     A.row0[1] = row0 + A.n_red;
-    A.pstride = kGrid;
+    A.pstride = pstride;
     A.flags = flags;
     A.b0_row = T.b0_rank[1 - p.col];
     A.b0_col = T.b0_rank[p.col];
-    const dim3 grid(rows_grid(T, p.col), MODE == S_REV ? 2 : 1);
+    A.grid = rows_grid(T, p.col);
+    return A;
+}
+
+template <int MODE>
+void launch_rows(const Tables &T, const RowPass &p, const double *theta, double2 *v0, double2 *v1,
+                 double *partial, int row0, int flags, hipStream_t s, double2 *t0 = nullptr,
+                 double2 *t1 = nullptr)
+{
+    const SpinTables &S = T.sp[p.col];
+    const RowsArgs A = rows_args(T, p, MODE == S_REV, theta, v0, v1, partial, row0, kGrid, flags,
+                                 t0, t1);
+    const dim3 grid(A.grid, MODE == S_REV ? 2 : 1);
     const uint32_t lds = rows_lds(T, p.col, A.n_red);
     if (S.is_long) {
         if (T.general)
@@ -1528,9 +1620,9 @@ void launch_rows(const Tables &T, const RowPass &p, const double *theta, double2
     }
 }
 
-// spin col's part of H (with_d: and the diagonal) on psi.
-void launch_ham(const Tables &T, int col, bool with_d, double2 *psi, double2 *out, int out_mode,
-                bool turn, double *partial, hipStream_t s)
+// Spin col's part of H (with_d: and the diagonal) on psi.
+HamArgs ham_args(const Tables &T, int col, bool with_d, double2 *psi, double2 *out, int out_mode,
+                 bool turn, double *partial)
 {
     const SpinTables &S = T.sp[col], &O = T.sp[1 - col];
     HamArgs A;
@@ -1552,11 +1644,28 @@ void launch_ham(const Tables &T, int col, bool with_d, double2 *psi, double2 *ou
     A.diag = with_d ? 1 : 0;
     A.out_mode = out_mode;
     A.turn = turn ? 1 : 0;
+    A.mix = T.mix;
     strides(T, col, &A.rs, &A.cs);
     A.psi = psi;
     A.out = out;
     A.partial = partial;
-    const dim3 grid(rows_grid(T, col));
+    A.grid = rows_grid(T, col);
+    return A;
+}
+
+// Short rows' H: about an element per thread and round.
+int ham_threads(const SpinTables &S) { return std::min(1024, 4 * S.threads); }
+uint32_t ham_lds(const Tables &T, const SpinTables &S)
+{
+    return short_vec_bytes(S.nslots, S.lr) + (T.general ? (64u << S.lr) * 8u : 0u) + 16u * 8u;
+}
+
+void launch_ham(const Tables &T, int col, bool with_d, double2 *psi, double2 *out, int out_mode,
+                bool turn, double *partial, hipStream_t s)
+{
+    const SpinTables &S = T.sp[col];
+    const HamArgs A = ham_args(T, col, with_d, psi, out, out_mode, turn, partial);
+    const dim3 grid(A.grid);
     if (S.is_long) {
         const uint32_t lds = long_vec_bytes(S.nslots) + 64u * 8u + 16u * 8u;
         if (T.general)
@@ -1564,11 +1673,8 @@ void launch_ham(const Tables &T, int col, bool with_d, double2 *psi, double2 *ou
         else
             hipLaunchKernelGGL((k_sec_ham_long<false>), grid, dim3(kLongT), lds, s, A);
     } else {
-        // an element per thread and round; no orbit lists here
-        const int want = ((S.n << S.lr) + 63) / 64 * 64;
-        const dim3 th((unsigned)std::min(1024, want));
-        const uint32_t lds = short_vec_bytes(S.nslots, S.lr) +
-                             (T.general ? (64u << S.lr) * 8u : 0u) + 16u * 8u;
+        const dim3 th(ham_threads(S));
+        const uint32_t lds = ham_lds(T, S);
         if (T.general)
             hipLaunchKernelGGL((k_sec_ham_short<true>), grid, th, lds, s, A);
         else
@@ -1593,7 +1699,10 @@ void set_attrs()
             (const void *)k_sec_rows_long<S_FWD, false>,  (const void *)k_sec_rows_long<S_FWD, true>,
             (const void *)k_sec_rows_long<S_REV, false>,  (const void *)k_sec_rows_long<S_REV, true>,
             (const void *)k_sec_ham_short<false>,         (const void *)k_sec_ham_short<true>,
-            (const void *)k_sec_ham_long<false>,          (const void *)k_sec_ham_long<true>};
+            (const void *)k_sec_ham_long<false>,          (const void *)k_sec_ham_long<true>,
+            (const void *)k_sec_rows_batch<S_FWD, false>, (const void *)k_sec_rows_batch<S_FWD, true>,
+            (const void *)k_sec_rows_batch<S_REV, false>, (const void *)k_sec_rows_batch<S_REV, true>,
+            (const void *)k_sec_ham_batch<false>,         (const void *)k_sec_ham_batch<true>};
         for (const void *f : fns)
             (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     });
@@ -1622,15 +1731,16 @@ double2 *forward(const Tables &T, const Program &P, const double *theta, double2
 
 // out <- H in for sector vectors in layout `col` (long rows; short ones have
 // one layout).  Long rows: in_y is `in` in the other layout, where the other
-// spin's hops act; their part comes back transposed.  mix: out <- lambda - i
-// psi and in <- lambda + i psi of lambda = H psi instead.  Energy parts to
-// partial rows 0 and 1 (partial != NULL).
-void hamiltonian(const Tables &T, int col, double2 *in, double2 *out, double2 *in_y, bool mix,
+// spin's hops act; their part comes back transposed.  last: HO_ADD; HO_MIX
+// for the reverse sweep's vectors (out and in); HO_NONE: the energy only.
+// Energy parts to partial rows 0 and 1 (partial != NULL).
+void hamiltonian(const Tables &T, int col, double2 *in, double2 *out, double2 *in_y, int last,
                  double *partial, hipStream_t s)
 {
     double *p1 = partial ? partial + kGrid : nullptr;
-    launch_ham(T, 1 - col, false, T.is_long ? in_y : in, out, HO_SET, T.is_long, p1, s);
-    launch_ham(T, col, true, in, out, mix ? HO_MIX : HO_ADD, false, partial, s);
+    launch_ham(T, 1 - col, false, T.is_long ? in_y : in, out, last == HO_NONE ? HO_NONE : HO_SET,
+               T.is_long, p1, s);
+    launch_ham(T, col, true, in, out, last, false, partial, s);
 }
 
 hubbard_status check(const char *what)
@@ -1639,6 +1749,50 @@ hubbard_status check(const char *what)
     if (e != hipSuccess)
         return fail(HUBBARD_ERR_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
     return HUBBARD_OK;
+}
+
+// Workspace of an evaluation: psi and lambda in both layouts, the partial rows
+// (of the energy alone: two).
+size_t eval_bytes(const Tables &T, const Program &P, bool grad = true)
+{
+    return 4 * align256(vec_elems(T) * 16) + align256((size_t)(grad ? P.n_rows : 2) * kGrid * 8);
+}
+
+// E and, with grad != NULL, the gradient of the circuit's energy.
+void evaluate(const Tables &T, const Program &P, const double *theta, double *E, double *grad,
+              char *w, hipStream_t s)
+{
+    set_attrs();
+    const size_t v = align256(vec_elems(T) * 16);
+    // the two layouts' buffers (short rows: one layout, index 0)
+    double2 *psi[2] = {(double2 *)w, (double2 *)(w + v)};
+    double2 *lam[2] = {(double2 *)(w + 2 * v), (double2 *)(w + 3 * v)};
+    double *partial = (double *)(w + 4 * v);
+    auto at = [&](int col) { return T.is_long ? col : 0; };
+    if (P.fwd.empty()) {
+        hipLaunchKernelGGL(k_sec_basis, dim3(2048), dim3(256), 0, s, psi[0], vec_elems(T),
+                           T.b0_pos);
+        if (T.is_long)
+            transpose(T, 0, psi[0], psi[1], s);
+    }
+    // layout A lives in the first buffers, B in the second
+    (void)forward(T, P, theta, psi[0], psi[1], true, true, s);
+    int col = P.final_col;
+    const bool rev = grad && !P.fwd.empty();
+    // lambda = H psi, the partial rows 0 and 1 get E; the reverse sweep runs
+    // on chi1 (psi's buffers) and chi2 (lambda's): brackets from their
+    // expectations
+    hamiltonian(T, col, psi[at(col)], lam[at(col)], psi[at(1 - col)], rev ? HO_MIX : HO_NONE,
+                partial, s);
+    for (int i = (int)P.fwd.size() - 1; rev && i >= 0; --i) {
+        const RowPass &p = P.fwd[i];
+        col = p.col;
+        launch_rows<S_REV>(T, p, theta, lam[at(col)], psi[at(col)], partial, P.red_row0[i],
+                           i == 0 ? SF_NO_STORE : (T.is_long ? SF_TURN : 0), s, lam[at(1 - col)],
+                           psi[at(1 - col)]);
+    }
+    hipLaunchKernelGGL(k_sec_reduce, dim3(rev ? P.n_out : 1), dim3(256), 0, s, partial, kGrid,
+                       P.d_nblk, P.d_ptr, P.d_rows, P.d_scale, E, grad);
 }
 
 // Angles of every op and diagonal phase tables were once kept in the
@@ -1650,6 +1804,327 @@ size_t ang_bytes(const Tables &T, int layers)
 }
 
 }  // namespace sec
+
+// ---------------------------------------------------------------- batches --
+// energy_grad_batch on the sectors: one launch per position of the forward
+// schedules, two of H and one per position of the reverse schedules, each
+// running that pass of every instance that has one (launches of their own for
+// each workgroup size and diagonal kind, on streams of their own).
+// Every workgroup does what it does in the instance's own evaluation, and the
+// partial sums are added in the same order: a batch's results are those of
+// energy_grad bit for bit.
+
+struct SectorBatch {
+    struct Launch {
+        int kind;   // S_FWD, S_REV, 2: H
+        bool gen;
+        int threads, lane, item0, n_items;
+        uint32_t lds;
+    };
+    std::vector<Launch> launches;
+    size_t partial_at = 0;   // byte offset of the partial sums in the workspace
+    sec::RowsArgs *d_rows = nullptr;
+    sec::HamArgs *d_ham = nullptr;
+    sec::SecWork *d_work = nullptr;
+    int32_t *d_seg_ptr = nullptr, *d_seg_cnt = nullptr;
+    int64_t *d_seg_off = nullptr, *d_out_idx = nullptr;
+    double *d_scale = nullptr;
+    int n_out = 0;
+    char *blob = nullptr;
+    ~SectorBatch() { (void)hipFree(blob); }
+};
+
+// Workspace bytes that a batch on the sectors needs at most; 0: the instances
+// do not all have such a form.
+size_t sector_batch_bound(const hubbard_t *hs, int n, const int32_t *layers)
+{
+    size_t at = 0;
+    for (int i = 0; i < n; ++i) {
+        const Model &m = *handle_model(hs[i]);
+        const uint32_t smask = (1u << m.ns) - 1u;
+        const int ne = __builtin_popcount((uint32_t)m.neel & smask);
+        size_t c = 1;   // C(ns, ne)
+        for (int k = 1; k <= ne; ++k)
+            c = c * (size_t)(m.ns - ne + k) / (size_t)k;
+        const int G = m.ngroups;
+        if (m.ansatz != 0 || c > (size_t)sec::kShortRow || layers[i] < 1 ||
+            2 * G + 1 > sec::kMaxRed)
+            return 0;
+        const size_t rows = 2 + 2 * (size_t)layers[i] * (2 * G + 1);
+        at += 2 * sec::align256(c * c * 16) + sec::align256(rows * (c + 8) * 8);
+    }
+    return at;
+}
+
+// Plans and uploads a batch (NULL with *st HUBBARD_OK: not available).
+SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
+                                const int64_t *toff, const int32_t *layers, char *ws, int lanes,
+                                hubbard_status *st)
+{
+    using namespace sec;
+    *st = HUBBARD_OK;
+    if (sector_batch_bound(hs, n, layers) == 0)
+        return nullptr;
+    std::unique_ptr<SectorBatch> B(new SectorBatch());
+    std::vector<Tables *> T(n);
+    std::vector<Program *> P(n);
+    size_t at = 0;
+    std::vector<size_t> voff(n);
+    for (int i = 0; i < n; ++i) {
+        if ((*st = get(hs[i], layers[i], &T[i], &P[i])) != HUBBARD_OK)
+            return nullptr;
+        voff[i] = at;
+        at += 2 * align256(vec_elems(*T[i]) * 16);
+    }
+    B->partial_at = at;
+    set_attrs();
+    // instances by workgroup size and diagonal kind
+    std::map<std::pair<int, bool>, std::vector<int>> classes;
+    std::map<std::pair<int, bool>, double> cost;
+    for (int i = 0; i < n; ++i) {
+        const std::pair<int, bool> c{std::max(T[i]->sp[0].threads, T[i]->sp[1].threads),
+                                     T[i]->general};
+        classes[c].push_back(i);
+        cost[c] += (double)vec_elems(*T[i]) * layers[i];
+    }
+    std::vector<std::pair<int, bool>> order;
+    for (auto &kv : classes) {
+        // the largest instances' workgroups start first
+        std::stable_sort(kv.second.begin(), kv.second.end(), [&](int a, int b) {
+            return T[a]->n[0] > T[b]->n[0];
+        });
+        order.push_back(kv.first);
+    }
+    std::stable_sort(order.begin(), order.end(),
+                     [&](const std::pair<int, bool> &a, const std::pair<int, bool> &b) {
+                         return cost[a] > cost[b];
+                     });
+    // outputs: the energies, then every instance's gradient
+    std::vector<size_t> gbase(n);
+    size_t n_out = n;
+    for (int i = 0; i < n; ++i) {
+        gbase[i] = n_out;
+        n_out += (size_t)P[i]->n_out - 1;
+    }
+    std::vector<std::vector<std::pair<int64_t, int32_t>>> segs(n_out);
+    std::vector<double> scale(n_out, 0.5);
+    std::vector<int64_t> out_idx(n_out);
+    std::vector<int64_t> prow(n);   // first partial entry of each instance
+    std::vector<int> pstride(n);
+    int64_t np = 0;
+    for (int i = 0; i < n; ++i) {
+        prow[i] = np;
+        pstride[i] = std::max(rows_grid(*T[i], 0), rows_grid(*T[i], 1));
+        np += (int64_t)P[i]->n_rows * pstride[i];
+        scale[i] = 1.0;
+        out_idx[i] = i;
+        const Program &p = *P[i];
+        auto seg = [&](int row, int col) {
+            return std::make_pair(prow[i] + (int64_t)row * pstride[i],
+                                  (int32_t)rows_grid(*T[i], col));
+        };
+        segs[i].push_back(seg(0, p.final_col));
+        segs[i].push_back(seg(1, 1 - p.final_col));
+        for (size_t k = 0; k < p.fwd.size(); ++k)
+            for (int half = 0; half < 2; ++half)
+                for (size_t r = 0; r < p.fwd[k].red_param.size(); ++r)
+                    segs[gbase[i] + p.fwd[k].red_param[r]].push_back(
+                        seg(p.red_row0[k] + half * (int)p.fwd[k].red_param.size() + (int)r,
+                            p.fwd[k].col));
+        for (int k = 0; k + 1 < p.n_out; ++k)
+            out_idx[gbase[i] + k] = toff[i] + k;
+    }
+    double *partial = (double *)(ws + at);
+    std::vector<RowsArgs> rows;
+    std::vector<HamArgs> hams;
+    std::vector<SecWork> work;
+    size_t longest = 0;
+    for (int i = 0; i < n; ++i)
+        longest = std::max(longest, P[i]->fwd.size());
+    // position `pos` of kind `kind`: one launch per class that has one
+    auto position = [&](int kind, size_t pos) {
+        for (size_t c = 0; c < order.size(); ++c) {
+            SectorBatch::Launch L;
+            L.kind = kind;
+            L.gen = order[c].second;
+            L.lane = lanes > 1 ? (int)(c % (size_t)lanes) : 0;
+            L.item0 = (int)work.size();
+            L.threads = 64;
+            L.lds = 0;
+            for (int i : classes[order[c]]) {
+                const Tables &t = *T[i];
+                const Program &p = *P[i];
+                const size_t len = kind == 2 ? 2 : p.fwd.size();
+                if (pos >= len)
+                    continue;
+                double2 *psi = (double2 *)(ws + voff[i]);
+                double2 *lam = (double2 *)(ws + voff[i] + align256(vec_elems(t) * 16));
+                int grid, vecs = 1;
+                SecWork w;
+                if (kind == 2) {
+                    const int col = pos == 0 ? 1 - p.final_col : p.final_col;
+                    w.args = (int32_t)hams.size();
+                    hams.push_back(ham_args(t, col, pos == 1, psi, lam, pos == 0 ? HO_SET : HO_MIX,
+                                            false,
+                                            partial + prow[i] + (pos == 0 ? pstride[i] : 0)));
+                    grid = hams.back().grid;
+                    L.threads = std::max(L.threads, ham_threads(t.sp[col]));
+                    L.lds = std::max(L.lds, ham_lds(t, t.sp[col]));
+                } else {
+                    const size_t k = kind == S_FWD ? pos : len - 1 - pos;
+                    const RowPass &rp = p.fwd[k];
+                    const bool rev = kind == S_REV;
+                    w.args = (int32_t)rows.size();
+                    rows.push_back(rows_args(t, rp, rev, theta + toff[i], rev ? lam : psi,
+                                             rev ? psi : nullptr, partial + prow[i],
+                                             rev ? p.red_row0[k] : 0, pstride[i],
+                                             rev ? (k == 0 ? SF_NO_STORE : 0)
+                                                 : (k == 0 ? SF_START : 0),
+                                             nullptr, nullptr));
+                    grid = rows.back().grid;
+                    vecs = rev ? 2 : 1;
+                    L.threads = std::max(L.threads, t.sp[rp.col].threads);
+                    L.lds = std::max(L.lds, rows_lds(t, rp.col, rows.back().n_red));
+                }
+                for (int v = 0; v < vecs; ++v)
+                    for (int b = 0; b < grid; ++b) {
+                        w.bid = b;
+                        w.vsel = v;
+                        w.pad = 0;
+                        work.push_back(w);
+                    }
+            }
+            L.n_items = (int)work.size() - L.item0;
+            if (L.n_items)
+                B->launches.push_back(L);
+        }
+    };
+    for (size_t j = 0; j < longest; ++j)
+        position(S_FWD, j);
+    position(2, 0);
+    position(2, 1);
+    for (size_t j = 0; j < longest; ++j)
+        position(S_REV, j);
+    std::vector<int32_t> seg_ptr{0}, seg_cnt;
+    std::vector<int64_t> seg_off;
+    for (auto &v : segs) {
+        for (auto &q : v) {
+            seg_off.push_back(q.first);
+            seg_cnt.push_back(q.second);
+        }
+        seg_ptr.push_back((int32_t)seg_off.size());
+    }
+    B->n_out = (int)n_out;
+    Blob blob;
+    blob.add(&B->d_rows, rows);
+    blob.add(&B->d_ham, hams);
+    blob.add(&B->d_work, work);
+    blob.add(&B->d_seg_ptr, seg_ptr);
+    blob.add(&B->d_seg_cnt, seg_cnt);
+    blob.add(&B->d_seg_off, seg_off);
+    blob.add(&B->d_out_idx, out_idx);
+    blob.add(&B->d_scale, scale);
+    const hipError_t e = blob.upload(&B->blob);
+    if (e != hipSuccess) {
+        *st = fail(HUBBARD_ERR_DEVICE, std::string("uploading batch: ") + hipGetErrorString(e));
+        return nullptr;
+    }
+    return B.release();
+}
+
+void sector_batch_free(SectorBatch *b) { delete b; }
+
+// Whether a launch runs on stream `lane` of the batch.
+bool sector_batch_uses(const SectorBatch *b, int lane)
+{
+    for (const SectorBatch::Launch &l : b->launches)
+        if (l.lane == lane)
+            return true;
+    return false;
+}
+
+// The launches of a batch on its lanes' streams (forked and joined by the caller).
+void sector_batch_launch(const SectorBatch *b, const hipStream_t *lane)
+{
+    using namespace sec;
+    for (const SectorBatch::Launch &l : b->launches) {
+        const SecWork *w = b->d_work + l.item0;
+        hipStream_t s = lane[l.lane];
+#define HV_SEC_BATCH(K, ARGS)                                                                   \
+    hipLaunchKernelGGL((K), dim3(l.n_items), dim3(l.threads), l.lds, s, ARGS, w)
+        if (l.kind == 2) {
+            if (l.gen)
+                HV_SEC_BATCH(k_sec_ham_batch<true>, b->d_ham);
+            else
+                HV_SEC_BATCH(k_sec_ham_batch<false>, b->d_ham);
+        } else if (l.kind == S_FWD) {
+            if (l.gen)
+                HV_SEC_BATCH((k_sec_rows_batch<S_FWD, true>), b->d_rows);
+            else
+                HV_SEC_BATCH((k_sec_rows_batch<S_FWD, false>), b->d_rows);
+        } else {
+            if (l.gen)
+                HV_SEC_BATCH((k_sec_rows_batch<S_REV, true>), b->d_rows);
+            else
+                HV_SEC_BATCH((k_sec_rows_batch<S_REV, false>), b->d_rows);
+        }
+#undef HV_SEC_BATCH
+    }
+}
+
+// The reduction's tables (k_reduce_seg), and where the partial sums are.
+void sector_batch_reduction(const SectorBatch *b, const int32_t **seg_ptr,
+                            const int64_t **seg_off, const int32_t **seg_cnt,
+                            const double **scale, const int64_t **out_idx, int *n_out,
+                            size_t *partial_at)
+{
+    *seg_ptr = b->d_seg_ptr;
+    *seg_off = b->d_seg_off;
+    *seg_cnt = b->d_seg_cnt;
+    *scale = b->d_scale;
+    *out_idx = b->d_out_idx;
+    *n_out = b->n_out;
+    *partial_at = b->partial_at;
+}
+
+// The evaluations of the full-vector entry points (energy, energy_grad,
+// energy_grad_noalloc) in the sector form: their circuits start from |b0>, so
+// every amplitude outside its sector is zero throughout.
+// Workspace bytes, uploading the tables if they are not there; 0: not
+// available for this model (then the full vector is used).
+size_t sector_eval_bytes(hubbard_t h, int layers, bool grad)
+{
+    sec::Tables *T = nullptr;
+    sec::Program *P = nullptr;
+    return sec::get(h, layers, &T, &P) == HUBBARD_OK ? sec::eval_bytes(*T, *P, grad) : 0;
+}
+
+// The same for tables already uploaded (allocates nothing; 0: not there).
+size_t sector_eval_ready(hubbard_t h, int layers)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess)
+        return 0;
+    std::lock_guard<std::mutex> lk(sec::g_mu);
+    auto it = sec::g_cache.find(std::make_pair(handle_uid(h), dev));
+    if (it == sec::g_cache.end() || !it->second.tab)
+        return 0;
+    auto p = it->second.progs.find(layers);
+    return p == it->second.progs.end() ? 0 : sec::eval_bytes(*it->second.tab, *p->second);
+}
+
+// grad NULL: the energy only.
+hubbard_status sector_eval(hubbard_t h, int layers, const double *theta, double *E, double *grad,
+                           void *ws, hipStream_t s)
+{
+    sec::Tables *T = nullptr;
+    sec::Program *P = nullptr;
+    hubbard_status st = sec::get(h, layers, &T, &P);
+    if (st != HUBBARD_OK)
+        return st;
+    sec::evaluate(*T, *P, theta, E, grad, (char *)ws, s);
+    return sec::check("sector evaluation");
+}
 
 // Drop the sector tables and programs of a destroyed handle.
 void sector_forget(uint64_t uid)
@@ -1696,7 +2171,7 @@ hubbard_status hubbard_sector_workspace_size(hubbard_t h, int32_t n_layers, int3
     else if (op == HUBBARD_SECTOR_LANCZOS)
         *bytes = 5 * v + lanczos_partial_bytes();
     else
-        *bytes = 4 * v + align256((size_t)P->n_rows * kGrid * 8) + ang_bytes(*T, n_layers);
+        *bytes = eval_bytes(*T, *P) + ang_bytes(*T, n_layers);
     return HUBBARD_OK;
 }
 
@@ -1750,7 +2225,7 @@ hubbard_status sector_hamiltonian_apply(hubbard_t h, const void *psi_dev, void *
     set_attrs();
     if (T->is_long)
         transpose(*T, 0, (const double2 *)psi_dev, (double2 *)ws_dev, (hipStream_t)stream);
-    hamiltonian(*T, 0, (double2 *)psi_dev, (double2 *)out_dev, (double2 *)ws_dev, false, nullptr,
+    hamiltonian(*T, 0, (double2 *)psi_dev, (double2 *)out_dev, (double2 *)ws_dev, HO_ADD, nullptr,
                 (hipStream_t)stream);
     return check("sector H");
 }
@@ -1784,7 +2259,7 @@ hubbard_status hubbard_sector_lanczos(hubbard_t h, const void *start_dev, int32_
     const ApplyH apply = [&](const double2 *in, double2 *out) {
         if (T->is_long)
             transpose(*T, 0, in, in_b, s);
-        hamiltonian(*T, 0, (double2 *)in, out, in_b, false, nullptr, s);
+        hamiltonian(*T, 0, (double2 *)in, out, in_b, HO_ADD, nullptr, s);
         return check("sector H");
     };
     return lanczos_run(apply, n, (const double2 *)start_dev, max_iter, tol, E0, iters, residual,
@@ -1802,42 +2277,8 @@ hubbard_status sector_energy_grad(hubbard_t h, const double *theta_dev, int32_t 
     hubbard_status st = get(h, n_layers, &T, &P);
     if (st != HUBBARD_OK)
         return st;
-    const size_t v = align256(vec_elems(*T) * 16);
-    const size_t pbytes = align256((size_t)P->n_rows * kGrid * 8);
-    if (!ws_dev || ws_bytes < 4 * v + pbytes + ang_bytes(*T, n_layers))
+    if (!ws_dev || ws_bytes < eval_bytes(*T, *P) + ang_bytes(*T, n_layers))
         return set_error(HUBBARD_ERR_SIZE, "workspace too small for sector_energy_grad");
-    set_attrs();
-    hipStream_t s = (hipStream_t)stream;
-    char *w = (char *)ws_dev;
-    // the two layouts' buffers (short rows: one layout, index 0)
-    double2 *psi[2] = {(double2 *)w, (double2 *)(w + v)};
-    double2 *lam[2] = {(double2 *)(w + 2 * v), (double2 *)(w + 3 * v)};
-    double *partial = (double *)(w + 4 * v);
-    auto at = [&](int col) { return T->is_long ? col : 0; };
-    if (P->fwd.empty()) {
-        hipLaunchKernelGGL(k_sec_basis, dim3(2048), dim3(256), 0, s, psi[0], vec_elems(*T),
-                           T->b0_pos);
-        if (T->is_long)
-            transpose(*T, 0, psi[0], psi[1], s);
-    }
-    double2 *end = forward(*T, *P, theta_dev, psi[0], psi[1], true, true, s);
-    int col = P->final_col;
-    if (end != psi[at(col)]) {   // cannot happen: layout A lives in psi[0], B in psi[1]
-        return set_error(HUBBARD_ERR_STATE, "sector forward ended in the wrong buffer");
-    }
-    // lambda = H psi, the partial rows 0 and 1 get E; the reverse sweep runs
-    // on chi1 = lambda + i psi (psi's buffers) and chi2 = lambda - i psi
-    // (lambda's): brackets from their expectations
-    hamiltonian(*T, col, psi[at(col)], lam[at(col)], psi[at(1 - col)], !P->fwd.empty(), partial,
-                s);
-    for (int i = (int)P->fwd.size() - 1; i >= 0; --i) {
-        const RowPass &p = P->fwd[i];
-        col = p.col;
-        launch_rows<S_REV>(*T, p, theta_dev, lam[at(col)], psi[at(col)], partial, P->red_row0[i],
-                           i == 0 ? SF_NO_STORE : (T->is_long ? SF_TURN : 0), s, lam[at(1 - col)],
-                           psi[at(1 - col)]);
-    }
-    hipLaunchKernelGGL(k_sec_reduce, dim3(P->n_out), dim3(256), 0, s, partial, kGrid,
-                       P->d_nblk, P->d_ptr, P->d_rows, P->d_scale, E_dev, grad_dev);
+    evaluate(*T, *P, theta_dev, E_dev, grad_dev, (char *)ws_dev, (hipStream_t)stream);
     return check("sector energy_grad");
 }
