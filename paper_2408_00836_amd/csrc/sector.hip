@@ -123,8 +123,8 @@ template <int CTRL>
 __device__ __forceinline__ double row_dpp(double y)
 {
     const long long b = __double_as_longlong(y);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
@@ -186,8 +186,8 @@ __host__ __device__ constexpr int duo(int a, int b)
 // two electrons, x[6..9] one (by its site), x[10..13] three (by the empty
 // site).  The orbits' sign bits are those of Rec.
 //   REV: w <- w + the sum over the pairs of sign Re(conj(x_a) x_b), before the rotation
-template <bool REV, int Q>
-__device__ __forceinline__ void hop2(double2 (&x)[kOrbitElems], double2 cs, uint32_t f, double &w)
+template <bool REV, int Q, int N>
+__device__ __forceinline__ void hop2(double2 (&x)[N], double2 cs, uint32_t f, double &w)
 {
     constexpr int A = kPosA[Q], B = kPosB[Q];
     constexpr int E0 = A != 0 && B != 0 ? 0 : (A != 1 && B != 1 ? 1 : 2);
@@ -200,17 +200,17 @@ __device__ __forceinline__ void hop2(double2 (&x)[kOrbitElems], double2 cs, uint
     rotate(x[a1], x[b1], cs.x, xor_sign(cs.y, m1));
 }
 
-template <bool REV, int Q>
-__device__ __forceinline__ void hop13(double2 (&x)[kOrbitElems], double2 cs, uint32_t f1,
-                                      uint32_t f3, double &w)
+// O: where the one-electron orbit begins (the three-electron one follows).
+template <bool REV, int Q, int O, int N>
+__device__ __forceinline__ void hop13(double2 (&x)[N], double2 cs, uint32_t f1, uint32_t f3,
+                                      double &w)
 {
-    constexpr int A = kPosA[Q], B = kPosB[Q];
+    constexpr int A1 = O + kPosA[Q], B1 = O + kPosB[Q], A3 = A1 + 4, B3 = B1 + 4;
     const uint32_t m1 = (f1 << (8 + Q)) & 0x80000000u, m3 = (f3 << (12 + Q)) & 0x80000000u;
     if constexpr (REV)
-        w += xor_sign(re_dot(x[6 + A], x[6 + B]), m1) +
-             xor_sign(re_dot(x[10 + A], x[10 + B]), m3);
-    rotate(x[6 + A], x[6 + B], cs.x, xor_sign(cs.y, m1));
-    rotate(x[10 + A], x[10 + B], cs.x, xor_sign(cs.y, m3));
+        w += xor_sign(re_dot(x[A1], x[B1]), m1) + xor_sign(re_dot(x[A3], x[B3]), m3);
+    rotate(x[A1], x[B1], cs.x, xor_sign(cs.y, m1));
+    rotate(x[A3], x[B3], cs.x, xor_sign(cs.y, m3));
 }
 
 // LDS of a row pass.
@@ -297,58 +297,123 @@ struct RowPassCtx {
             acc[i] = 0.0;
     }
     // a thread's sum of one reduction slot's terms into that slot: four lanes
-    // are added in registers, one of them adds to its LDS entry
+    // are added in registers, one of them adds to the four's own LDS entry (an
+    // add that nothing waits for)
     __device__ __forceinline__ void flush(int slot, double &racc)
     {
         double x = racc;
         x += row_dpp<0xB1>(x);
         x += row_dpp<0x4E>(x);
         if ((tid & 3) == 0)
-            acc[slot * (T / 4) + (tid >> 2)] += x;
+            __hip_atomic_fetch_add(&acc[slot * (T / 4) + (tid >> 2)], x, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
         racc = 0.0;
     }
-    // positions Q, Q + 1 (one matching) of phase ph on a thread's orbits
-    template <int Q>
-    __device__ __forceinline__ void matching(double2 (&x)[kOrbitElems], int run, int ph,
-                                             uint32_t f2, uint32_t f1, uint32_t f3, bool w2,
-                                             bool w13, double &racc)
+    // what a phase's hops need besides the orbits, read before anything waits:
+    // angles, and in reverse the weights -2 t (<chi|G|chi> counts every pair
+    // twice) and reduction slots
+    struct PhaseArgs {
+        double2 c[kPositions];
+        double t[kPositions];
+        int slot[kPositions], last[kPositions];
+    };
+    __device__ __forceinline__ PhaseArgs phase_args(int run, int ph) const
     {
-        const double2 *an = ang + (run * A.n_phases + ph) * kPositions + Q;
-        const double2 c0 = an[0], c1 = an[1];
+        PhaseArgs a;
+        const double2 *an = ang + (run * A.n_phases + ph) * kPositions;
+        const kGate *g = (const kGate *)A.gates + ph * kPositions;
+        const int base = (run ? post_slot : 0) - 1;
+#pragma unroll
+        for (int q = 0; q < kPositions; ++q) {
+            a.c[q] = an[q];
+            if constexpr (REV) {
+                a.t[q] = -2.0 * g[q].t;
+                a.slot[q] = base + g[q].slot;
+                a.last[q] = g[q].last;
+            }
+        }
+        return a;
+    }
+    // positions Q, Q + 1 (one matching): two(c0, c1, p0, p1) applies them to
+    // the thread's orbits
+    template <int Q, typename F>
+    __device__ __forceinline__ void matching(const PhaseArgs &a, double &racc, F &&two)
+    {
         double p0 = 0.0, p1 = 0.0;
-        if (w2) {
-            hop2<REV, Q>(x, c0, f2, p0);
-            hop2<REV, Q + 1>(x, c1, f2, p1);
-        }
-        if (w13) {
-            hop13<REV, Q>(x, c0, f1, f3, p0);
-            hop13<REV, Q + 1>(x, c1, f1, f3, p1);
-        }
+        two(a.c[Q], a.c[Q + 1], p0, p1);
         if constexpr (REV) {
-            // <chi|G|chi> counts every pair twice; the position executed
-            // next decides whether the sum goes on
-            const kGate *g = (const kGate *)A.gates + ph * kPositions + Q;
-            const int base = (run ? post_slot : 0) - 1;
-            racc = fma(-2.0 * g[1].t, p1, racc);
-            if (g[0].slot != g[1].slot)
-                flush(base + g[1].slot, racc);
-            racc = fma(-2.0 * g[0].t, p0, racc);
-            if (Q == 0 || g[-1].slot != g[0].slot)
-                flush(base + g[0].slot, racc);
+            racc = fma(a.t[Q + 1], p1, racc);
+            if (a.last[Q + 1])
+                flush(a.slot[Q + 1], racc);
+            racc = fma(a.t[Q], p0, racc);
+            if (a.last[Q])
+                flush(a.slot[Q], racc);
         }
     }
-    // the phase's hops on a thread's orbits
-    __device__ __forceinline__ void gates(double2 (&x)[kOrbitElems], int run, int ph, uint32_t f2,
-                                          uint32_t f1, uint32_t f3, bool w2, bool w13)
+    template <typename F0, typename F2>
+    __device__ __forceinline__ void both(const PhaseArgs &a, F0 &&first, F2 &&second)
     {
         double racc = 0.0;
         if constexpr (!REV) {
-            matching<0>(x, run, ph, f2, f1, f3, w2, w13, racc);
-            matching<2>(x, run, ph, f2, f1, f3, w2, w13, racc);
+            matching<0>(a, racc, first);
+            matching<2>(a, racc, second);
         } else {
-            matching<2>(x, run, ph, f2, f1, f3, w2, w13, racc);
-            matching<0>(x, run, ph, f2, f1, f3, w2, w13, racc);
+            matching<2>(a, racc, second);
+            matching<0>(a, racc, first);
         }
+    }
+    // the phase's hops on an orbit of six
+    __device__ __forceinline__ void gates2(double2 (&x)[6], const PhaseArgs &a, uint32_t f)
+    {
+        both(a,
+             [&](double2 c0, double2 c1, double &p0, double &p1) __attribute__((always_inline)) {
+                 hop2<REV, 0>(x, c0, f, p0);
+                 hop2<REV, 1>(x, c1, f, p1);
+             },
+             [&](double2 c0, double2 c1, double &p0, double &p1) __attribute__((always_inline)) {
+                 hop2<REV, 2>(x, c0, f, p0);
+                 hop2<REV, 3>(x, c1, f, p1);
+             });
+    }
+    // on two orbits of four
+    __device__ __forceinline__ void gates13(double2 (&x)[8], const PhaseArgs &a, uint32_t f1,
+                                            uint32_t f3)
+    {
+        both(a,
+             [&](double2 c0, double2 c1, double &p0, double &p1) __attribute__((always_inline)) {
+                 hop13<REV, 0, 0>(x, c0, f1, f3, p0);
+                 hop13<REV, 1, 0>(x, c1, f1, f3, p1);
+             },
+             [&](double2 c0, double2 c1, double &p0, double &p1) __attribute__((always_inline)) {
+                 hop13<REV, 2, 0>(x, c0, f1, f3, p0);
+                 hop13<REV, 3, 0>(x, c1, f1, f3, p1);
+             });
+    }
+    // on all of a long row's orbits (w2, w13: the wave has any of the kind)
+    __device__ __forceinline__ void gates(double2 (&x)[kOrbitElems], const PhaseArgs &a, uint32_t f,
+                                          bool w2, bool w13)
+    {
+        both(a,
+             [&](double2 c0, double2 c1, double &p0, double &p1) __attribute__((always_inline)) {
+                 if (w2) {
+                     hop2<REV, 0>(x, c0, f, p0);
+                     hop2<REV, 1>(x, c1, f, p1);
+                 }
+                 if (w13) {
+                     hop13<REV, 0, 6>(x, c0, f, f, p0);
+                     hop13<REV, 1, 6>(x, c1, f, f, p1);
+                 }
+             },
+             [&](double2 c0, double2 c1, double &p0, double &p1) __attribute__((always_inline)) {
+                 if (w2) {
+                     hop2<REV, 2>(x, c0, f, p0);
+                     hop2<REV, 3>(x, c1, f, p1);
+                 }
+                 if (w13) {
+                     hop13<REV, 2, 6>(x, c0, f, f, p0);
+                     hop13<REV, 3, 6>(x, c1, f, f, p1);
+                 }
+             });
     }
     // the workgroup's partial sums (after a barrier)
     __device__ void finish(int bid, int vsel, bool negate)
@@ -429,7 +494,10 @@ __device__ __forceinline__ int group_of(int i, int n)
 // per vector).  One exchange per phase instead of one per hop, several rows
 // per workgroup and no transposes took its energy+gradient evaluation with
 // the general diagonal from 4.19 to 1.03 ms, and a 20-qubit chain's from 0.554
-// to 0.283 ms.
+// to 0.283 ms.  Half the threads for the orbits of six and half for those of
+// four, a phase's records and scalars fetched a phase ahead, and the diagonal's
+// tables four elements at a time: 1.02 and 0.189 ms; a 16-qubit chain 0.219 to
+// 0.149 ms, a 28-qubit ladder 4.18 to 3.36 ms.
 //   S_FWD: v[0] <- ops applied.  SF_START: the input is |b0>, not read; the
 //          rows without it are zero.
 //   S_REV: vsel picks chi2 = v[0] or chi1 = v[1]; the ops un-applied in
@@ -453,14 +521,17 @@ __device__ __forceinline__ void rows_short(const AT &A, int bid, int vsel, char 
     const gu16 *__restrict__ colslot = (const gu16 *)A.colslot;
     const gu16 *__restrict__ patslot = (const gu16 *)A.patslot;
     const gu128 *__restrict__ recs = (const gu128 *)A.recs;
-    const kPhase *__restrict__ phases = (const kPhase *)A.phases;
     C.prologue();
     for (int i = tid; i < (A.nslots + 1) << lr; i += T)   // holes and the dummy slot stay zero
         vec[i] = make_double2(0.0, 0.0);
     const int n_pre = A.l_pre >= 0 ? A.n_phases : 0;
     const int n_steps = n_pre + (A.l_post >= 0 ? A.n_phases : 0);
-    const int row = tid & (R - 1), orb = tid >> lr;
-    const int worb = __builtin_amdgcn_readfirstlane(tid & ~63) >> lr;   // the wave's first orbit
+    // the first half of the threads takes the orbits of six, the second half
+    // those of four (a thread one with one and one with three electrons): the
+    // same work for either, in half the time of one thread taking all three
+    const int TH = T >> 1;
+    const bool duo_half = __builtin_amdgcn_readfirstlane(tid) < TH;
+    const int row = tid & (R - 1), orb = (duo_half ? tid : tid - TH) >> lr, lanes = TH >> lr;
     const uint32_t rofs = (uint32_t)row * 16u;
     const int ng = (A.n_rows + R - 1) >> lr, total = A.n << lr;
 
@@ -538,19 +609,37 @@ __device__ __forceinline__ void rows_short(const AT &A, int bid, int vsel, char 
             const double *nb = nib + row * 64;
             const gf64 *baseslot = (const gf64 *)A.baseslot;
             double racc = 0.0;
-            for (int i = tid; i < A.nslots << lr; i += T) {
-                const int sl = i >> lr;
-                const uint32_t cp = patslot[sl];
-                double2 a = vec[i];
-                if constexpr (GEN) {
-                    double err;
-                    const double d = diag_gen(rb, baseslot[sl], nb, cp, err);
-                    diag_el<REV, true>(a, d, err, a, th, C.dtab, racc);
-                } else {
-                    const int k = __popc(rp & cp);
-                    diag_el<REV, false>(a, A.U * (double)k, 0.0, C.dtab[k], th, nullptr, racc);
+            const int last = (A.nslots << lr) - 1;
+            for (int i0 = tid; i0 <= last; i0 += 4 * T) {
+                uint32_t cp[4];
+                double cb[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {   // the tables' loads in flight together
+                    const int sl = min(i0 + u * T, last) >> lr;
+                    cp[u] = patslot[sl];
+                    cb[u] = GEN ? baseslot[sl] : 0.0;
                 }
-                vec[i] = a;
+                double2 a[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    a[u] = vec[min(i0 + u * T, last)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    double sum = racc;
+                    if constexpr (GEN) {
+                        double err;
+                        const double d = diag_gen(rb, cb[u], nb, cp[u], err);
+                        diag_el<REV, true>(a[u], d, err, a[u], th, C.dtab, sum);
+                    } else {
+                        const int k = __popc(rp & cp[u]);
+                        diag_el<REV, false>(a[u], A.U * (double)k, 0.0, C.dtab[k], th, nullptr,
+                                            sum);
+                    }
+                    if (i0 + u * T <= last) {
+                        vec[i0 + u * T] = a[u];
+                        racc = sum;
+                    }
+                }
             }
             if constexpr (REV)
                 C.flush(C.dslot, racc);
@@ -558,74 +647,64 @@ __device__ __forceinline__ void rows_short(const AT &A, int bid, int vsel, char 
         };
         // records of a step's orbits (the next step's are fetched while one runs)
         struct Recs {
-            uint4 q[3];
+            uint4 a, b;
         };
         auto fetch = [&](int st) __attribute__((always_inline)) {
-            const kPhase &ph = phases[st < A.n_phases ? st : st - A.n_phases];
-            Recs q;
-            const int n2 = ph.n[0], n1 = ph.n[1], n3 = ph.n[2], at = ph.rec;
-            auto ld = [&](int i) {
+            const int first = (3 * (st < A.n_phases ? st : st - A.n_phases) + (duo_half ? 0 : 1)) *
+                                  lanes + orb;
+            auto ld = [&](int i) __attribute__((always_inline)) {
                 const gu128 *p = recs + i;
                 return make_uint4(p->x, p->y, p->z, p->w);
             };
-            // lanes past a list's end read its last record (and do nothing with it)
-            q.q[0] = n2 ? ld(at + min(orb, n2 - 1)) : make_uint4(0, 0, 0, 0);
-            q.q[1] = n1 ? ld(at + n2 + min(orb, n1 - 1)) : make_uint4(0, 0, 0, 0);
-            q.q[2] = n3 ? ld(at + n2 + n1 + min(orb, n3 - 1)) : make_uint4(0, 0, 0, 0);
+            Recs q;
+            q.a = ld(first);
+            q.b = ld(first + (duo_half ? 0 : lanes));   // no branch around a load in flight
             return q;
         };
-        auto lo = [&](uint32_t w) { return ((w & 0xFFFFu) << 4) + rofs; };
-        auto hi = [&](uint32_t w) { return ((w >> 16) << 4) + rofs; };
-        auto at = [&](uint32_t o) -> double2 & { return *(double2 *)(smem + o); };
+        // element j of a record
+        auto at = [&](const uint4 &q, int j) __attribute__((always_inline)) -> double2 & {
+            const uint32_t w = j < 2 ? q.x : (j < 4 ? q.y : q.z);
+            return *(double2 *)(smem + ((j & 1 ? w >> 16 : w & 0xFFFFu) << 4) + rofs);
+        };
         auto phase = [&](int st, const Recs &q) __attribute__((always_inline)) {
             const int p = st < A.n_phases ? st : st - A.n_phases;
-            const kPhase &ph = phases[p];
-            const int n2 = ph.n[0], n1 = ph.n[1], n3 = ph.n[2];
-            const bool w2 = worb < n2, w13 = worb < n1 || worb < n3;   // wave-uniform
-            const bool a2 = orb < n2, a1 = orb < n1, a3 = orb < n3;
-            double2 x[kOrbitElems];
+            const typename RowPassCtx<MODE, GEN, AT>::PhaseArgs pa =
+                C.phase_args(st < n_pre ? 0 : 1, p);
+            if (duo_half) {
+                const bool act = q.a.w & 1u;
+                if (__ballot(act)) {
+                    double2 x[6];
 #pragma unroll
-            for (int j = 0; j < kOrbitElems; ++j)
-                x[j] = make_double2(0.0, 0.0);
-            if (a2) {
+                    for (int j = 0; j < 6; ++j)
+                        x[j] = at(q.a, j);
+                    C.gates2(x, pa, q.a.w);
+                    if (act) {
 #pragma unroll
-                for (int j = 0; j < 6; ++j) {
-                    const uint32_t w = j < 2 ? q.q[0].x : (j < 4 ? q.q[0].y : q.q[0].z);
-                    x[j] = at(j & 1 ? hi(w) : lo(w));
+                        for (int j = 0; j < 6; ++j)
+                            at(q.a, j) = x[j];
+                    }
                 }
-            }
-            if (a1) {
+            } else {
+                const bool a1 = q.a.z & 1u, a3 = q.b.z & 1u;
+                if (__ballot(a1 || a3)) {
+                    double2 x[8];
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    x[6 + j] = at(j & 1 ? hi(j < 2 ? q.q[1].x : q.q[1].y)
-                                        : lo(j < 2 ? q.q[1].x : q.q[1].y));
-            }
-            if (a3) {
+                    for (int j = 0; j < 4; ++j) {
+                        x[j] = at(q.a, j);
+                        x[4 + j] = at(q.b, j);
+                    }
+                    C.gates13(x, pa, q.a.z, q.b.z);
+                    if (a1) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    x[10 + j] = at(j & 1 ? hi(j < 2 ? q.q[2].x : q.q[2].y)
-                                         : lo(j < 2 ? q.q[2].x : q.q[2].y));
-            }
-            if (w2 || w13)
-                C.gates(x, st < n_pre ? 0 : 1, p, q.q[0].w, q.q[1].w, q.q[2].w, w2, w13);
-            if (a2) {
+                        for (int j = 0; j < 4; ++j)
+                            at(q.a, j) = x[j];
+                    }
+                    if (a3) {
 #pragma unroll
-                for (int j = 0; j < 6; ++j) {
-                    const uint32_t w = j < 2 ? q.q[0].x : (j < 4 ? q.q[0].y : q.q[0].z);
-                    at(j & 1 ? hi(w) : lo(w)) = x[j];
+                        for (int j = 0; j < 4; ++j)
+                            at(q.b, j) = x[4 + j];
+                    }
                 }
-            }
-            if (a1) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    at(j & 1 ? hi(j < 2 ? q.q[1].x : q.q[1].y)
-                             : lo(j < 2 ? q.q[1].x : q.q[1].y)) = x[6 + j];
-            }
-            if (a3) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    at(j & 1 ? hi(j < 2 ? q.q[2].x : q.q[2].y)
-                             : lo(j < 2 ? q.q[2].x : q.q[2].y)) = x[10 + j];
             }
             __syncthreads();
         };
@@ -890,7 +969,7 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
             if (!REV && st == n_pre && A.l_diag >= 0)
                 diag();
             const uint32_t f = cur.w[7];
-            C.gates(x, st < n_pre ? 0 : 1, ph_of(st), f, f, f, wave0 < ph.n[0],
+            C.gates(x, C.phase_args(st < n_pre ? 0 : 1, ph_of(st)), f, wave0 < ph.n[0],
                     wave0 < ph.n[1] || wave0 < ph.n[2]);
             if (REV && st == n_pre && A.l_diag >= 0)
                 diag();
@@ -1654,7 +1733,7 @@ HamArgs ham_args(const Tables &T, int col, bool with_d, double2 *psi, double2 *o
 }
 
 // Short rows' H: about an element per thread and round.
-int ham_threads(const SpinTables &S) { return std::min(1024, 4 * S.threads); }
+int ham_threads(const SpinTables &S) { return std::min(1024, 2 * S.threads); }
 uint32_t ham_lds(const Tables &T, const SpinTables &S)
 {
     return short_vec_bytes(S.nslots, S.lr) + (T.general ? (64u << S.lr) * 8u : 0u) + 16u * 8u;

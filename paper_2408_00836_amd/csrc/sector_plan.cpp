@@ -141,6 +141,10 @@ void plan_clusters(const Model &m, SectorPlan &P)
             P.gates.push_back(g);
         }
         std::reverse(P.gates.end() - kPositions, P.gates.end());
+        for (int q = 0; q < kPositions; ++q) {
+            SecGate *g = &P.gates[P.gates.size() - kPositions + q];
+            g->last = q == 0 || g[-1].slot != g->slot;
+        }
         todo = without(w);
     } while (!todo.empty());
 }
@@ -200,8 +204,8 @@ std::vector<uint32_t> deal(const std::vector<uint32_t> &list, int M, const uint3
 }
 
 // Rows of a workgroup (log2), threads and bank classes of short rows.
-//   rows: as many as leave >= kMinGroups workgroups, at most kMaxWgT threads
-//   and kRowsLds bytes of rows (two workgroups per CU); at least one.
+//   rows: as many as leave >= kMinGroups workgroups, at most kMaxWgT lanes per
+//   list and kRowsLds bytes of rows (two workgroups per CU); at least one.
 constexpr int kMinGroups = 60;
 constexpr int kMaxWgT = 512;
 constexpr int kRowsLds = 72 * 1024;
@@ -213,7 +217,7 @@ void shape(SpinPlan &S, int n_rows, int longest_list)
            (longest_list << (S.lr + 1)) <= kMaxWgT && ((S.n * 16) << (S.lr + 1)) <= kRowsLds)
         ++S.lr;
     const int lanes = std::max(1, longest_list << S.lr);
-    S.threads = std::min(1024, (lanes + 63) / 64 * 64);
+    S.threads = 2 * ((lanes + 63) / 64 * 64);   // a half for the orbits of six, one for the others
     S.classes = std::max(1, 16 >> S.lr);
 }
 
@@ -327,7 +331,6 @@ void build_spin(const Model &m, SectorPlan &P, int s, int n_rows)
         SecPhase D{};
         static const int kOrder[3] = {2, 1, 3};
         if (!S.is_long) {
-            D.rec = (int)S.recs.size();
             for (int l = 0; l < 3; ++l) {
                 const int k = kOrder[l];
                 const std::vector<uint32_t> o = deal(orbits(S, ns, c, k), M, best_v);
@@ -341,9 +344,14 @@ void build_spin(const Model &m, SectorPlan &P, int s, int n_rows)
                     Rec R;
                     for (int i = 0; i < 4; ++i)
                         R.w[i] = (uint32_t)e[2 * i] | ((uint32_t)e[2 * i + 1] << 16);
-                    R.w[3] = flags(k, r);
+                    R.w[k == 2 ? 3 : 2] = flags(k, r) | 1u;
                     S.recs.push_back(R);
                 }
+                // the lanes without an orbit read the zero slot
+                const uint32_t z = (uint32_t)(S.nslots << S.lr);
+                Rec none = {{z | z << 16, z | z << 16, k == 2 ? z | z << 16 : 0, 0}};
+                for (int i = D.n[l]; i < (S.threads / 2) >> S.lr; ++i)
+                    S.recs.push_back(none);
             }
         } else {
             const size_t at = S.lcode.size();

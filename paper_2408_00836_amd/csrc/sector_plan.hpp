@@ -44,26 +44,26 @@ constexpr int kPositions = 4;
 constexpr int kPosA[kPositions] = {0, 2, 0, 1}, kPosB[kPositions] = {1, 3, 2, 3};
 struct SecGate {
     int32_t slot;    // parameter slot in the layer, 1..groups
-    int32_t pad;
+    int32_t last;    // reverse order: the phase's next position has another slot
     double t;        // hopping t_b
 };
 static_assert(sizeof(SecGate) == 16, "SecGate layout");
 
-// One phase of one spin.  Short rows: n[] orbits with 2, 1, 3 electrons,
-// their records (uint4 each) starting at rec, list after list; long rows: n[]
-// only.
+// One phase of a long row: orbits with 2, 1, 3 electrons.
 struct SecPhase {
     int32_t n[3];
-    int32_t rec;
+    int32_t pad;
 };
 static_assert(sizeof(SecPhase) == 16, "SecPhase layout");
 
 // A phase record of a short row (16 bytes): u16 slots of the orbit's elements
 // (6 for k = 2 in the order 01 02 03 12 13 23, 4 for k = 1 by the occupied
-// site and for k = 3 by the empty one), and in the last dword the hops'
+// site and for k = 3 by the empty one), and in the dword after them the hops'
 // Jordan-Wigner signs: with two electrons bit 31 - (2 q + e) for position q
 // and the e-th of the two spectator sites, with one bit 23 - q, with three
-// bit 19 - q.
+// bit 19 - q; bit 0 is set.  A phase's records are three lists (k = 2, 1, 3),
+// each filled up to the lanes of half a workgroup with records of the zero
+// slot (bit 0 clear).
 struct Rec {
     uint32_t w[4];
 };
@@ -85,7 +85,7 @@ struct SpinPlan {
     std::vector<double> baseslot;    // the same per slot
     std::vector<double> wrow;        // per rank: 16 x (U p_j + sum_i V_ij p_i)
     std::vector<SecPhase> phases;
-    std::vector<Rec> recs;           // short rows
+    std::vector<Rec> recs;           // short rows: phase by phase, three lists each
     std::vector<uint32_t> lcode;     // long rows: per phase and thread 8 dwords: 15 u16 slots
                                      // and the upper half of the three orbits' sign bits
     std::vector<uint32_t> lpat;      // long rows: phase 0's patterns, 8 dwords per thread
