@@ -42,8 +42,9 @@
  *     hubbard_workspace_size (or hubbard_batch_workspace_size) for the byte
  *     count and passes a buffer.  The only device memory the library
  *     allocates itself is small read-only tables (model constants and pass
- *     plans, KiB per handle, layer count and device; batch tables per
- *     distinct batch), uploaded on first use and kept until
+ *     plans, KiB per handle, layer count and device; sector tables, a few
+ *     MiB at most per handle and device; batch tables per distinct
+ *     batch), uploaded on first use and kept until
  *     hubbard_destroy (batch tables: until the process ends).
  *   - Every call returns a hubbard_status; on failure hubbard_last_error()
  *     returns a message (thread-local, valid until the next call on the same
@@ -202,6 +203,11 @@ hubbard_status hubbard_init_neel(hubbard_t h, void *psi_dev, void *stream);
  * n_layers * params_per_layer doubles in device memory.  n_layers >= 0. */
 hubbard_status ansatz_apply(hubbard_t h, const double *theta_dev, int32_t n_layers,
                             void *psi_dev, void *stream);
+
+/* psi_dev <- U_P(theta_P) ... U_1(theta_1)|b0>: hubbard_init_neel and
+ * ansatz_apply in one call (2^n complex128 written, not read). */
+hubbard_status hubbard_prepare_state(hubbard_t h, const double *theta_dev, int32_t n_layers,
+                                     void *psi_dev, void *stream);
 
 /* Matrix-free H|psi> (Eq. (4)'s operator): out_dev <- H psi_dev.  Both are
  * 2^n complex128; out_dev must not overlap psi_dev (HUBBARD_ERR_ARG). */

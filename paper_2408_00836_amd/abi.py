@@ -38,7 +38,7 @@ HUBBARD_SECTOR_LANCZOS = 3
 EXPORTED = [
     "hubbard_create", "hubbard_create_graph", "hubbard_destroy", "hubbard_query", "hubbard_bonds",
     "hubbard_last_error", "hubbard_workspace_size", "hubbard_init_neel",
-    "ansatz_apply", "hamiltonian_apply", "energy", "energy_grad",
+    "ansatz_apply", "hubbard_prepare_state", "hamiltonian_apply", "energy", "energy_grad",
     "hubbard_plan_dump", "hubbard_set_tiles", "hubbard_set_timing", "hubbard_phase_ms",
     "hubbard_kernel_ms",
     "hubbard_batch_workspace_size", "energy_grad_batch", "hubbard_get_tiles", "hubbard_tune",
@@ -123,6 +123,7 @@ def lib() -> ctypes.CDLL:
             "hubbard_workspace_size": ([vp, i32, i32, P(ctypes.c_size_t)], st),
             "hubbard_init_neel": ([vp, vp, vp], st),
             "ansatz_apply": ([vp, vp, i32, vp, vp], st),
+            "hubbard_prepare_state": ([vp, vp, i32, vp, vp], st),
             "hamiltonian_apply": ([vp, vp, vp, vp], st),
             "energy": ([vp, vp, i32, vp, vp, ctypes.c_size_t, vp], st),
             "energy_grad": ([vp, vp, i32, vp, vp, vp, ctypes.c_size_t, vp], st),
@@ -275,6 +276,11 @@ def hubbard_init_neel(h: int, psi_dev: int, stream: int = 0) -> None:
 
 def ansatz_apply(h: int, theta_dev: int, n_layers: int, psi_dev: int, stream: int = 0) -> None:
     _check(lib().ansatz_apply(h, theta_dev, int(n_layers), psi_dev, stream))
+
+
+def hubbard_prepare_state(h: int, theta_dev: int, n_layers: int, psi_dev: int,
+                          stream: int = 0) -> None:
+    _check(lib().hubbard_prepare_state(h, theta_dev, int(n_layers), psi_dev, stream))
 
 
 def hamiltonian_apply(h: int, psi_dev: int, out_dev: int, stream: int = 0) -> None:

@@ -52,6 +52,9 @@ hubbard_status lanczos_run(const ApplyH &apply, uint64_t n, const double2 *start
                            double2 *partial, hipStream_t s);
 size_t lanczos_partial_bytes();
 // sector.hip: evaluations from |b0> on its particle-number sector
+bool sector_state_ok(hubbard_t h, int layers);
+hubbard_status sector_state(hubbard_t h, int layers, const double *theta, double2 *psi,
+                            hipStream_t s);
 size_t sector_eval_bytes(hubbard_t h, int layers, bool grad);
 size_t sector_eval_ready(hubbard_t h, int layers);
 hubbard_status sector_eval(hubbard_t h, int layers, const double *theta, double *E, double *grad,
@@ -1576,6 +1579,29 @@ hubbard_status ansatz_apply(hubbard_t h, const double *theta_dev, int32_t n_laye
     st = run_forward(*pr, *ds, theta_dev, (double2 *)psi_dev, (hipStream_t)stream, h);
     mark(h, 1, (hipStream_t)stream);
     return st;
+}
+
+// The start state's circuit runs on its sector inside psi (sector.hip,
+// spread_at), which takes no scratch, and is faster at every size measured
+// (full vector's passes / this: 8 qubits 30 / 23 us, 16 qubits 104 / 31 us, 24
+// qubits 1.86 / 0.20 ms, 28 qubits 28.1 / 1.83 ms).  The passes remain for what
+// sector_route leaves to them and for 16 sites, whose rows do not fit in LDS.
+hubbard_status hubbard_prepare_state(hubbard_t h, const double *theta_dev, int32_t n_layers,
+                                     void *psi_dev, void *stream)
+{
+    if (!h || !psi_dev || n_layers < 0 || (n_layers > 0 && !theta_dev))
+        return fail(HUBBARD_ERR_ARG, "bad arguments to hubbard_prepare_state");
+    if (n_layers > 0 && h->m.ansatz == 0 && !h->timing) {
+        const std::string err = g_err;   // a refusal is no error of this call
+        if (sector_state_ok(h, n_layers)) {
+            h->ev_used = 0;
+            h->kmode.clear();
+            return sector_state(h, n_layers, theta_dev, (double2 *)psi_dev, (hipStream_t)stream);
+        }
+        g_err = err;
+    }
+    hubbard_status st = run_init(h, (double2 *)psi_dev, (hipStream_t)stream);
+    return st == HUBBARD_OK ? ansatz_apply(h, theta_dev, n_layers, psi_dev, stream) : st;
 }
 
 hubbard_status hamiltonian_apply(hubbard_t h, const void *psi_dev, void *out_dev, void *stream)

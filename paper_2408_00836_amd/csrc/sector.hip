@@ -108,6 +108,8 @@ struct RowsArgs {
     int l_pre, l_diag, l_post;   // layer of the hops before the diagonal, of the
                                  // diagonal and of the hops after it (-1: none)
     int64_t rs, cs;              // element (row, col) at row rs + col cs
+    const uint32_t *dnpat;       // in a full vector's place (SpreadAt): spin-down patterns,
+    int ns, skew;                //   sites and the skew's mask
     double2 *v[2];
     double2 *t[2];               // long rows, SF_TURN: the transposed result
     double *partial;
@@ -484,6 +486,17 @@ __device__ __forceinline__ int group_of(int i, int n)
     return (i >> 3) < chunk && g < n ? g : -1;
 }
 
+// A sector vector kept in the memory of the full vector that it becomes: the
+// amplitudes of a spin-down pattern, packed, in the pattern's own row of the
+// full vector, so that every row can be expanded by itself.  The skew (128
+// bytes per rank, under half a row: the patterns with a given number of
+// electrons are at most half of all) keeps a column's elements off one memory
+// channel.
+__device__ __forceinline__ int64_t spread_at(const gu32 *dnpat, int rank, int ns, int skew)
+{
+    return ((int64_t)dnpat[rank] << ns) + ((rank * 8) & skew);
+}
+
 // ------------------------------------------------------------ short rows --
 // 2^lr rows of up to kShortRow elements per workgroup, in LDS: element (slot,
 // row) at slot 2^lr + row, lanes with the row in their low bits.  Each phase
@@ -507,7 +520,9 @@ __device__ __forceinline__ int group_of(int i, int n)
 //          with chi1, chi2 = lambda / m +- i m psi for any m: one near the
 //          square root of |lambda| / |psi| keeps the difference's rounding
 //          as small as the bracket's own.
-template <int MODE, bool GEN, typename AT>
+//   SPREAD: the vector lies inside the full vector that it is going to become
+//          (spread_at).
+template <int MODE, bool GEN, bool SPREAD, typename AT>
 __device__ __forceinline__ void rows_short(const AT &A, int bid, int vsel, char *smem)
 {
     constexpr bool REV = MODE == S_REV;
@@ -552,14 +567,29 @@ __device__ __forceinline__ void rows_short(const AT &A, int bid, int vsel, char 
             continue;
         const int r = (g << lr) + row;
         const bool live = r < A.n_rows;
-        gc128 *__restrict__ vr = v + (int64_t)r * A.rs;
+        // element (r, col); a spread vector's row is the one of the two that
+        // indexes spin-down patterns (cs 1: the rows do)
+        gc128 *__restrict__ vr;
+        if constexpr (SPREAD)
+            vr = v + (A.cs == 1 ? spread_at((const gu32 *)A.dnpat, min(r, A.n_rows - 1), A.ns,
+                                            A.skew)
+                                : (int64_t)r);
+        else
+            vr = v + (int64_t)r * A.rs;
+        auto elem = [&](int col) __attribute__((always_inline)) -> gc128 * {
+            if constexpr (SPREAD)
+                return vr + (A.cs == 1 ? (int64_t)col
+                                       : spread_at((const gu32 *)A.dnpat, col, A.ns, A.skew));
+            else
+                return vr + (int64_t)col * A.cs;
+        };
         if constexpr (!REV) {
             if (A.flags & SF_START) {
                 const bool here = (g << lr) <= A.b0_row && A.b0_row < ((g + 1) << lr);
                 if (!here) {
                     for (int i = tid; i < total; i += T)
                         if (live) {
-                            gc128 *p = vr + (int64_t)(i >> lr) * A.cs;
+                            gc128 *p = elem(i >> lr);
                             p->x = 0.0;
                             p->y = 0.0;
                         }
@@ -580,7 +610,7 @@ __device__ __forceinline__ void rows_short(const AT &A, int bid, int vsel, char 
                 if (start) {
                     x[u].x = r == A.b0_row && col == A.b0_col ? 1.0 : 0.0;
                 } else if (live && i < total) {
-                    const gc128 *p = vr + (int64_t)col * A.cs;
+                    const gc128 *p = elem(col);
                     x[u] = make_double2(p->x, p->y);
                 }
             }
@@ -729,7 +759,7 @@ __device__ __forceinline__ void rows_short(const AT &A, int bid, int vsel, char 
         if (!(A.flags & SF_NO_STORE) && live) {
             each([&](int, int col) __attribute__((always_inline)) {
                 const double2 x = vec[(colslot[col] << lr) + row];
-                gc128 *p = vr + (int64_t)col * A.cs;
+                gc128 *p = elem(col);
                 p->x = x.x;
                 p->y = x.y;
             });
@@ -745,7 +775,77 @@ template <int MODE, bool GEN>
 __global__ void __launch_bounds__(1024) k_sec_rows_short(RowsArgs A)
 {
     extern __shared__ __align__(16) char smem[];
-    rows_short<MODE, GEN>(A, (int)blockIdx.x, MODE == S_REV ? (int)blockIdx.y : 0, smem);
+    rows_short<MODE, GEN, false>(A, (int)blockIdx.x, MODE == S_REV ? (int)blockIdx.y : 0, smem);
+}
+
+// A forward pass on a vector spread over its full vector's memory.
+template <bool GEN>
+__global__ void __launch_bounds__(1024) k_sec_rows_spread(RowsArgs A)
+{
+    extern __shared__ __align__(16) char smem[];
+    rows_short<S_FWD, GEN, true>(A, (int)blockIdx.x, 0, smem);
+}
+
+// The full vector from a spread one, in place: a workgroup reads a spin-down
+// pattern's amplitudes into LDS and writes the pattern's whole row, a spin-up
+// pattern's amplitude found by its rank: patterns are in numeric order, so the
+// rank is the number of sector patterns with smaller high bits plus the rank of
+// the low six bits among those with the same number of electrons.
+// Bound by the full vector's write (24 qubits, 268 MB: 40 us).
+__global__ void __launch_bounds__(512)
+k_sec_expand(double2 *vec, int ns, int skew, int n_up, int e_up, int e_dn)
+{
+    extern __shared__ __align__(16) char smem[];
+    double2 *row = (double2 *)smem;
+    gc128 *v = (gc128 *)vec;
+    const int tid = threadIdx.x, T = blockDim.x;
+    const int lb = min(ns, 6), nhi = 1 << (ns - lb), lmask = (1 << lb) - 1;
+    int *first[2];   // of each spin's patterns, by their high bits
+    first[0] = (int *)(smem + (size_t)n_up * 16);
+    first[1] = first[0] + nhi;
+    int *lo_rank = first[1] + nhi, *binom = lo_rank + 64;
+    if (tid < 64) {
+        int k = 0;
+        for (int j = 0; j < tid; ++j)
+            k += __popc(j) == __popc(tid) ? 1 : 0;
+        lo_rank[tid] = k;
+    }
+    if (tid < 8) {
+        int c = tid <= lb ? 1 : 0;
+        for (int q = 0; q < tid && q < lb; ++q)
+            c = c * (lb - q) / (q + 1);
+        binom[tid] = c;
+    }
+    __syncthreads();
+    for (int i = tid; i < 2 * nhi; i += T) {
+        const int e0 = i < nhi ? e_up : e_dn;
+        int k = 0;
+        for (int j = 0; j < (i & (nhi - 1)); ++j) {
+            const int e = e0 - __popc(j);   // electrons left for the low bits
+            k += e >= 0 && e <= lb ? binom[e] : 0;
+        }
+        first[0][i] = k;
+    }
+    const int n_rows = 1 << ns;
+    for (int d = blockIdx.x; d < n_rows; d += gridDim.x) {
+        gc128 *out = v + ((int64_t)d << ns);
+        const bool in = __popc(d) == e_dn;
+        __syncthreads();   // the tables; the last row's reads
+        if (in) {
+            const int rank = first[1][d >> lb] + lo_rank[d & lmask];
+            const gc128 *x = out + ((rank * 8) & skew);
+            for (int i = tid; i < n_up; i += T)
+                row[i] = make_double2(x[i].x, x[i].y);
+            __syncthreads();
+        }
+        for (int i = tid; i < n_rows; i += T) {
+            double2 a = make_double2(0.0, 0.0);
+            if (in && __popc(i) == e_up)
+                a = row[first[0][i >> lb] + lo_rank[i & lmask]];
+            out[i].x = a.x;
+            out[i].y = a.y;
+        }
+    }
 }
 
 // A batch's pass: every workgroup runs one workgroup's part of one instance's
@@ -761,7 +861,7 @@ k_sec_rows_batch(const RowsArgs *__restrict__ args, const SecWork *__restrict__ 
 {
     extern __shared__ __align__(16) char smem[];
     const SecWork w = work[blockIdx.x];
-    rows_short<MODE, GEN>(((kRowsArgs *)args)[w.args], w.bid, w.vsel, smem);
+    rows_short<MODE, GEN, false>(((kRowsArgs *)args)[w.args], w.bid, w.vsel, smem);
 }
 
 // ------------------------------------------------------------- long rows --
@@ -1365,7 +1465,7 @@ struct SpinTables {
 
 // Sector tables of one model on one device.
 struct Tables {
-    int n[2] = {0, 0};
+    int n[2] = {0, 0}, ne[2] = {0, 0};   // patterns and electrons of each spin
     size_t b0_pos = 0;            // position of |b0> in layout A
     int b0_rank[2] = {0, 0};      // ranks of |b0>'s patterns
     bool general = false;         // eps or V terms in the diagonal
@@ -1438,6 +1538,8 @@ hubbard_status build_tables(const Model &m, Tables &T)
     if (!err.empty())
         return fail(HUBBARD_ERR_ARG, err);
     const uint32_t smask = (1u << m.ns) - 1u;
+    T.ne[0] = __builtin_popcount((uint32_t)m.neel & smask);
+    T.ne[1] = __builtin_popcount((uint32_t)(m.neel >> m.ns) & smask);
     T.b0_rank[0] = P.spin[0].rank_of[(uint32_t)m.neel & smask];
     T.b0_rank[1] = P.spin[1].rank_of[(uint32_t)(m.neel >> m.ns) & smask];
     T.general = m.general;
@@ -1775,6 +1877,8 @@ void set_attrs()
         const void *fns[] = {
             (const void *)k_sec_rows_short<S_FWD, false>, (const void *)k_sec_rows_short<S_FWD, true>,
             (const void *)k_sec_rows_short<S_REV, false>, (const void *)k_sec_rows_short<S_REV, true>,
+            (const void *)k_sec_rows_spread<false>,       (const void *)k_sec_rows_spread<true>,
+            (const void *)k_sec_expand,
             (const void *)k_sec_rows_long<S_FWD, false>,  (const void *)k_sec_rows_long<S_FWD, true>,
             (const void *)k_sec_rows_long<S_REV, false>,  (const void *)k_sec_rows_long<S_REV, true>,
             (const void *)k_sec_ham_short<false>,         (const void *)k_sec_ham_short<true>,
@@ -1872,6 +1976,32 @@ void evaluate(const Tables &T, const Program &P, const double *theta, double *E,
     }
     hipLaunchKernelGGL(k_sec_reduce, dim3(rev ? P.n_out : 1), dim3(256), 0, s, partial, kGrid,
                        P.d_nblk, P.d_ptr, P.d_rows, P.d_scale, E, grad);
+}
+
+// psi, a full vector (2^(2 ns) amplitudes, not read) <- the circuit's state.
+void state(const Tables &T, const Program &P, int ns, const double *theta, double2 *psi,
+           hipStream_t s)
+{
+    set_attrs();
+    const int skew = (1 << (ns - 1)) - 1;
+    for (size_t i = 0; i < P.fwd.size(); ++i) {
+        const RowPass &p = P.fwd[i];
+        const SpinTables &S = T.sp[p.col];
+        RowsArgs A = rows_args(T, p, false, theta, psi, nullptr, nullptr, 0, kGrid,
+                               i == 0 ? SF_START : 0, nullptr, nullptr);
+        A.dnpat = T.sp[1].pat;
+        A.ns = ns;
+        A.skew = skew;
+        A.cs = p.col == 0 ? 1 : 0;
+        const uint32_t lds = rows_lds(T, p.col, 0);
+        if (T.general)
+            hipLaunchKernelGGL((k_sec_rows_spread<true>), dim3(A.grid), dim3(S.threads), lds, s, A);
+        else
+            hipLaunchKernelGGL((k_sec_rows_spread<false>), dim3(A.grid), dim3(S.threads), lds, s, A);
+    }
+    const uint32_t lds = (uint32_t)T.n[0] * 16u + ((ns > 6 ? 2u << (ns - 6) : 2u) + 72u) * 4u;
+    hipLaunchKernelGGL(k_sec_expand, dim3(std::min(1 << ns, 1024)), dim3(512), lds, s, psi, ns,
+                       skew, T.n[0], T.ne[0], T.ne[1]);
 }
 
 // Angles of every op and diagonal phase tables were once kept in the
@@ -2203,6 +2333,27 @@ hubbard_status sector_eval(hubbard_t h, int layers, const double *theta, double 
         return st;
     sec::evaluate(*T, *P, theta, E, grad, (char *)ws, s);
     return sec::check("sector evaluation");
+}
+
+// Whether a start-state circuit's full vector can be made on its sector: a
+// plan of short rows and at least one pass.
+bool sector_state_ok(hubbard_t h, int layers)
+{
+    sec::Tables *T = nullptr;
+    sec::Program *P = nullptr;
+    return sec::get(h, layers, &T, &P) == HUBBARD_OK && !T->is_long && !P->fwd.empty();
+}
+
+hubbard_status sector_state(hubbard_t h, int layers, const double *theta, double2 *psi,
+                            hipStream_t s)
+{
+    sec::Tables *T = nullptr;
+    sec::Program *P = nullptr;
+    hubbard_status st = sec::get(h, layers, &T, &P);
+    if (st != HUBBARD_OK)
+        return st;
+    sec::state(*T, *P, handle_model(h)->ns, theta, psi, s);
+    return sec::check("state preparation");
 }
 
 // Drop the sector tables and programs of a destroyed handle.

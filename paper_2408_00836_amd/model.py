@@ -174,7 +174,9 @@ class Hubbard:
     def ansatz(self, theta: torch.Tensor, psi: torch.Tensor | None = None) -> torch.Tensor:
         L = self._layers(theta)
         if psi is None:
-            psi = self.new_state(theta.device)
+            psi = torch.empty(self.dim, dtype=torch.complex128, device=theta.device)
+            abi.hubbard_prepare_state(self.handle, theta.data_ptr(), L, psi.data_ptr(), _stream())
+            return psi
         _require_gpu(psi, "psi", torch.complex128)
         abi.ansatz_apply(self.handle, theta.data_ptr(), L, psi.data_ptr(), _stream())
         return psi

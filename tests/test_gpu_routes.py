@@ -98,3 +98,44 @@ def test_batch_is_its_members_bit_for_bit(gpu):
         o = int(b.offsets[i])
         Ei, gi = m.energy_grad(th[o:o + w.n_params].contiguous())
         assert torch.equal(E[i:i + 1], Ei) and torch.equal(g[o:o + w.n_params], gi), i
+
+
+def prepared(m, th, psi):
+    """The start state's circuit on a vector that holds NaN before, and by
+    init and ansatz_apply."""
+    psi.fill_(float("nan"))
+    abi.hubbard_prepare_state(m.handle, th.data_ptr(), m._layers(th), psi.data_ptr(),
+                              torch.cuda.current_stream().cuda_stream)
+    return psi, m.ansatz(th, m.new_state())
+
+
+STATES = dict(CASES, **{"1x13 general": inst(1, 13, 3, 3, 908, U=3.0, eps_width=0.3, V=0.2),
+                        "2x7": inst(2, 7, 2, 5, 909, U=4.0)})
+
+
+@pytest.mark.parametrize("key", list(STATES))
+def test_prepared_state_is_init_and_ansatz(gpu, key):
+    # both routes round every amplitude of a unit vector some hundred times:
+    # far below 1e-13 each; outside the sector both are exactly zero
+    w = STATES[key]
+    m = Hubbard(w.nx, w.ny, **w.kwargs())
+    th = torch.tensor(w.theta, device=gpu)
+    got, ref = prepared(m, th, m.new_state())
+    assert (got - ref).abs().max().item() <= 1e-13
+    i = torch.arange(m.dim, device=gpu)
+    ns, neel = w.nx * w.ny, int(m.new_state().abs().argmax())
+    lo, hi = i & ((1 << ns) - 1), i >> ns
+    bits = [sum((x >> k) & 1 for k in range(ns)) for x in (lo, hi)]
+    want = [bin(neel & ((1 << ns) - 1)).count("1"), bin(neel >> ns).count("1")]
+    out = (bits[0] != want[0]) | (bits[1] != want[1])
+    assert not got[out].abs().any().item()
+
+
+@pytest.mark.parametrize("key", list(GRAPHS))
+def test_prepared_graph_state(gpu, key):
+    n, bonds, spins = GRAPHS[key]
+    m = Hubbard.graph(n, np.asarray(bonds, dtype=np.int32).reshape(-1, 2), U=3.0, site_spin=spins)
+    th = torch.tensor(np.random.default_rng(42).uniform(-0.4, 0.4, 2 * m.params_per_layer),
+                      device=gpu)
+    got, ref = prepared(m, th, m.new_state())
+    assert (got - ref).abs().max().item() <= 1e-13
