@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhubvqe.so")
 SOURCES = ["model.cpp", "plan.cpp", "tridiag.cpp", "lbfgs.cpp", "sector_plan.cpp", "engine.hip",
-           "kernels.hip", "sector.hip"]
+           "kernels.hip", "ham.hip", "sector.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 

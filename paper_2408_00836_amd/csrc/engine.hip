@@ -52,6 +52,11 @@ hubbard_status lanczos_run(const ApplyH &apply, uint64_t n, const double2 *start
                            double2 *partial, hipStream_t s);
 size_t lanczos_partial_bytes();
 // sector.hip: evaluations from |b0> on its particle-number sector
+// ham.hip: H on full vectors by gathering
+bool ham_gather_ok(const Model &m);
+std::vector<double> ham_site_table(const Model &m);
+void ham_gather(const Model &m, const double *site, const double2 *psi, double2 *out,
+                hipStream_t s);
 bool sector_state_ok(hubbard_t h, int layers);
 hubbard_status sector_state(hubbard_t h, int layers, const double *theta, double2 *psi,
                             hipStream_t s);
@@ -240,6 +245,7 @@ struct Program {
 
 struct DeviceState {
     DevModel *d_model = nullptr;
+    double *d_site = nullptr;   // ham_site_table (general models, once H is applied)
     std::map<std::pair<int, int>, std::unique_ptr<Program>> progs;
 };
 
@@ -880,6 +886,46 @@ hubbard_status run_ham(const Program &pr, const DeviceState &ds, const double2 *
     return check_launch("hamiltonian pass");
 }
 
+// Whether hamiltonian_apply and hubbard_lanczos gather (ham.hip); uploads the
+// tables of a general model.  The passes remain for H with energies (the
+// gradient's), for the timing mode, which times them, and for models that
+// ham_gather_ok leaves to them.
+bool gather_route(hubbard_model *h, DeviceState &ds)
+{
+    if (h->timing || !ham_gather_ok(h->m))
+        return false;
+    if (!h->m.general)
+        return true;
+    std::lock_guard<std::mutex> lk(h->mu);
+    if (ds.d_site)
+        return true;
+    try {
+        const std::vector<double> e = ham_site_table(h->m);
+        double *p = nullptr;
+        if (hipMalloc((void **)&p, e.size() * sizeof(double)) == hipSuccess) {
+            if (hipMemcpy(p, e.data(), e.size() * sizeof(double), hipMemcpyHostToDevice) ==
+                hipSuccess)
+                ds.d_site = p;
+            else
+                (void)hipFree(p);
+        }
+    } catch (const std::exception &) {
+    }
+    if (!ds.d_site)
+        (void)hipGetLastError();
+    return ds.d_site != nullptr;
+}
+
+// out <- H in
+hubbard_status apply_ham(hubbard_model *h, const Program &pr, DeviceState &ds, const double2 *in,
+                         double2 *out, hipStream_t s)
+{
+    if (!gather_route(h, ds))
+        return run_ham(pr, ds, in, out, nullptr, s, h);
+    ham_gather(h->m, ds.d_site, in, out, s);
+    return check_launch("hamiltonian");
+}
+
 hubbard_status run_init(const hubbard_model *h, double2 *psi, hipStream_t s,
                         VecLayout vl = VecLayout())
 {
@@ -1491,6 +1537,7 @@ void hubbard_destroy(hubbard_t h)
         (void)hipSetDevice(kv.first);
         kv.second.progs.clear();
         (void)hipFree(kv.second.d_model);
+        (void)hipFree(kv.second.d_site);
     }
     delete h;
 }
@@ -1620,8 +1667,8 @@ hubbard_status hamiltonian_apply(hubbard_t h, const void *psi_dev, void *out_dev
     h->ev_used = 0;
     h->kmode.clear();
     mark(h, 1, (hipStream_t)stream);
-    st = run_ham(*pr, *ds, (const double2 *)psi_dev, (double2 *)out_dev, nullptr,
-                 (hipStream_t)stream, h);
+    st = apply_ham(h, *pr, *ds, (const double2 *)psi_dev, (double2 *)out_dev,
+                   (hipStream_t)stream);
     mark(h, 2, (hipStream_t)stream);
     return st;
 }
@@ -2494,7 +2541,7 @@ hubbard_status hubbard_lanczos(hubbard_t h, const void *start_dev, int32_t max_i
     hipStream_t s = (hipStream_t)stream;
     double2 *buf[3] = {(double2 *)ws_dev, (double2 *)(ws + vb), (double2 *)(ws + 2 * vb)};
     const hv::ApplyH apply = [&](const double2 *in, double2 *out) {
-        return run_ham(*pr, *ds, in, out, nullptr, s);
+        return apply_ham(h, *pr, *ds, in, out, s);
     };
     return hv::lanczos_run(apply, (uint64_t)1 << h->m.nq, (const double2 *)start_dev, max_iter,
                            tol, E0, iters, residual, (double2 *)gs_dev, buf,
