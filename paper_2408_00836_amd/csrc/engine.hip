@@ -968,11 +968,11 @@ VecLayout grad_layout(const hubbard_model *h)
 // the full vector.  The HVA circuit keeps (N_up, N_dn), so the results are
 // the same and all but C(Ns, N_up) C(Ns, N_dn) of the 2^n amplitudes stay
 // zero.  The sector form won at every size measured (full vector / sector
-// form, one evaluation): 8 qubits 75 / 41 us, 16 qubits 486 / 219 us, 24
-// qubits with the general diagonal 16.2 / 1.03 ms, 28 qubits 92.9 / 4.2 ms.  The full vector remains for the NP
-// ansatz, for models whose sector plan is refused, for a workspace too small
-// for the sector's vectors, and under hubbard_set_timing, which times the
-// full vector's pass kernels.
+// form, one evaluation): 8 qubits 75 / 17 us, 16 qubits 486 / 148 us, 24
+// qubits with the general diagonal 16.2 / 0.98 ms, 28 qubits 92.9 / 3.2 ms.
+// The full vector remains for the NP ansatz, for models whose sector plan is
+// refused, for a workspace too small for the sector's vectors, and under
+// hubbard_set_timing, which times the full vector's pass kernels.
 bool sector_route(hubbard_model *h, int layers, bool grad, size_t ws_bytes)
 {
     if (h->m.ansatz != 0 || h->timing)
@@ -1360,7 +1360,7 @@ hubbard_status build_batch(const hubbard_t *hs, int n, const double *theta, cons
             bp.uids.push_back(hs[i]->uid);
     // On the instances' sectors, by the rule of energy_grad: 256 uneven
     // instances of 8 to 20 qubits take 12.9 ms on the full vectors (each
-    // launch listed below) and 1.68 ms on the sectors.  Only the workspace
+    // launch listed below) and 1.48 ms on the sectors.  Only the workspace
     // size comes from the full vectors' layout then.
     bool timing = false;
     for (int i = 0; i < n; ++i)

@@ -64,6 +64,8 @@ size_t lanczos_partial_bytes();
 namespace sec {
 
 constexpr int kMaxRed = 16;               // reduction slots of one row pass
+constexpr int kWholeN = 35, kWholeEl = 8; // whole evaluations: patterns of a spin, amplitudes
+constexpr int kWholeLayers = 1024;        // of a thread, layers
 constexpr int kGrid = 1024;               // at most this many workgroups write partials
 
 enum { S_FWD = 0, S_REV = 1 };
@@ -318,16 +320,22 @@ struct RowPassCtx {
         double2 c[kPositions];
         double t[kPositions];
         int slot[kPositions], last[kPositions];
+        bool on[kPositions];   // false: the position has no bond (reverse)
     };
     __device__ __forceinline__ PhaseArgs phase_args(int run, int ph) const
     {
+        return phase_args(run, ph, run);
+    }
+    __device__ __forceinline__ PhaseArgs phase_args(int run, int ph, int buf) const
+    {
         PhaseArgs a;
-        const double2 *an = ang + (run * A.n_phases + ph) * kPositions;
+        const double2 *an = ang + (buf * A.n_phases + ph) * kPositions;
         const kGate *g = (const kGate *)A.gates + ph * kPositions;
         const int base = (run ? post_slot : 0) - 1;
 #pragma unroll
         for (int q = 0; q < kPositions; ++q) {
             a.c[q] = an[q];
+            a.on[q] = !REV || g[q].t != 0.0;
             if constexpr (REV) {
                 a.t[q] = -2.0 * g[q].t;
                 a.slot[q] = base + g[q].slot;
@@ -369,12 +377,16 @@ struct RowPassCtx {
     {
         both(a,
              [&](double2 c0, double2 c1, double &p0, double &p1) __attribute__((always_inline)) {
-                 hop2<REV, 0>(x, c0, f, p0);
-                 hop2<REV, 1>(x, c1, f, p1);
+                 if (a.on[0])
+                     hop2<REV, 0>(x, c0, f, p0);
+                 if (a.on[1])
+                     hop2<REV, 1>(x, c1, f, p1);
              },
              [&](double2 c0, double2 c1, double &p0, double &p1) __attribute__((always_inline)) {
-                 hop2<REV, 2>(x, c0, f, p0);
-                 hop2<REV, 3>(x, c1, f, p1);
+                 if (a.on[2])
+                     hop2<REV, 2>(x, c0, f, p0);
+                 if (a.on[3])
+                     hop2<REV, 3>(x, c1, f, p1);
              });
     }
     // on two orbits of four
@@ -383,12 +395,16 @@ struct RowPassCtx {
     {
         both(a,
              [&](double2 c0, double2 c1, double &p0, double &p1) __attribute__((always_inline)) {
-                 hop13<REV, 0, 0>(x, c0, f1, f3, p0);
-                 hop13<REV, 1, 0>(x, c1, f1, f3, p1);
+                 if (a.on[0])
+                     hop13<REV, 0, 0>(x, c0, f1, f3, p0);
+                 if (a.on[1])
+                     hop13<REV, 1, 0>(x, c1, f1, f3, p1);
              },
              [&](double2 c0, double2 c1, double &p0, double &p1) __attribute__((always_inline)) {
-                 hop13<REV, 2, 0>(x, c0, f1, f3, p0);
-                 hop13<REV, 3, 0>(x, c1, f1, f3, p1);
+                 if (a.on[2])
+                     hop13<REV, 2, 0>(x, c0, f1, f3, p0);
+                 if (a.on[3])
+                     hop13<REV, 3, 0>(x, c1, f1, f3, p1);
              });
     }
     // on all of a long row's orbits (w2, w13: the wave has any of the kind)
@@ -510,7 +526,9 @@ __device__ __forceinline__ int64_t spread_at(const gu32 *dnpat, int rank, int ns
 // to 0.283 ms.  Half the threads for the orbits of six and half for those of
 // four, a phase's records and scalars fetched a phase ahead, and the diagonal's
 // tables four elements at a time: 1.02 and 0.189 ms; a 16-qubit chain 0.219 to
-// 0.149 ms, a 28-qubit ladder 4.18 to 3.36 ms.
+// 0.149 ms, a 28-qubit ladder 4.18 to 3.36 ms.  A reverse phase's positions
+// without a bond skipped: 0.98 and 0.188, 0.148 and 3.23 ms (forward, where
+// nothing else reads the gates, the skip cost more than it gave).
 //   S_FWD: v[0] <- ops applied.  SF_START: the input is |b0>, not read; the
 //          rows without it are zero.
 //   S_REV: vsel picks chi2 = v[0] or chi1 = v[1]; the ops un-applied in
@@ -1249,6 +1267,350 @@ k_sec_ham_batch(const HamArgs *__restrict__ args, const SecWork *__restrict__ wo
     ham_short<GEN>(((kHamArgs *)args)[w.args], w.bid, smem);
 }
 
+// ------------------------------------------------------- whole evaluations --
+// Sectors of up to kWholeN x kWholeN amplitudes: the matrix stays in one
+// workgroup's LDS for a whole evaluation.  Two workgroups run the circuit and
+// H, the same work in both, and then the reverse sweep of one of the vectors
+// chi1, chi2 each, so that nothing passes between them: one launch, then the
+// reduction.  Up passes rotate along the rows, down passes along the columns
+// of the matrix (an odd pitch keeps either side's lanes on different banks);
+// index n of a row or column is the zero element.
+// Bound by latency and by one CU's VALU (14 qubits, three phases a half layer:
+// about 1.5 us a phase, of both sweeps).
+struct WholeArgs {
+    const SecGate *gates;
+    const uint4 *recs;           // per spin and phase: n2 + 1 orbits of six, n13 + 1 pairs of
+                                 // orbits of four (the last of each: zero elements)
+    const uint16_t *hcode;       // per spin, rank and bond: partner | sign << 15
+    const uint32_t *pat[2];      // per rank
+    const double *base[2];
+    const double *wrow;          // of the spin-down patterns
+    const double *tb, *theta;
+    double U, mix;
+    int n, pitch, n_phases, per, layers, nb, n_red;
+    int n2[2], n13[2];
+    uint32_t magic;              // i / n = i magic >> 20
+    int b0_row, b0_col;
+    double *partial;
+    int pstride, grad;
+};
+
+// LDS of a whole evaluation: the matrix, every layer's angles and (U-only)
+// diagonal phases, the tables, and a pass's sums.
+struct WholeLds {
+    uint32_t ang, dtab, nib, base, pat, recs, hcode, acc, total;
+};
+__host__ __device__ inline int whole_recs(const int (&n2)[2], const int (&n13)[2], int n_phases,
+                                          int spin)   // records before spin's
+{
+    return spin == 0 ? 0 : n_phases * (n2[0] + 1 + 2 * (n13[0] + 1));
+}
+__host__ __device__ inline WholeLds whole_lds(int n, int pitch, int n_phases, int layers, int nb,
+                                              int n_red, const int (&n2)[2], const int (&n13)[2], int threads,
+                                              bool gen)
+{
+    WholeLds L;
+    uint32_t at = (uint32_t)((n + 1) * pitch) * 16u;
+    L.ang = at;
+    at += (uint32_t)(layers * n_phases * kPositions) * 16u;
+    L.dtab = at;
+    at += (gen ? 1u << kCisBits : (uint32_t)(layers * kDiagTab)) * 16u;
+    L.recs = at;
+    at += (uint32_t)(whole_recs(n2, n13, n_phases, 1) +
+                     n_phases * (n2[1] + 1 + 2 * (n13[1] + 1))) * 16u;
+    L.nib = at;
+    at += gen ? (uint32_t)n * 64u * 8u : 0u;
+    L.base = at;
+    at += gen ? (uint32_t)n * 16u : 0u;
+    L.acc = at;   // (the energy's sums per wave: at most 16)
+    at += (uint32_t)(n_red * (threads / 4) + 16) * 8u;
+    L.pat = at;
+    at += (uint32_t)n * 8u;
+    L.hcode = at;
+    at += ((uint32_t)(2 * n * nb) * 2u + 15u) & ~15u;
+    L.total = at;
+    return L;
+}
+
+// A pass of a whole evaluation, as RowPassCtx sees it.
+struct WholePass {
+    const SecGate *gates;
+    const double *theta;
+    double U;
+    double *partial;
+    int l_pre, l_diag, l_post, per, n_phases, n_red, pstride;
+    int row0[2];
+};
+
+template <bool GEN, typename AT>
+__device__ __forceinline__ void whole(const AT &A, int vsel, char *smem)
+{
+    const int tid = threadIdx.x, T = blockDim.x, n = A.n, P = A.pitch;
+    const int N2[2] = {A.n2[0], A.n2[1]}, N13[2] = {A.n13[0], A.n13[1]};
+    const WholeLds L = whole_lds(n, P, A.n_phases, A.layers, A.nb, A.n_red, N2, N13, T, GEN);
+    double2 *vec = (double2 *)smem, *ang = (double2 *)(smem + L.ang);
+    double2 *dtab = (double2 *)(smem + L.dtab);
+    double *nib = (double *)(smem + L.nib), *base = (double *)(smem + L.base);
+    double *acc = (double *)(smem + L.acc);
+    uint32_t *pat = (uint32_t *)(smem + L.pat);
+    uint4 *recs = (uint4 *)(smem + L.recs);
+    uint16_t *hcode = (uint16_t *)(smem + L.hcode);
+    const gf64 *theta = (const gf64 *)A.theta;
+    const int n_gates = A.n_phases * kPositions, ne = n * n;
+    auto div_n = [&](int i) __attribute__((always_inline)) {
+        return (int)(((uint32_t)i * A.magic) >> 20);
+    };
+    // tables, and |b0>
+    const int n_recs = whole_recs(N2, N13, A.n_phases, 1) +
+                       A.n_phases * (N2[1] + 1 + 2 * (N13[1] + 1));
+    for (int i = tid; i < n_recs; i += T) {
+        const gu128 *p = (const gu128 *)A.recs + i;
+        recs[i] = make_uint4(p->x, p->y, p->z, p->w);
+    }
+    for (int i = tid; i < 2 * n * A.nb; i += T)
+        hcode[i] = ((const gu16 *)A.hcode)[i];
+    for (int i = tid; i < n; i += T)
+        for (int s = 0; s < 2; ++s) {
+            pat[s * n + i] = ((const gu32 *)A.pat[s])[i];
+            if constexpr (GEN)
+                base[s * n + i] = ((const gf64 *)A.base[s])[i];
+        }
+    if constexpr (GEN) {
+        for (int i = tid; i < n * 64; i += T)
+            nib[i] = nibble_sum((const gf64 *)A.wrow + (i >> 6) * 16, i & 63);
+        build_cis(dtab, tid, T);
+    }
+    // angles and phases of all layers (the reverse sweep takes their conjugates)
+    for (int i = tid; i < A.layers * n_gates; i += T) {
+        const int l = i / n_gates;
+        const __attribute__((address_space(1))) SecGate &g =
+            ((const __attribute__((address_space(1))) SecGate *)A.gates)[i - l * n_gates];
+        double s, c;
+        sincos(theta[l * A.per + g.slot] * g.t, &s, &c);
+        ang[i] = make_double2(c, s);
+    }
+    if constexpr (!GEN)
+        for (int i = tid; i < A.layers * kDiagTab; i += T) {
+            const int l = i / kDiagTab;
+            double s, c;
+            sincos(theta[l * A.per] * (A.U * (double)(i - l * kDiagTab)), &s, &c);
+            dtab[i] = make_double2(c, -s);
+        }
+    for (int i = tid; i < (n + 1) * P; i += T)
+        vec[i] = make_double2(i == A.b0_row * P + A.b0_col ? 1.0 : 0.0, 0.0);
+    __syncthreads();
+
+    const int TH = T >> 1;
+    const bool duo_half = __builtin_amdgcn_readfirstlane(tid) < TH;
+    const int t0 = duo_half ? tid : tid - TH;
+
+    // pass i of the forward sweep, or its reverse
+    auto pass = [&](auto mode, int i, int row0) __attribute__((always_inline)) {
+        constexpr int MODE = decltype(mode)::value;
+        constexpr bool REV = MODE == S_REV;
+        const int col = i & 1;
+        WholePass V;
+        V.gates = A.gates;
+        V.theta = A.theta;
+        V.U = A.U;
+        V.partial = A.partial;
+        V.l_pre = i - 1;
+        V.l_diag = V.l_post = i < A.layers ? i : -1;
+        V.per = A.per;
+        V.n_phases = A.n_phases;
+        V.n_red = REV ? (V.l_pre >= 0 ? A.per - 1 : 0) + (V.l_diag >= 0 ? A.per : 0) : 0;
+        V.pstride = A.pstride;
+        V.row0[0] = row0;
+        V.row0[1] = row0 + V.n_red;
+        RowLds rl;
+        rl.ang = L.ang;
+        rl.dtab = L.dtab;
+        rl.acc = L.acc;
+        RowPassCtx<MODE, GEN, WholePass> C(V, smem, rl);
+        for (int q = tid; q < V.n_red * (T / 4); q += T)
+            acc[q] = 0.0;
+        __syncthreads();
+        const int rs = col == 0 ? P * 16 : 16;   // bytes between rows of the other spin
+        const int m2 = N2[col], m13 = N13[col], per_phase = m2 + 1 + 2 * (m13 + 1);
+        const uint4 *mine = recs + (col == 0 ? 0 : whole_recs(N2, N13, A.n_phases, 1));
+        const int items = (duo_half ? m2 : m13) * n;
+        auto at = [&](const uint4 &q, int j, uint32_t ofs)
+                      __attribute__((always_inline)) -> double2 & {
+            const uint32_t w = j < 2 ? q.x : (j < 4 ? q.y : q.z);
+            return *(double2 *)(smem + ((j & 1 ? w >> 16 : w & 0xFFFFu) << 4) + ofs);
+        };
+        auto phase = [&](int run, int ph) __attribute__((always_inline)) {
+            typename RowPassCtx<MODE, GEN, WholePass>::PhaseArgs pa =
+                C.phase_args(run, ph, run ? V.l_post : V.l_pre);
+            if constexpr (REV)
+#pragma unroll
+                for (int q = 0; q < kPositions; ++q)
+                    pa.c[q].y = -pa.c[q].y;
+            const uint4 *list = mine + ph * per_phase + (duo_half ? 0 : m2 + 1);
+            for (int k = t0 & ~63; k < items; k += TH) {   // whole waves
+                const int it = k + (tid & 63);
+                const bool act = it < items;
+                const int orb = act ? div_n(it) : (duo_half ? m2 : m13);
+                const uint32_t ofs = act ? (uint32_t)((it - orb * n) * rs) : 0u;
+                if (duo_half) {
+                    const uint4 q = list[orb];
+                    double2 x[6];
+#pragma unroll
+                    for (int j = 0; j < 6; ++j)
+                        x[j] = at(q, j, ofs);
+                    C.gates2(x, pa, q.w);
+                    if (act) {
+#pragma unroll
+                        for (int j = 0; j < 6; ++j)
+                            at(q, j, ofs) = x[j];
+                    }
+                } else {
+                    const uint4 q1 = list[orb], q3 = list[m13 + 1 + orb];
+                    double2 x[8];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        x[j] = at(q1, j, ofs);
+                        x[4 + j] = at(q3, j, ofs);
+                    }
+                    C.gates13(x, pa, q1.z, q3.z);
+                    if (act) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            at(q1, j, ofs) = x[j];
+                            at(q3, j, ofs) = x[4 + j];
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+        };
+        auto diag = [&]() __attribute__((always_inline)) {
+            const double th = theta[V.l_diag * A.per];
+            double racc = 0.0;
+            for (int e = tid; e < ne; e += T) {
+                const int rd = div_n(e), ru = e - rd * n;
+                double2 &a = vec[rd * P + ru];
+                if constexpr (GEN) {
+                    double err;
+                    const double d = diag_gen(base[n + rd], base[ru], nib + rd * 64, pat[ru], err);
+                    diag_el<REV, true>(a, d, err, a, th, dtab, racc);
+                } else {
+                    const int k = __popc(pat[n + rd] & pat[ru]);
+                    double2 f = dtab[V.l_diag * kDiagTab + k];
+                    if constexpr (REV)
+                        f.y = -f.y;
+                    diag_el<REV, false>(a, A.U * (double)k, 0.0, f, th, nullptr, racc);
+                }
+            }
+            if constexpr (REV)
+                C.flush(C.dslot, racc);
+            __syncthreads();
+        };
+        if constexpr (!REV) {
+            for (int ph = 0; V.l_pre >= 0 && ph < A.n_phases; ++ph)
+                phase(0, ph);
+            if (V.l_diag >= 0)
+                diag();
+            for (int ph = 0; V.l_post >= 0 && ph < A.n_phases; ++ph)
+                phase(1, ph);
+        } else {
+            for (int ph = A.n_phases - 1; V.l_post >= 0 && ph >= 0; --ph)
+                phase(1, ph);
+            if (V.l_diag >= 0)
+                diag();
+            for (int ph = A.n_phases - 1; V.l_pre >= 0 && ph >= 0; --ph)
+                phase(0, ph);
+            C.finish(0, vsel, vsel == 1);
+            __syncthreads();
+        }
+    };
+    const int n_pass = A.layers > 0 ? A.layers + 1 : 0;
+    for (int i = 0; i < n_pass; ++i)
+        pass(std::integral_constant<int, S_FWD>(), i, 0);
+
+    // H psi, kept in registers; the energy; chi1 or chi2 in psi's place
+    double2 phi[kWholeEl];
+    double e = 0.0;
+    const kf64 *tb = (const kf64 *)A.tb;
+#pragma unroll
+    for (int u = 0; u < kWholeEl; ++u) {
+        const int el = tid + u * T;
+        phi[u] = make_double2(0.0, 0.0);
+        if (el < ne) {
+            const int rd = div_n(el), ru = el - rd * n;
+            const double2 own = vec[rd * P + ru];
+            double d;
+            if constexpr (GEN)
+                d = diag_gen(base[n + rd], base[ru], nib + rd * 64, pat[ru]);
+            else
+                d = A.U * (double)__popc(pat[n + rd] & pat[ru]);
+            double2 f = make_double2(d * own.x, d * own.y);
+            const uint16_t *hu = hcode + ru * A.nb, *hd = hcode + (n + rd) * A.nb;
+            for (int b = 0; b < A.nb; ++b) {
+                const uint32_t cu = hu[b], cd = hd[b];
+                const double2 pu = vec[rd * P + (int)(cu & 0x7FFFu)];
+                const double2 pd = vec[(int)(cd & 0x7FFFu) * P + ru];
+                const double mu = xor_sign(tb[b], code_sign(cu, 0));
+                const double md = xor_sign(tb[b], code_sign(cd, 0));
+                f.x = fma(mu, pu.x, f.x);
+                f.y = fma(mu, pu.y, f.y);
+                f.x = fma(md, pd.x, f.x);
+                f.y = fma(md, pd.y, f.y);
+            }
+            e += re_dot(own, f);
+            phi[u] = f;
+        }
+    }
+    e = wave_sum(e);
+    if ((tid & 63) == 0)
+        acc[tid >> 6] = e;
+    __syncthreads();
+    if (vsel == 0 && tid == 0) {
+        double sum = 0.0;
+        for (int w = 0; w < T >> 6; ++w)
+            sum += acc[w];
+        A.partial[0] = sum;
+        A.partial[A.pstride] = 0.0;
+    }
+    if (!A.grad || n_pass == 0)
+        return;
+    const double im = 1.0 / A.mix, sg = vsel == 1 ? 1.0 : -1.0;   // im: exact
+#pragma unroll
+    for (int u = 0; u < kWholeEl; ++u) {
+        const int el = tid + u * T;
+        if (el < ne) {
+            const int rd = div_n(el);
+            double2 &a = vec[rd * P + (el - rd * n)];
+            const double2 own = make_double2(a.x * A.mix, a.y * A.mix);
+            a = make_double2(phi[u].x * im - sg * own.y, phi[u].y * im + sg * own.x);
+        }
+    }
+    int row0 = 2 + 2 * ((2 * A.per - 1) * A.layers);
+    for (int i = n_pass - 1; i >= 0; --i) {
+        const int red = (i > 0 ? A.per - 1 : 0) + (i < A.layers ? A.per : 0);
+        row0 -= 2 * red;
+        __syncthreads();
+        pass(std::integral_constant<int, S_REV>(), i, row0);
+    }
+}
+
+template <bool GEN>
+__global__ void __launch_bounds__(1024) k_sec_whole(WholeArgs A)
+{
+    extern __shared__ __align__(16) char smem[];
+    whole<GEN>(A, (int)blockIdx.x, smem);
+}
+
+typedef const __attribute__((address_space(4))) WholeArgs kWholeArgs;
+template <bool GEN>
+__global__ void __launch_bounds__(1024)
+k_sec_whole_batch(const WholeArgs *__restrict__ args, const SecWork *__restrict__ work)
+{
+    extern __shared__ __align__(16) char smem[];
+    const SecWork w = work[blockIdx.x];
+    whole<GEN>(((kWholeArgs *)args)[w.args], w.vsel, smem);
+}
+
 // Long rows: H is real, so the real and the imaginary parts of a row take
 // turns in LDS.  Thread t sums for the slots t + j kLongT: lanes of
 // neighbouring slots are in different bank classes, and so are their
@@ -1475,6 +1837,12 @@ struct Tables {
     SpinTables sp[2];
     SecGate *d_gates = nullptr;
     double *d_tb = nullptr;
+    // whole evaluations (threads 0: the sector has none)
+    struct {
+        int threads = 0, n2[2] = {0, 0}, n13[2] = {0, 0};
+        uint4 *recs = nullptr;
+        uint16_t *hcode = nullptr;
+    } whole;
     char *blob = nullptr;
     ~Tables() { (void)hipFree(blob); }
 };
@@ -1486,6 +1854,7 @@ struct Program {
     // pass's slots (forward order of passes)
     std::vector<int> red_row0;    // per forward pass: its chi2 rows, then its chi1 rows
     int n_rows = 0, max_red = 0;
+    bool whole = false;           // runs as a whole evaluation
     int32_t *d_ptr = nullptr, *d_rows = nullptr, *d_nblk = nullptr;
     double *d_scale = nullptr;
     char *blob = nullptr;
@@ -1530,6 +1899,74 @@ struct Blob {
         return e;
     }
 };
+
+// The tables of whole evaluations; false (threads 0) where a sector does not
+// fit.  Elements by rank, of spin-down orbits times the pitch; rank n, and the
+// orbits that fill a phase's lists up to the longest one, are zero elements.
+// A launch per pass over the chip / one workgroup per vector: 8 qubits 38 / 17
+// us, 14 qubits 156 / 97 us (ten layers), 256 instances of 8 to 20 qubits 1.63 /
+// 1.48 ms.  With 70 patterns (16 qubits) one CU is too slow: 148 / 182 us.
+bool plan_whole(const Model &m, const SectorPlan &P, Tables &T, std::vector<uint4> &recs,
+                std::vector<uint16_t> &code)
+{
+    const int n = P.spin[0].n, nph = (int)P.sites.size(), pitch = (n + 1) | 1;
+    if (n > kWholeN || P.spin[1].n != n || 2 * m.params_per_layer() - 1 > kMaxRed)
+        return false;
+    auto &W = T.whole;
+    auto rec = [&](int s, int ph, int list, int k) -> const Rec & {
+        const SpinPlan &S = P.spin[s];
+        return S.recs[(size_t)(3 * ph + list) * (size_t)((S.threads / 2) >> S.lr) + (size_t)k];
+    };
+    int items = 0;
+    for (int s = 0; s < 2; ++s) {
+        const int lanes = (P.spin[s].threads / 2) >> P.spin[s].lr;
+        for (int ph = 0; ph < nph; ++ph)
+            for (int list = 0; list < 3; ++list)
+                for (int k = 0; k < lanes; ++k)
+                    if (rec(s, ph, list, k).w[list == 0 ? 3 : 2] & 1u) {
+                        int &c = list == 0 ? W.n2[s] : W.n13[s];
+                        c = std::max(c, k + 1);
+                    }
+        items = std::max(items, std::max(W.n2[s], W.n13[s]) * n);
+    }
+    const int th = std::min(512, std::max(64, (items + 63) / 64 * 64));
+    const int threads = std::max(2 * th, std::min(1024, (n * n + 1023) / 1024 * 128));
+    const int n_red = 2 * m.params_per_layer() - 1;
+    if (n * n > kWholeEl * threads ||
+        whole_lds(n, pitch, nph, 0, m.nb, n_red, W.n2, W.n13, threads, m.general).total > 160u * 1024u)
+        return false;
+    for (int s = 0; s < 2; ++s) {
+        const SpinPlan &S = P.spin[s];
+        const int lanes = (S.threads / 2) >> S.lr, scale = s == 0 ? 1 : pitch;
+        std::vector<int> rank(S.nslots + 1, n);
+        for (int r = 0; r < n; ++r)
+            rank[S.colslot[r]] = r;
+        for (int ph = 0; ph < nph; ++ph)
+            for (int list = 0; list < 3; ++list) {
+                const int len = list == 0 ? W.n2[s] : W.n13[s];
+                for (int k = 0; k <= len; ++k) {
+                    Rec q = {{0, 0, 0, 0}};
+                    const bool have = k < len && k < lanes && (rec(s, ph, list, k).w[list == 0 ? 3 : 2] & 1u);
+                    if (have)
+                        q = rec(s, ph, list, k);
+                    for (int w = 0; w < (list == 0 ? 3 : 2); ++w) {
+                        const uint32_t lo = (uint32_t)((have ? rank[q.w[w] & 0xFFFFu] : n) * scale);
+                        const uint32_t hi = (uint32_t)((have ? rank[q.w[w] >> 16] : n) * scale);
+                        q.w[w] = lo | hi << 16;
+                    }
+                    recs.push_back(make_uint4(q.w[0], q.w[1], q.w[2], q.w[3]));
+                }
+            }
+        const int hb = ham_bonds(m.nb);
+        for (int r = 0; r < n; ++r)
+            for (int b = 0; b < m.nb; ++b) {
+                const uint16_t c = S.hcode[(size_t)r * hb + b];
+                code.push_back((uint16_t)(rank[c & 0x7FFF] | (c & 0x8000)));
+            }
+    }
+    W.threads = threads;
+    return true;
+}
 
 hubbard_status build_tables(const Model &m, Tables &T)
 {
@@ -1588,6 +2025,12 @@ hubbard_status build_tables(const Model &m, Tables &T)
         B.add(&D.patslot, S.patslot);
         B.add(&D.hcode, S.hcode);
     }
+    std::vector<uint4> wrecs;
+    std::vector<uint16_t> wcode;
+    if (plan_whole(m, P, T, wrecs, wcode)) {
+        B.add(&T.whole.recs, wrecs);
+        B.add(&T.whole.hcode, wcode);
+    }
     // one electron per site: C(Ns, N_up) = C(Ns, N_dn)
     if (T.n[0] != T.n[1])
         return fail(HUBBARD_ERR_STATE, "sector matrix is not square");
@@ -1608,6 +2051,20 @@ int rows_grid(const Tables &T, int col)
     const int ng = (T.n[1 - col] + (1 << T.sp[col].lr) - 1) >> T.sp[col].lr;
     return std::min((ng + 7) / 8 * 8, kGrid);
 }
+
+uint32_t whole_lds(const Tables &T, int layers)
+{
+    return whole_lds(T.n[0], (T.n[0] + 1) | 1, T.n_phases, layers, T.nb, 2 * T.per - 1, T.whole.n2,
+                     T.whole.n13, T.whole.threads, T.general)
+        .total;
+}
+
+// Whether evaluations of `layers` layers run whole: every layer's angles fit, too.
+bool runs_whole(const Tables &T, int layers)
+{
+    return T.whole.threads && layers <= kWholeLayers && whole_lds(T, layers) <= 160u * 1024u;
+}
+
 
 uint32_t rows_lds(const Tables &T, int col, int n_red)
 {
@@ -1648,7 +2105,10 @@ hubbard_status build_program(const Model &m, const Tables &T, int layers, Progra
     P.final_col = P.fwd.empty() ? 0 : P.fwd.back().col;
     // reduction rows, and the workgroups of the pass that writes each
     P.n_rows = 2;
-    std::vector<int32_t> nblk{rows_grid(T, P.final_col), rows_grid(T, 1 - P.final_col)};
+    P.whole = runs_whole(T, layers);
+    // (a whole evaluation: one workgroup)
+    auto red_grid = [&](int col) { return P.whole ? 1 : rows_grid(T, col); };
+    std::vector<int32_t> nblk{red_grid(P.final_col), red_grid(1 - P.final_col)};
     std::vector<std::vector<int>> rows_of(1 + layers * per);
     rows_of[0] = {0, 1};
     for (const RowPass &p : P.fwd) {
@@ -1656,7 +2116,7 @@ hubbard_status build_program(const Model &m, const Tables &T, int layers, Progra
         for (int half = 0; half < 2; ++half) {   // chi2, then chi1 (stored negated)
             for (size_t s = 0; s < p.red_param.size(); ++s) {
                 rows_of[1 + p.red_param[s]].push_back(P.n_rows + (int)s);
-                nblk.push_back(rows_grid(T, p.col));
+                nblk.push_back(red_grid(p.col));
             }
             P.n_rows += (int)p.red_param.size();
         }
@@ -1879,6 +2339,8 @@ void set_attrs()
             (const void *)k_sec_rows_short<S_REV, false>, (const void *)k_sec_rows_short<S_REV, true>,
             (const void *)k_sec_rows_spread<false>,       (const void *)k_sec_rows_spread<true>,
             (const void *)k_sec_expand,
+            (const void *)k_sec_whole<false>,             (const void *)k_sec_whole<true>,
+            (const void *)k_sec_whole_batch<false>,       (const void *)k_sec_whole_batch<true>,
             (const void *)k_sec_rows_long<S_FWD, false>,  (const void *)k_sec_rows_long<S_FWD, true>,
             (const void *)k_sec_rows_long<S_REV, false>,  (const void *)k_sec_rows_long<S_REV, true>,
             (const void *)k_sec_ham_short<false>,         (const void *)k_sec_ham_short<true>,
@@ -1941,6 +2403,41 @@ size_t eval_bytes(const Tables &T, const Program &P, bool grad = true)
     return 4 * align256(vec_elems(T) * 16) + align256((size_t)(grad ? P.n_rows : 2) * kGrid * 8);
 }
 
+// Arguments of a whole evaluation.
+WholeArgs whole_args(const Tables &T, int layers, const double *theta, double *partial,
+                     int pstride, bool grad)
+{
+    WholeArgs A;
+    std::memset(&A, 0, sizeof(A));
+    A.gates = T.d_gates;
+    A.recs = T.whole.recs;
+    A.hcode = T.whole.hcode;
+    for (int s = 0; s < 2; ++s) {
+        A.pat[s] = T.sp[s].pat;
+        A.base[s] = T.sp[s].base;
+        A.n2[s] = T.whole.n2[s];
+        A.n13[s] = T.whole.n13[s];
+    }
+    A.wrow = T.sp[1].wrow;
+    A.tb = T.d_tb;
+    A.theta = theta;
+    A.U = T.U;
+    A.mix = T.mix;
+    A.n = T.n[0];
+    A.pitch = (T.n[0] + 1) | 1;
+    A.n_phases = T.n_phases;
+    A.per = T.per;
+    A.layers = layers;
+    A.nb = T.nb;
+    A.n_red = 2 * T.per - 1;
+    A.magic = ((1u << 20) + (uint32_t)T.n[0] - 1u) / (uint32_t)T.n[0];
+    A.b0_row = T.b0_rank[1];
+    A.b0_col = T.b0_rank[0];
+    A.partial = partial;
+    A.pstride = pstride;
+    A.grad = grad ? 1 : 0;
+    return A;
+}
 // E and, with grad != NULL, the gradient of the circuit's energy.
 void evaluate(const Tables &T, const Program &P, const double *theta, double *E, double *grad,
               char *w, hipStream_t s)
@@ -1951,6 +2448,20 @@ void evaluate(const Tables &T, const Program &P, const double *theta, double *E,
     double2 *psi[2] = {(double2 *)w, (double2 *)(w + v)};
     double2 *lam[2] = {(double2 *)(w + 2 * v), (double2 *)(w + 3 * v)};
     double *partial = (double *)(w + 4 * v);
+    const bool rev = grad && !P.fwd.empty();
+    if (P.whole) {
+        const int layers = std::max(0, (int)P.fwd.size() - 1);
+        const WholeArgs A = whole_args(T, layers, theta, partial, kGrid, rev);
+        const uint32_t lds = whole_lds(T, layers);
+        const dim3 grid(rev ? 2 : 1), th(T.whole.threads);
+        if (T.general)
+            hipLaunchKernelGGL((k_sec_whole<true>), grid, th, lds, s, A);
+        else
+            hipLaunchKernelGGL((k_sec_whole<false>), grid, th, lds, s, A);
+        hipLaunchKernelGGL(k_sec_reduce, dim3(rev ? P.n_out : 1), dim3(256), 0, s, partial, kGrid,
+                           P.d_nblk, P.d_ptr, P.d_rows, P.d_scale, E, grad);
+        return;
+    }
     auto at = [&](int col) { return T.is_long ? col : 0; };
     if (P.fwd.empty()) {
         hipLaunchKernelGGL(k_sec_basis, dim3(2048), dim3(256), 0, s, psi[0], vec_elems(T),
@@ -1961,7 +2472,6 @@ void evaluate(const Tables &T, const Program &P, const double *theta, double *E,
     // layout A lives in the first buffers, B in the second
     (void)forward(T, P, theta, psi[0], psi[1], true, true, s);
     int col = P.final_col;
-    const bool rev = grad && !P.fwd.empty();
     // lambda = H psi, the partial rows 0 and 1 get E; the reverse sweep runs
     // on chi1 (psi's buffers) and chi2 (lambda's): brackets from their
     // expectations
@@ -2025,7 +2535,7 @@ size_t ang_bytes(const Tables &T, int layers)
 
 struct SectorBatch {
     struct Launch {
-        int kind;   // S_FWD, S_REV, 2: H
+        int kind;   // S_FWD, S_REV, 2: H, 3: whole evaluations
         bool gen;
         int threads, lane, item0, n_items;
         uint32_t lds;
@@ -2034,6 +2544,7 @@ struct SectorBatch {
     size_t partial_at = 0;   // byte offset of the partial sums in the workspace
     sec::RowsArgs *d_rows = nullptr;
     sec::HamArgs *d_ham = nullptr;
+    sec::WholeArgs *d_whole = nullptr;
     sec::SecWork *d_work = nullptr;
     int32_t *d_seg_ptr = nullptr, *d_seg_cnt = nullptr;
     int64_t *d_seg_off = nullptr, *d_out_idx = nullptr;
@@ -2091,7 +2602,10 @@ SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
     std::map<std::pair<int, bool>, std::vector<int>> classes;
     std::map<std::pair<int, bool>, double> cost;
     for (int i = 0; i < n; ++i) {
-        const std::pair<int, bool> c{std::max(T[i]->sp[0].threads, T[i]->sp[1].threads),
+        // (whole evaluations: classes of their own)
+        const std::pair<int, bool> c{P[i]->whole
+                                         ? -T[i]->whole.threads
+                                         : std::max(T[i]->sp[0].threads, T[i]->sp[1].threads),
                                      T[i]->general};
         classes[c].push_back(i);
         cost[c] += (double)vec_elems(*T[i]) * layers[i];
@@ -2123,14 +2637,15 @@ SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
     int64_t np = 0;
     for (int i = 0; i < n; ++i) {
         prow[i] = np;
-        pstride[i] = std::max(rows_grid(*T[i], 0), rows_grid(*T[i], 1));
+        auto red_grid = [&](int col) { return P[i]->whole ? 1 : rows_grid(*T[i], col); };
+        pstride[i] = std::max(red_grid(0), red_grid(1));
         np += (int64_t)P[i]->n_rows * pstride[i];
         scale[i] = 1.0;
         out_idx[i] = i;
         const Program &p = *P[i];
         auto seg = [&](int row, int col) {
             return std::make_pair(prow[i] + (int64_t)row * pstride[i],
-                                  (int32_t)rows_grid(*T[i], col));
+                                  (int32_t)red_grid(col));
         };
         segs[i].push_back(seg(0, p.final_col));
         segs[i].push_back(seg(1, 1 - p.final_col));
@@ -2146,6 +2661,7 @@ SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
     double *partial = (double *)(ws + at);
     std::vector<RowsArgs> rows;
     std::vector<HamArgs> hams;
+    std::vector<WholeArgs> wholes;
     std::vector<SecWork> work;
     size_t longest = 0;
     for (int i = 0; i < n; ++i)
@@ -2153,6 +2669,8 @@ SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
     // position `pos` of kind `kind`: one launch per class that has one
     auto position = [&](int kind, size_t pos) {
         for (size_t c = 0; c < order.size(); ++c) {
+            if ((order[c].first < 0) != (kind == 3))
+                continue;
             SectorBatch::Launch L;
             L.kind = kind;
             L.gen = order[c].second;
@@ -2163,6 +2681,18 @@ SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
             for (int i : classes[order[c]]) {
                 const Tables &t = *T[i];
                 const Program &p = *P[i];
+                if (kind == 3) {
+                    SecWork w;
+                    w.args = (int32_t)wholes.size();
+                    w.bid = w.pad = 0;
+                    wholes.push_back(whole_args(t, (int)p.fwd.size() - 1, theta + toff[i],
+                                                partial + prow[i], pstride[i], true));
+                    L.threads = t.whole.threads;
+                    L.lds = std::max(L.lds, whole_lds(t, (int)p.fwd.size() - 1));
+                    for (w.vsel = 0; w.vsel < 2; ++w.vsel)
+                        work.push_back(w);
+                    continue;
+                }
                 const size_t len = kind == 2 ? 2 : p.fwd.size();
                 if (pos >= len)
                     continue;
@@ -2208,6 +2738,7 @@ SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
                 B->launches.push_back(L);
         }
     };
+    position(3, 0);
     for (size_t j = 0; j < longest; ++j)
         position(S_FWD, j);
     position(2, 0);
@@ -2227,6 +2758,7 @@ SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
     Blob blob;
     blob.add(&B->d_rows, rows);
     blob.add(&B->d_ham, hams);
+    blob.add(&B->d_whole, wholes);
     blob.add(&B->d_work, work);
     blob.add(&B->d_seg_ptr, seg_ptr);
     blob.add(&B->d_seg_cnt, seg_cnt);
@@ -2261,7 +2793,12 @@ void sector_batch_launch(const SectorBatch *b, const hipStream_t *lane)
         hipStream_t s = lane[l.lane];
 #define HV_SEC_BATCH(K, ARGS)                                                                   \
     hipLaunchKernelGGL((K), dim3(l.n_items), dim3(l.threads), l.lds, s, ARGS, w)
-        if (l.kind == 2) {
+        if (l.kind == 3) {
+            if (l.gen)
+                HV_SEC_BATCH(k_sec_whole_batch<true>, b->d_whole);
+            else
+                HV_SEC_BATCH(k_sec_whole_batch<false>, b->d_whole);
+        } else if (l.kind == 2) {
             if (l.gen)
                 HV_SEC_BATCH(k_sec_ham_batch<true>, b->d_ham);
             else

@@ -32,6 +32,10 @@ CASES = {
     "1x10 U=0": inst(1, 10, 2, 3, 906, U=0.0),
     "3x4 cylinder": inst(3, 4, 2, 5, 907, U=4.0, periodic_y=True),
     "0 layers": inst(2, 3, 0, 5, 908, U=4.0, V=0.3),
+    # the largest sector that is evaluated whole, and more layers than that takes
+    "1x7": inst(1, 7, 5, 3, 910, U=4.0),
+    "1x7 general": inst(1, 7, 4, 3, 911, U=2.0, V=0.5, eps_width=0.4, disorder=0.1),
+    "1x2 deep": inst(1, 2, 1030, 2, 912, U=1.0),
 }
 
 
@@ -87,7 +91,7 @@ def test_graph_routes(gpu, key):
 def test_batch_is_its_members_bit_for_bit(gpu):
     # workgroup sizes 64, 128 and 320; U-only and general members; one model twice
     ws = [CASES[k] for k in ("1x2", "2x2 general", "1x6 ring", "3x3", "2x5 general",
-                             "3x4 cylinder", "3x3")]
+                             "3x4 cylinder", "1x7 general", "3x3")]
     models = [Hubbard(w.nx, w.ny, **w.kwargs()) for w in ws[:-1]]
     models.append(models[3])
     b = Batch(models, [w.layers for w in ws])
