@@ -35,7 +35,7 @@ CASES = {
     # the largest sector that is evaluated whole, and more layers than that takes
     "1x7": inst(1, 7, 5, 3, 910, U=4.0),
     "1x7 general": inst(1, 7, 4, 3, 911, U=2.0, V=0.5, eps_width=0.4, disorder=0.1),
-    "1x2 deep": inst(1, 2, 1030, 2, 912, U=1.0),
+    "1x7 deep": inst(1, 7, 700, 3, 912, U=1.0, V=0.2),
 }
 
 
