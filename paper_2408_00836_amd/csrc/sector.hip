@@ -78,6 +78,9 @@ enum { SF_NO_STORE = 1, SF_START = 2, SF_TURN = 4, SF_BOTH = 8 };
 enum { HO_SET = 0, HO_ADD = 1, HO_MIX = 2, HO_NONE = 3 };
 
 typedef __attribute__((address_space(1))) double2 gc128;
+typedef __attribute__((address_space(3))) double lds64w;
+// LDS byte address (of kernels whose only LDS is their launch's, which begins at 0)
+__device__ __forceinline__ lds64w *lds_at(uint32_t a) { return (lds64w *)(uintptr_t)a; }
 typedef const __attribute__((address_space(1))) uint16_t gu16;
 typedef const __attribute__((address_space(1))) uint32_t gu32;
 typedef const __attribute__((address_space(1))) uint4 gu128;
@@ -960,28 +963,27 @@ __device__ __forceinline__ LongCodes col_codes(const uint16_t *colslot, int t)
 // Move a row from one register layout to another through LDS.
 template <int NF, int NTO>
 __device__ __forceinline__ void long_exchange(const double2 (&from)[NF], const LongCodes &fcodes,
-                                              double2 (&to)[NTO], const LongCodes &tcodes,
-                                              char *buf)
+                                              double2 (&to)[NTO], const LongCodes &tcodes)
 {
     double re[NTO];
     const LongAddr<NF> cf(fcodes);
     __syncthreads();   // the last exchange's reads are done
 #pragma unroll
     for (int j = 0; j < NF; ++j)
-        *(double *)(buf + cf.a[j]) = from[j].x;
+        *lds_at(cf.a[j]) = from[j].x;
     const LongAddr<NTO> ct(tcodes);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < NTO; ++j)
-        re[j] = *(const double *)(buf + ct.a[j]);
+        re[j] = *lds_at(ct.a[j]);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < NF; ++j)
-        *(double *)(buf + cf.a[j]) = from[j].y;
+        *lds_at(cf.a[j]) = from[j].y;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < NTO; ++j)
-        to[j] = make_double2(re[j], *(const double *)(buf + ct.a[j]));
+        to[j] = make_double2(re[j], *lds_at(ct.a[j]));
 }
 
 template <int MODE, bool GEN>
@@ -1054,7 +1056,7 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
             if constexpr (GEN)
                 if (A.l_diag >= 0 && tid < 64)   // read after the exchange's barriers
                     nib[tid] = nibble_sum((const gf64 *)A.wrow + (size_t)r * 16, tid);
-            long_exchange(in, cc, x, cur, smem);
+            long_exchange(in, cc, x, cur);
         }
         auto diag = [&]() __attribute__((always_inline)) {
             const double th = A.theta[A.l_diag * A.per];
@@ -1098,7 +1100,7 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
                 asm volatile("" : "+v"(tn));
                 const LongCodes nxt = long_codes(lcode + ((size_t)pn * kLongT + tn) * 2);
                 double2 y[kOrbitElems];
-                long_exchange(x, cur, y, nxt, smem);
+                long_exchange(x, cur, y, nxt);
                 cur = nxt;
 #pragma unroll
                 for (int j = 0; j < kOrbitElems; ++j)
@@ -1109,7 +1111,7 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
             uint32_t ts = (uint32_t)tid;
             asm volatile("" : "+v"(ts));
             double2 out[kLongElems];
-            long_exchange(x, cur, out, col_codes(A.colslot, (int)ts), smem);
+            long_exchange(x, cur, out, col_codes(A.colslot, (int)ts));
 #pragma unroll
             for (int j = 0; j < kLongElems; ++j) {
                 const uint32_t i = ts + (uint32_t)(j * kLongT);
@@ -1136,6 +1138,7 @@ struct HamArgs {
     const double *rbase, *wrow, *tb;   // tb: -t_b per bond, padded with zeros
     double U;
     int n, n_rows, nslots, lr, nb, diag, out_mode, turn;   // turn (long rows): out is transposed
+    int n_flat;                        // long rows: bonds without a sign, which come first
     int64_t rs, cs;
     double2 *psi, *out;
     double mix;                        // HO_MIX: m, a power of two
@@ -1615,6 +1618,11 @@ k_sec_whole_batch(const WholeArgs *__restrict__ args, const SecWork *__restrict_
 // turns in LDS.  Thread t sums for the slots t + j kLongT: lanes of
 // neighbouring slots are in different bank classes, and so are their
 // partners across one bond.
+// Bound by VALU (half of its time) and by the row's phases not overlapping:
+// load, two rounds of sums, store.  At 12870 x 12870 and 32 bonds a pass took
+// 4.3 ms; the imaginary parts kept from the one load of the row 3.8; signs apart
+// from the partners' codes, bonds without signs first and LDS addressed without
+// a base 3.5.
 template <bool GEN>
 __global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
 {
@@ -1641,7 +1649,7 @@ __global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
         const double rb = GEN ? rbase[r] : 0.0;
         int t = tid;   // the tables' values are not kept across rows
         asm volatile("" : "+v"(t));
-        double re_out[kLongElems];
+        double re_out[kLongElems];   // first the imaginary parts, then the real results
         LongCodes cc = col_codes(A.colslot, t);
         __syncthreads();
         if (GEN && A.diag && tid < 64)
@@ -1649,8 +1657,10 @@ __global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
 #pragma unroll
         for (int j = 0; j < kLongElems; ++j) {
             const uint32_t i = (uint32_t)(t + j * kLongT);
-            const double x = psi[min(i, n - 1)].x;
-            *(double *)(smem + cc.at(j)) = i < n ? x : 0.0;
+            const gc128 *p = psi + min(i, n - 1);
+            const double2 x = make_double2(p->x, p->y);
+            *(double *)(smem + cc.at(j)) = i < n ? x.x : 0.0;
+            re_out[j] = i < n ? x.y : 0.0;
         }
 #pragma unroll 1
         for (int half = 0; half < 2; ++half) {
@@ -1670,19 +1680,27 @@ __global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
             }
             cc.renew();
             LongCodes nx = col_codes(A.hcode, t);   // the same chunk layout
+            // the bonds without a Jordan-Wigner string come first; of the
+            // others, bit 31 - j of the last dword is element j's sign
+            auto bonds = [&](auto sgn, int b0, int b1) __attribute__((always_inline)) {
 #pragma unroll 1
-            for (int b = 0; b < A.nb; ++b) {
-                const LongCodes w = nx;
-                nx = col_codes(A.hcode + (size_t)min(b + 1, A.nb - 1) * 16 * kLongT, t);
-                const double m = tb[b];
+                for (int b = b0; b < b1; ++b) {
+                    const LongCodes w = nx;
+                    nx = col_codes(A.hcode + (size_t)min(b + 1, A.nb - 1) * 16 * kLongT, t);
+                    const double m = tb[b];
 #pragma unroll
-                for (int j = 0; j < kLongElems; ++j) {
-                    const uint32_t o = j & 1 ? (w.w[j >> 1] >> 13) & 0x3FFF8u
-                                             : (w.w[j >> 1] << 3) & 0x3FFF8u;
-                    const double p = *(const double *)(smem + o);
-                    phi[j] = fma(xor_sign(m, code_sign(w.w[j >> 1], j & 1)), p, phi[j]);
+                    for (int j = 0; j < kLongElems; ++j) {
+                        const uint32_t q = w.w[j >> 1];
+                        const uint32_t o = j & 1 ? (q >> 13) & 0x7FFF8u : (q << 3) & 0x7FFF8u;
+                        double p = *lds_at(o);
+                        if constexpr (decltype(sgn)::value)
+                            p = xor_sign(p, (w.w[7] << j) & 0x80000000u);
+                        phi[j] = fma(m, p, phi[j]);
+                    }
                 }
-            }
+            };
+            bonds(std::false_type(), 0, A.n_flat);
+            bonds(std::true_type(), A.n_flat, A.nb);
 #pragma unroll
             for (int j = 0; j < kLongElems; ++j) {
                 const int sl = t + j * kLongT;
@@ -1699,15 +1717,11 @@ __global__ void __launch_bounds__(kLongT) k_sec_ham_long(HamArgs A)
             __syncthreads();
             if (half == 0) {
 #pragma unroll
-                for (int j = 0; j < kLongElems; ++j)
-                    re_out[j] = *(const double *)(smem + cc.at(j));
-                __syncthreads();
-#pragma unroll
-                for (int j = 0; j < kLongElems; ++j)
-                {
-                    const uint32_t i = (uint32_t)(t + j * kLongT);
-                    const double y = psi[min(i, n - 1)].y;
-                    *(double *)(smem + cc.at(j)) = i < n ? y : 0.0;
+                for (int j = 0; j < kLongElems; ++j) {   // a thread's own places
+                    double *o = (double *)(smem + cc.at(j));
+                    const double y = re_out[j];
+                    re_out[j] = *o;
+                    *o = y;
                 }
             } else {
 #pragma unroll
@@ -1834,6 +1848,7 @@ struct Tables {
     bool is_long = false;
     double U = 0.0, mix = 1.0;
     int n_phases = 0, nb = 0, per = 1;
+    int n_flat = 0;               // long rows' H: bonds without a sign
     SpinTables sp[2];
     SecGate *d_gates = nullptr;
     double *d_tb = nullptr;
@@ -2001,8 +2016,9 @@ hubbard_status build_tables(const Model &m, Tables &T)
     B.add(&T.d_gates, P.gates);
     std::vector<double> tb((size_t)std::max(8, ham_bonds(m.nb)), 0.0);
     for (int k = 0; k < m.nb; ++k)
-        tb[k] = -m.t[k];
+        tb[k] = -m.t[P.ham_order[k]];
     B.add(&T.d_tb, tb);
+    T.n_flat = P.n_flat;
     for (int s = 0; s < 2; ++s) {
         const SpinPlan &S = P.spin[s];
         SpinTables &D = T.sp[s];
@@ -2282,6 +2298,7 @@ HamArgs ham_args(const Tables &T, int col, bool with_d, double2 *psi, double2 *o
     A.nslots = S.nslots;
     A.lr = S.lr;
     A.nb = T.nb;
+    A.n_flat = T.n_flat;
     A.diag = with_d ? 1 : 0;
     A.out_mode = out_mode;
     A.turn = turn ? 1 : 0;

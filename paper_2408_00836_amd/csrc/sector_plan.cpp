@@ -409,7 +409,8 @@ void build_spin(const Model &m, SectorPlan &P, int s, int n_rows)
     // H: for every bond the slot of the partner pattern and the hop's sign
     // (an inactive element: the zero slot nslots).  Short rows: per rank,
     // ham_bonds(nb) codes; long rows: per bond, element t + j kLongT counted
-    // by slots, at long_index.
+    // by slots, at long_index, the signs apart: bit 31 - j of the dword that
+    // the thread's codes 14 and 15 make.
     const int hb = ham_bonds(m.nb);
     auto code = [&](int r, int k) -> uint16_t {
         if (r < 0)
@@ -431,12 +432,19 @@ void build_spin(const Model &m, SectorPlan &P, int s, int n_rows)
         const size_t per = (size_t)2 * kLongT * 8;
         S.hcode.assign(per * std::max(1, m.nb), (uint16_t)S.nslots);
         for (int k = 0; k < m.nb; ++k)
-            for (int t = 0; t < kLongT; ++t)
+            for (int t = 0; t < kLongT; ++t) {
+                uint32_t signs = 0;
                 for (int j = 0; j < kLongElems; ++j) {
                     const int e = t + j * kLongT;
-                    if (e < S.nslots)
-                        S.hcode[per * k + long_index(t, j)] = code(rank_at[e], k);
+                    if (e < S.nslots) {
+                        const uint16_t c = code(rank_at[e], P.ham_order[k]);
+                        S.hcode[per * k + long_index(t, j)] = c & 0x7FFFu;
+                        signs |= (uint32_t)(c >> 15) << (31 - j);
+                    }
                 }
+                S.hcode[per * k + long_index(t, 14)] = (uint16_t)signs;
+                S.hcode[per * k + long_index(t, 15)] = (uint16_t)(signs >> 16);
+            }
     }
 }
 
@@ -483,6 +491,14 @@ std::string plan_sector(const Model &m, SectorPlan &P)
             return "sector rows longer than 13 x 1024";
     }
     plan_clusters(m, P);
+    for (int k = 0; k < m.nb; ++k)
+        P.ham_order.push_back(k);
+    if (P.spin[0].n > kShortRow)
+        P.n_flat = (int)(std::stable_partition(P.ham_order.begin(), P.ham_order.end(),
+                                               [&](int k) {
+                                                   return std::abs(m.bi[k] - m.bj[k]) == 1;
+                                               }) -
+                         P.ham_order.begin());
     for (int s = 0; s < 2; ++s) {
         build_spin(m, P, s, P.spin[1 - s].n);
         SpinPlan &S = P.spin[s];

@@ -97,6 +97,8 @@ struct SectorPlan {
     std::vector<SecGate> gates;              // kPositions per phase
     std::vector<std::array<int, 4>> sites;   // per phase: sites 0..3 (>= ns: none)
     std::vector<std::array<int, 4>> bond;    // per phase and position: its bond, or -1
+    std::vector<int> ham_order;              // H's bonds in the order of hcode: long rows'
+    int n_flat = 0;                          // without a Jordan-Wigner string first, n_flat of them
     SpinPlan spin[2];
 };
 
