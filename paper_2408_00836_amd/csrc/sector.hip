@@ -1054,8 +1054,11 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
             }
             const LongCodes cc = col_codes(A.colslot, (int)t);
             if constexpr (GEN)
-                if (A.l_diag >= 0 && tid < 64)   // read after the exchange's barriers
-                    nib[tid] = nibble_sum((const gf64 *)A.wrow + (size_t)r * 16, tid);
+                if (A.l_diag >= 0) {
+                    __syncthreads();   // the diagonal may have been the last row's last step
+                    if (tid < 64)      // read after the exchange's barriers
+                        nib[tid] = nibble_sum((const gf64 *)A.wrow + (size_t)r * 16, tid);
+                }
             long_exchange(in, cc, x, cur);
         }
         auto diag = [&]() __attribute__((always_inline)) {
