@@ -894,8 +894,11 @@ k_sec_rows_batch(const RowsArgs *__restrict__ args, const SecWork *__restrict__ 
 // Bound by LDS traffic and VALU: 206 KB go through LDS in each direction per
 // phase, eight phases per layer and spin at 4x4 periodic where an exchange per
 // hop needed 32.  At 12870 x 12870 (5.3 GB moved) a forward pass of 64 hops
-// takes 3.07 ms (7.89 ms with an exchange per hop), the reverse pass of both
-// vectors 7.72 ms (18.6 ms).
+// with its transposed store takes 3.9 ms (an exchange per hop and a transpose:
+// 9.1 ms), the reverse pass of both vectors 8.6 (20.9).  The diagonal's
+// products must not be put off past flush: kept waiting there they spilled 750
+// bytes per thread in reverse, 55 against 40 ms per evaluation of a general
+// torus of two layers.
 struct LongCodes {
     uint32_t w[8];
     // LDS byte offset of element j
@@ -1081,7 +1084,9 @@ __global__ void __launch_bounds__(kLongT) k_sec_rows_long(RowsArgs A)
                     const int k = __popc(rp & cp);
                     diag_el<REV, false>(x[j], A.U * (double)k, 0.0, C.dtab[k], th, nullptr, racc);
                 }
-                __builtin_amdgcn_sched_barrier(0);   // fewer values in flight
+                // fewer values in flight, and none of the products put off past flush
+                asm volatile("" : "+v"(x[j].x), "+v"(x[j].y));
+                __builtin_amdgcn_sched_barrier(0);
             }
             if constexpr (REV)
                 C.flush(C.dslot, racc);
@@ -2022,6 +2027,7 @@ hubbard_status build_tables(const Model &m, Tables &T)
         tb[k] = -m.t[P.ham_order[k]];
     B.add(&T.d_tb, tb);
     T.n_flat = P.n_flat;
+    const bool same = T.ne[0] == T.ne[1];   // one set of tables
     for (int s = 0; s < 2; ++s) {
         const SpinPlan &S = P.spin[s];
         SpinTables &D = T.sp[s];
@@ -2031,6 +2037,8 @@ hubbard_status build_tables(const Model &m, Tables &T)
         D.threads = S.threads;
         D.is_long = S.is_long;
         T.is_long = T.is_long || S.is_long;
+        if (s == 1 && same)
+            break;
         B.add(&D.phases, S.phases);
         B.add(&D.recs, S.recs);
         B.add(&D.lcode, S.lcode);
@@ -2058,6 +2066,8 @@ hubbard_status build_tables(const Model &m, Tables &T)
     if (e != hipSuccess)
         return fail(HUBBARD_ERR_DEVICE, std::string("uploading sector tables: ") +
                                             hipGetErrorString(e));
+    if (same)
+        T.sp[1] = T.sp[0];
     return HUBBARD_OK;
 }
 

@@ -500,6 +500,10 @@ std::string plan_sector(const Model &m, SectorPlan &P)
                                                }) -
                          P.ham_order.begin());
     for (int s = 0; s < 2; ++s) {
+        if (s == 1 && P.spin[1].n_el == P.spin[0].n_el) {   // the same rows
+            P.spin[1] = P.spin[0];
+            break;
+        }
         build_spin(m, P, s, P.spin[1 - s].n);
         SpinPlan &S = P.spin[s];
         if (S.is_long && S.nslots > kMaxRows)
