@@ -25,8 +25,9 @@
 //
 // Rows of up to kShortRow elements live in LDS, 2^lr of them per workgroup;
 // down passes read the matrix by columns.  Longer rows (16 sites) live in
-// registers, one per workgroup, and the state is transposed between the
-// passes of the two spins (layout A: rows r_dn; layout B: the transpose).
+// registers, one per workgroup, and a pass stores its result transposed for
+// the other spin's (layout A: rows r_dn; layout B: the transpose).  Small
+// matrices stay in one workgroup's LDS for a whole evaluation.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
