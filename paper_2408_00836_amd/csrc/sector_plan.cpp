@@ -128,7 +128,10 @@ void plan_clusters(const Model &m, SectorPlan &P)
         }
         P.sites.push_back({sites[order[0]], sites[order[1]], sites[order[2]], sites[order[3]]});
         P.bond.push_back(bond);
-        int slot = 1;   // of a position without a hop: any hop's of the phase
+        // a position without a hop takes the slot of a hop of its phase; in the
+        // one phase of a model without bonds there is none: slot 0, which is a
+        // parameter (the layer has no other) but no group's, and nothing reduced
+        int slot = 0;
         for (int q = 0; q < kPositions; ++q)
             if (bond[q] >= 0)
                 slot = m.slot[bond[q]];
@@ -143,7 +146,7 @@ void plan_clusters(const Model &m, SectorPlan &P)
         std::reverse(P.gates.end() - kPositions, P.gates.end());
         for (int q = 0; q < kPositions; ++q) {
             SecGate *g = &P.gates[P.gates.size() - kPositions + q];
-            g->last = q == 0 || g[-1].slot != g->slot;
+            g->last = g->slot > 0 && (q == 0 || g[-1].slot != g->slot);
         }
         todo = without(w);
     } while (!todo.empty());

@@ -43,8 +43,9 @@ constexpr int kOrbitElems = 15;               // a long-row thread's elements in
 constexpr int kPositions = 4;
 constexpr int kPosA[kPositions] = {0, 2, 0, 1}, kPosB[kPositions] = {1, 3, 2, 3};
 struct SecGate {
-    int32_t slot;    // parameter slot in the layer, 1..groups
-    int32_t last;    // reverse order: the phase's next position has another slot
+    int32_t slot;    // parameter slot in the layer, 1..groups (0: the model has no bonds)
+    int32_t last;    // reverse order: the phase's next position has another slot, so the
+                     // slot's sum is complete (never with slot 0, which has no sum)
     double t;        // hopping t_b
 };
 static_assert(sizeof(SecGate) == 16, "SecGate layout");
