@@ -2008,19 +2008,7 @@ hubbard_status build_tables(const Model &m, Tables &T)
     T.n_phases = (int)P.sites.size();
     T.nb = m.nb;
     T.per = m.params_per_layer();
-    // m = 2^k near sqrt |H psi|: an evenly filled state's hops give |H psi|^2
-    // a term t^2 per bond (both spins) and its diagonal a mean value
-    double hop2 = 0.0, mean = 0.25 * m.U * m.ns;
-    for (int k = 0; k < m.nb; ++k) {
-        hop2 += m.t[k] * m.t[k];
-        mean += m.V[k];
-    }
-    for (int i = 0; i < m.ns; ++i)
-        mean += m.eps[i];
-    const double norm = std::sqrt(hop2 + mean * mean);
-    T.mix = norm > 0.0 && std::isfinite(norm)
-                ? std::ldexp(1.0, std::max(-64, std::min(64, (int)std::lround(0.5 * std::log2(norm)))))
-                : 1.0;
+    T.mix = P.mix;
     Blob B;
     B.add(&T.d_gates, P.gates);
     std::vector<double> tb((size_t)std::max(8, ham_bonds(m.nb)), 0.0);

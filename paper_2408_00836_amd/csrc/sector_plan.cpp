@@ -1,6 +1,7 @@
 // sector_plan.cpp -- clusters, orbits and LDS slots of the particle-number
 // sector form.  Host only; no GPU calls.
 #include <algorithm>
+#include <cmath>
 #include <string>
 
 #include "sector_plan.hpp"
@@ -451,6 +452,53 @@ void build_spin(const Model &m, SectorPlan &P, int s, int n_rows)
     }
 }
 
+// m of the reverse sweep's vectors chi = lambda / m -+ i m psi: a power of two
+// near the square root of |H psi| / |psi|.  The rounding of <chi2|G|chi2> -
+// <chi1|G|chi1> grows with |lambda|^2 / m^2 + m^2 |psi|^2, which is least there.
+// |H psi|^2 of an evenly filled state: t^2 for every bond and spin that moves an
+// electron, and the sector's mean of D^2.  (The mean of D in D^2's place vanishes
+// for a staggered potential and for eps against U: m = 2 instead of 32 for eps =
+// +-1000, and the gradient's error was ten to thirty times that of Im
+// <lambda|G|psi> summed directly; with D^2 the two are alike.)
+double mix_scale(const Model &m, const SectorPlan &P)
+{
+    const SpinPlan &X = P.spin[0], &Y = P.spin[1];
+    const int ns = m.ns;
+    // the probability that two sites hold two electrons, or one
+    auto two = [ns](double n) { return ns > 1 ? n * (n - 1.0) / (ns * (ns - 1.0)) : 0.0; };
+    auto one = [ns](double n) { return ns > 1 ? 2.0 * n * (ns - n) / (ns * (ns - 1.0)) : 0.0; };
+    double norm2 = 0.0;
+    for (int k = 0; k < m.nb; ++k)
+        norm2 += m.t[k] * m.t[k] * (one(X.n_el) + one(Y.n_el));
+    // D = A(p) + A(q) + sum_j p_j w_j(q), p and q the two spins' patterns: the mean
+    // over p of the square from A's and the p_j's moments, then over q
+    double a1 = 0.0, a2 = 0.0, ap[16] = {0.0};
+    for (int r = 0; r < X.n; ++r) {
+        a1 += X.base[r] / X.n;
+        a2 += X.base[r] * X.base[r] / X.n;
+        for (int i = 0; i < ns; ++i)
+            ap[i] += (X.pat[r] >> i) & 1u ? X.base[r] / X.n : 0.0;
+    }
+    const double p1 = (double)X.n_el / ns, p2 = two(X.n_el);
+    for (int r = 0; r < Y.n; ++r) {
+        const double b = Y.base[r];
+        double sum = 0.0, sq = 0.0, aw = 0.0;
+        for (int i = 0; i < ns; ++i) {
+            const double w = m.general ? Y.wrow[(size_t)r * 16 + i]
+                                       : ((Y.pat[r] >> i) & 1u ? m.U : 0.0);
+            sum += w;
+            sq += w * w;
+            aw += w * ap[i];
+        }
+        norm2 += (a2 + b * b + sq * p1 + (sum * sum - sq) * p2 +
+                  2.0 * (a1 * b + aw + b * sum * p1)) / Y.n;
+    }
+    const double norm = std::sqrt(norm2);
+    if (!(norm > 0.0) || !std::isfinite(norm))
+        return 1.0;
+    return std::ldexp(1.0, std::max(-64, std::min(64, (int)std::lround(0.5 * std::log2(norm)))));
+}
+
 }  // namespace
 
 std::string plan_sector(const Model &m, SectorPlan &P)
@@ -512,6 +560,7 @@ std::string plan_sector(const Model &m, SectorPlan &P)
         if (S.is_long && S.nslots > kMaxRows)
             return "sector row slots exceed 13 x 1024";
     }
+    P.mix = mix_scale(m, P);
     return "";
 }
 

@@ -101,6 +101,7 @@ struct SectorPlan {
     std::vector<int> ham_order;              // H's bonds in the order of hcode: long rows'
     int n_flat = 0;                          // without a Jordan-Wigner string first, n_flat of them
     SpinPlan spin[2];
+    double mix = 1.0;                        // m of the reverse sweep's vectors, a power of two
 };
 
 // Codes per row element of H's tables: bonds padded to whole 16-byte chunks.

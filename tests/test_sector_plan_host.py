@@ -1,6 +1,6 @@
 """The sector form's host plan (sector_plan.cpp), compiled with g++ and read
 directly: what the kernels index with it stays inside the angles and the
-reduction slots of a layer."""
+reduction slots of a layer, and the scale of the reverse sweep's vectors."""
 import os
 import subprocess
 
@@ -40,7 +40,7 @@ int main()
         std::printf("error %s\n", err.c_str());
         return 1;
     }
-    std::printf("per %d\nphases %zu\n", m.params_per_layer(), P.sites.size());
+    std::printf("per %d\nphases %zu\nmix %.17g\n", m.params_per_layer(), P.sites.size(), P.mix);
     for (const sec::SecGate &g : P.gates)
         std::printf("gate %d %d %.17g\n", g.slot, g.last, g.t);
     return 0;
@@ -115,3 +115,47 @@ def test_gates_stay_in_the_layers_parameters(plan, key):
         assert ends == (want if bonds else [0] * 4)
     # and every bond is applied once a layer
     assert sum(1 for g in r["gate"] if g[2] != 0.0) == len(bonds)
+
+
+def mean_h2(ns, bonds, U, t, V, eps, spins):
+    """|H psi|^2 of a state spread evenly over the sector with random phases:
+    the mean over its basis states of D^2 plus the squares of H's hops."""
+    up = [p for p in range(1 << ns) if bin(p).count("1") == spins.count(0)]
+    dn = [p for p in range(1 << ns) if bin(p).count("1") == spins.count(1)]
+    tot = 0.0
+    for u in up:
+        for d in dn:
+            n = [(u >> i & 1) + (d >> i & 1) for i in range(ns)]
+            D = U * bin(u & d).count("1") + sum(e * k for e, k in zip(eps, n))
+            D += sum(v * n[i] * n[j] for (i, j), v in zip(bonds, V))
+            tot += D * D + sum(a * a * ((p >> i ^ p >> j) & 1) for (i, j), a in zip(bonds, t)
+                               for p in (u, d))
+    return tot / (len(up) * len(dn))
+
+
+def staggered(n, e):
+    return [e if i % 2 == 0 else -e for i in range(n)]
+
+
+MODELS = {
+    "U": dict(U=4.0),
+    "general": dict(U=4.0, V=[0.5, -0.3, 0.2, 0.4, -0.1], eps=[0.3, -0.2, 0.1, 0.4, -0.5, 0.2]),
+    "staggered": dict(U=4.0, eps=staggered(6, 1e3)),
+    "eps against U": dict(U=1e4, eps=[-2.5e3] * 6),
+    "eps against U, weak hops": dict(U=8.0, t=[1e-3] * 5, eps=[-2.0] * 6),
+    "V against U": dict(U=-20.0, V=[6.0] * 5),
+    "off half filling": dict(U=3.0, eps=staggered(6, 50.0), spins=[0, 0, 1, 0, 0, 0]),
+    "one spin": dict(U=3.0, eps=[1.0, 2.0, 3.0, 4.0, 5.0, 6.0], spins=[0] * 6),
+}
+
+
+@pytest.mark.parametrize("key", list(MODELS))
+def test_mix_is_near_the_root_of_h(plan, key):
+    # m = 2^k nearest to sqrt |H psi|: m^4 within a factor of four of |H psi|^2,
+    # whatever cancels in the mean of D
+    kw = dict(t=[1.0] * 5, V=[0.0] * 5, eps=[0.0] * 6, spins=[0, 1, 0, 1, 0, 1])
+    kw.update(MODELS[key])
+    m = plan(6, path(6), **kw)["mix"]
+    h2 = mean_h2(6, path(6), **kw)
+    assert m == 2.0 ** round(np.log2(m))
+    assert 0.25 * (1 - 1e-9) <= m ** 4 / h2 <= 4.0 * (1 + 1e-9)
