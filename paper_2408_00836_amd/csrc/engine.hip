@@ -51,16 +51,16 @@ hubbard_status lanczos_run(const ApplyH &apply, uint64_t n, const double2 *start
                            double *residual, double2 *gs_dev, double2 *const buf[3],
                            double2 *partial, hipStream_t s);
 size_t lanczos_partial_bytes();
-// sector.hip: evaluations from |b0> on its particle-number sector
 // ham.hip: H on full vectors by gathering
 bool ham_gather_ok(const Model &m);
 std::vector<double> ham_site_table(const Model &m);
 void ham_gather(const Model &m, const double *site, const double2 *psi, double2 *out,
                 hipStream_t s);
-bool sector_state_ok(hubbard_t h, int layers);
+// sector.hip: evaluations from |b0> on its particle-number sector
+bool sector_state_ok(hubbard_t h, int layers, hipStream_t s);
 hubbard_status sector_state(hubbard_t h, int layers, const double *theta, double2 *psi,
                             hipStream_t s);
-size_t sector_eval_bytes(hubbard_t h, int layers, bool grad);
+size_t sector_eval_bytes(hubbard_t h, int layers, bool grad, hipStream_t s);
 size_t sector_eval_ready(hubbard_t h, int layers);
 hubbard_status sector_eval(hubbard_t h, int layers, const double *theta, double *E, double *grad,
                            void *ws, hipStream_t s);
@@ -888,9 +888,10 @@ hubbard_status run_ham(const Program &pr, const DeviceState &ds, const double2 *
 
 // Whether hamiltonian_apply and hubbard_lanczos gather (ham.hip); uploads the
 // tables of a general model.  The passes remain for H with energies (the
-// gradient's), for the timing mode, which times them, and for models that
-// ham_gather_ok leaves to them.
-bool gather_route(hubbard_model *h, DeviceState &ds)
+// gradient's), for the timing mode, which times them, for models that
+// ham_gather_ok leaves to them, and for a capture before the tables are there,
+// which may not allocate them.
+bool gather_route(hubbard_model *h, DeviceState &ds, hipStream_t s)
 {
     if (h->timing || !ham_gather_ok(h->m))
         return false;
@@ -899,6 +900,9 @@ bool gather_route(hubbard_model *h, DeviceState &ds)
     std::lock_guard<std::mutex> lk(h->mu);
     if (ds.d_site)
         return true;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
+        return false;
     try {
         const std::vector<double> e = ham_site_table(h->m);
         double *p = nullptr;
@@ -920,7 +924,7 @@ bool gather_route(hubbard_model *h, DeviceState &ds)
 hubbard_status apply_ham(hubbard_model *h, const Program &pr, DeviceState &ds, const double2 *in,
                          double2 *out, hipStream_t s)
 {
-    if (!gather_route(h, ds))
+    if (!gather_route(h, ds, s))
         return run_ham(pr, ds, in, out, nullptr, s, h);
     ham_gather(h->m, ds.d_site, in, out, s);
     return check_launch("hamiltonian");
@@ -971,14 +975,15 @@ VecLayout grad_layout(const hubbard_model *h)
 // form, one evaluation): 8 qubits 75 / 17 us, 16 qubits 486 / 148 us, 24
 // qubits with the general diagonal 16.2 / 0.98 ms, 28 qubits 92.9 / 3.2 ms.
 // The full vector remains for the NP ansatz, for models whose sector plan is
-// refused, for a workspace too small for the sector's vectors, and under
-// hubbard_set_timing, which times the full vector's pass kernels.
-bool sector_route(hubbard_model *h, int layers, bool grad, size_t ws_bytes)
+// refused, for a workspace too small for the sector's vectors, for a capture
+// before the sector's tables are there (the full vector's are: the caller has
+// them), and under hubbard_set_timing, which times its pass kernels.
+bool sector_route(hubbard_model *h, int layers, bool grad, size_t ws_bytes, hipStream_t s)
 {
     if (h->m.ansatz != 0 || h->timing)
         return false;
     const std::string err = g_err;   // a refusal is no error of this call
-    const size_t need = sector_eval_bytes(h, layers, grad);
+    const size_t need = sector_eval_bytes(h, layers, grad, s);
     if (need == 0)
         g_err = err;
     return need != 0 && need <= ws_bytes;
@@ -1640,7 +1645,7 @@ hubbard_status hubbard_prepare_state(hubbard_t h, const double *theta_dev, int32
         return fail(HUBBARD_ERR_ARG, "bad arguments to hubbard_prepare_state");
     if (n_layers > 0 && h->m.ansatz == 0 && !h->timing) {
         const std::string err = g_err;   // a refusal is no error of this call
-        if (sector_state_ok(h, n_layers)) {
+        if (sector_state_ok(h, n_layers, (hipStream_t)stream)) {
             h->ev_used = 0;
             h->kmode.clear();
             return sector_state(h, n_layers, theta_dev, (double2 *)psi_dev, (hipStream_t)stream);
@@ -1687,7 +1692,7 @@ hubbard_status energy(hubbard_t h, const double *theta_dev, int32_t n_layers, do
     if (ws_bytes < vb + pr->partial_bytes)
         return fail(HUBBARD_ERR_SIZE, "workspace too small for energy");
     hipStream_t s = (hipStream_t)stream;
-    if (sector_route(h, n_layers, false, ws_bytes)) {
+    if (sector_route(h, n_layers, false, ws_bytes, s)) {
         h->ev_used = 0;
         h->kmode.clear();
         return sector_eval(h, n_layers, theta_dev, E_dev, nullptr, ws_dev, s);
@@ -1864,7 +1869,7 @@ hubbard_status energy_grad_on(hubbard_t h, const double *theta_dev, int32_t n_la
     if (ws_bytes < 2 * vb + pr->partial_bytes)
         return fail(HUBBARD_ERR_SIZE, "workspace too small for energy_grad");
     hipStream_t s = (hipStream_t)stream;
-    if (sector && sector_route(h, n_layers, true, ws_bytes)) {
+    if (sector && sector_route(h, n_layers, true, ws_bytes, s)) {
         h->ev_used = 0;
         h->kmode.clear();
         return sector_eval(h, n_layers, theta_dev, E_dev, grad_dev, ws_dev, s);

@@ -2866,56 +2866,84 @@ void sector_batch_reduction(const SectorBatch *b, const int32_t **seg_ptr,
 // The evaluations of the full-vector entry points (energy, energy_grad,
 // energy_grad_noalloc) in the sector form: their circuits start from |b0>, so
 // every amplitude outside its sector is zero throughout.
-// Workspace bytes, uploading the tables if they are not there; 0: not
-// available for this model (then the full vector is used).
-size_t sector_eval_bytes(hubbard_t h, int layers, bool grad)
+
+namespace sec {
+
+// Tables and program that are already there (allocates nothing).
+bool find(hubbard_t h, int layers, Tables **T, Program **P)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess)
+        return false;
+    std::shared_ptr<Entry> en;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        auto it = g_cache.find(std::make_pair(handle_uid(h), dev));
+        if (it == g_cache.end())
+            return false;
+        en = it->second;
+    }
+    std::lock_guard<std::mutex> lk(en->mu);
+    if (!en->tab)
+        return false;
+    auto p = en->progs.find(layers);
+    if (p == en->progs.end())
+        return false;
+    *T = en->tab.get();
+    *P = p->second.get();
+    return true;
+}
+
+// The same, uploaded if they are not there; not under capture, where nothing may
+// be allocated and the caller has launches that need none of it.
+bool find_or_upload(hubbard_t h, int layers, hipStream_t s, Tables **T, Program **P)
+{
+    if (find(h, layers, T, P))
+        return true;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
+        return false;
+    return get(h, layers, T, P) == HUBBARD_OK;
+}
+
+}  // namespace sec
+
+// Workspace bytes of an evaluation, uploading the tables if they are not there
+// and s is not being captured; 0: not available (then the full vector is used).
+size_t sector_eval_bytes(hubbard_t h, int layers, bool grad, hipStream_t s)
 {
     sec::Tables *T = nullptr;
     sec::Program *P = nullptr;
-    return sec::get(h, layers, &T, &P) == HUBBARD_OK ? sec::eval_bytes(*T, *P, grad) : 0;
+    return sec::find_or_upload(h, layers, s, &T, &P) ? sec::eval_bytes(*T, *P, grad) : 0;
 }
 
 // The same for tables already uploaded (allocates nothing; 0: not there).
 size_t sector_eval_ready(hubbard_t h, int layers)
 {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess)
-        return 0;
-    std::shared_ptr<sec::Entry> en;
-    {
-        std::lock_guard<std::mutex> lk(sec::g_mu);
-        auto it = sec::g_cache.find(std::make_pair(handle_uid(h), dev));
-        if (it == sec::g_cache.end())
-            return 0;
-        en = it->second;
-    }
-    std::lock_guard<std::mutex> lk(en->mu);
-    if (!en->tab)
-        return 0;
-    auto p = en->progs.find(layers);
-    return p == en->progs.end() ? 0 : sec::eval_bytes(*en->tab, *p->second);
+    sec::Tables *T = nullptr;
+    sec::Program *P = nullptr;
+    return sec::find(h, layers, &T, &P) ? sec::eval_bytes(*T, *P) : 0;
 }
 
-// grad NULL: the energy only.
+// After either of them.  grad NULL: the energy only.
 hubbard_status sector_eval(hubbard_t h, int layers, const double *theta, double *E, double *grad,
                            void *ws, hipStream_t s)
 {
     sec::Tables *T = nullptr;
     sec::Program *P = nullptr;
-    hubbard_status st = sec::get(h, layers, &T, &P);
-    if (st != HUBBARD_OK)
-        return st;
+    if (!sec::find(h, layers, &T, &P))
+        return set_error(HUBBARD_ERR_STATE, "no sector tables");
     sec::evaluate(*T, *P, theta, E, grad, (char *)ws, s);
     return sec::check("sector evaluation");
 }
 
 // Whether a start-state circuit's full vector can be made on its sector: a
 // plan of short rows and at least one pass.
-bool sector_state_ok(hubbard_t h, int layers)
+bool sector_state_ok(hubbard_t h, int layers, hipStream_t s)
 {
     sec::Tables *T = nullptr;
     sec::Program *P = nullptr;
-    return sec::get(h, layers, &T, &P) == HUBBARD_OK && !T->is_long && !P->fwd.empty();
+    return sec::find_or_upload(h, layers, s, &T, &P) && !T->is_long && !P->fwd.empty();
 }
 
 hubbard_status sector_state(hubbard_t h, int layers, const double *theta, double2 *psi,
@@ -2923,9 +2951,8 @@ hubbard_status sector_state(hubbard_t h, int layers, const double *theta, double
 {
     sec::Tables *T = nullptr;
     sec::Program *P = nullptr;
-    hubbard_status st = sec::get(h, layers, &T, &P);
-    if (st != HUBBARD_OK)
-        return st;
+    if (!sec::find(h, layers, &T, &P))
+        return set_error(HUBBARD_ERR_STATE, "no sector tables");
     sec::state(*T, *P, handle_model(h)->ns, theta, psi, s);
     return sec::check("state preparation");
 }

@@ -33,3 +33,51 @@ hh.hh_hold(0)
 t.join()
 assert st == [0]
 """)
+
+
+@pytest.mark.parametrize("call", ["energy_grad", "energy", "noalloc"])
+def test_evaluations_under_capture_before_the_sectors_tables(run, call):
+    # under hubbard_set_timing the full vector's plan is uploaded and no sector
+    # table; a capture after that launches what is there and allocates nothing,
+    # and the next eager call runs on the sector
+    run(f"""
+for kw in (dict(), dict(V_bond=[0.5] * 7)):
+    m = Model(1, 8, 2, U=4.0, **kw)
+    m.timing(True)
+    assert m.energy_grad()[0] == 0 and m.energy()[0] == 0
+    m.timing(False)
+    hh.hh_capture(1)
+    st, k = m.{call}()
+    assert st == 0 and has(k, "6k_pass") and not has(k, "k_sec"), (st, k)
+    assert hh.hh_refused_in_capture() == 0 and hh.hh_last_error() == 0
+    hh.hh_capture(0)
+    assert m.energy_grad()[0] == 0
+    st, k = m.{call}()
+    assert st == 0 and has(k, "k_sec") and not has(k, "6k_pass"), (st, k)
+    hh.hh_capture(1)            # the tables are there now
+    assert m.{call}() == (0, k) and hh.hh_refused_in_capture() == 0
+    hh.hh_capture(0)
+""")
+
+
+def test_h_and_states_under_capture_before_their_tables(run):
+    run("""
+m = Model(1, 8, 2, U=4.0, V_bond=[0.5] * 7)
+m.timing(True)
+assert m.apply_h()[0] == 0 and m.ansatz()[0] == 0
+m.timing(False)
+hh.hh_capture(1)
+st, k = m.apply_h()
+assert st == 0 and has(k, "6k_pass") and not has(k, "gather"), (st, k)
+st, k = m.prepare()             # by init and the pass kernels
+assert st == 0 and has(k, "6k_pass") and not has(k, "k_sec"), (st, k)
+assert hh.hh_refused_in_capture() == 0
+hh.hh_capture(0)
+st, k = m.apply_h()
+assert st == 0 and has(k, "gather") and not has(k, "6k_pass"), (st, k)
+st, k = m.prepare()
+assert st == 0 and has(k, "k_sec_expand"), (st, k)
+hh.hh_capture(1)
+assert has(m.apply_h()[1], "gather") and has(m.prepare()[1], "k_sec_expand")
+assert hh.hh_refused_in_capture() == 0
+""")
