@@ -1363,35 +1363,8 @@ hubbard_status build_batch(const hubbard_t *hs, int n, const double *theta, cons
     for (int i = 0; i < n; ++i)
         if (std::find(bp.uids.begin(), bp.uids.end(), hs[i]->uid) == bp.uids.end())
             bp.uids.push_back(hs[i]->uid);
-    // On the instances' sectors, by the rule of energy_grad: 256 uneven
-    // instances of 8 to 20 qubits take 12.9 ms on the full vectors (each
-    // launch listed below) and 1.48 ms on the sectors.  Only the workspace
-    // size comes from the full vectors' layout then.
-    bool timing = false;
-    for (int i = 0; i < n; ++i)
-        timing = timing || hs[i]->timing;
-    if (!timing) {
-        const std::string err = g_err;
-        hubbard_status st = HUBBARD_OK;
-        bp.sector = sector_batch_build(hs, n, theta, toff, layers, ws, cfg.lanes, &st);
-        if (st == HUBBARD_ERR_DEVICE || st == HUBBARD_ERR_NOMEM)
-            return st;
-        g_err = err;
-    }
-    if (bp.sector) {
-        std::vector<std::unique_ptr<Program>> own;
-        std::vector<const Program *> host;
-        hubbard_status st = batch_host_programs(hs, n, layers, own, host);
-        if (st == HUBBARD_OK)
-            st = batch_layout(hs, n, toff, host, cfg, bp.L);
-        if (st != HUBBARD_OK)
-            return st;
-        const size_t ws_bytes = bp.L.ws_bytes;
-        bp.L = BatchLayout();
-        bp.L.ws_bytes = ws_bytes;
-        return make_lanes(bp, [&bp](int l) { return sector_batch_uses(bp.sector, l); });
-    }
-    // the instances' device programs (cached per handle, device and layer count)
+    // the instances' device programs (cached per handle, device and layer
+    // count; energy_grad and energy_grad_noalloc of a member find them there)
     std::vector<const Program *> progs(n);
     std::vector<DevInstance> insts(n);
     for (int i = 0; i < n; ++i) {
@@ -1413,6 +1386,27 @@ hubbard_status build_batch(const hubbard_t *hs, int n, const double *theta, cons
     hubbard_status st = batch_layout(hs, n, toff, progs, cfg, bp.L);
     if (st != HUBBARD_OK)
         return st;
+    // On the instances' sectors, by the rule of energy_grad: 256 uneven
+    // instances of 8 to 20 qubits take 12.9 ms on the full vectors (each
+    // launch listed below) and 1.48 ms on the sectors.  Only the workspace
+    // size comes from the full vectors' layout then.
+    bool timing = false;
+    for (int i = 0; i < n; ++i)
+        timing = timing || hs[i]->timing;
+    if (!timing) {
+        const std::string err = g_err;
+        st = HUBBARD_OK;
+        bp.sector = sector_batch_build(hs, n, theta, toff, layers, ws, cfg.lanes, &st);
+        if (st == HUBBARD_ERR_DEVICE || st == HUBBARD_ERR_NOMEM)
+            return st;
+        g_err = err;
+    }
+    if (bp.sector) {
+        const size_t ws_bytes = bp.L.ws_bytes;
+        bp.L = BatchLayout();
+        bp.L.ws_bytes = ws_bytes;
+        return make_lanes(bp, [&bp](int l) { return sector_batch_uses(bp.sector, l); });
+    }
     st = make_lanes(bp, [&bp](int l) {
         return std::any_of(bp.L.launches.begin(), bp.L.launches.end(),
                            [l](const BatchLaunch &bl) { return bl.lane == l; });
@@ -1644,6 +1638,13 @@ hubbard_status hubbard_prepare_state(hubbard_t h, const double *theta_dev, int32
     if (!h || !psi_dev || n_layers < 0 || (n_layers > 0 && !theta_dev))
         return fail(HUBBARD_ERR_ARG, "bad arguments to hubbard_prepare_state");
     if (n_layers > 0 && h->m.ansatz == 0 && !h->timing) {
+        // the circuit's own plan, too: what it refuses is refused here, and an
+        // ansatz_apply that is captured next finds it
+        Program *pr;
+        DeviceState *ds;
+        const hubbard_status st = get_program(h, PROG_ANSATZ, n_layers, &pr, &ds);
+        if (st != HUBBARD_OK)
+            return st;
         const std::string err = g_err;   // a refusal is no error of this call
         if (sector_state_ok(h, n_layers, (hipStream_t)stream)) {
             h->ev_used = 0;

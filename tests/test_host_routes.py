@@ -81,3 +81,37 @@ hh.hh_capture(1)
 assert has(m.apply_h()[1], "gather") and has(m.prepare()[1], "k_sec_expand")
 assert hh.hh_refused_in_capture() == 0
 """)
+
+
+def test_calls_that_others_prepared_can_still_be_captured(run):
+    # a prepared state uploads ansatz_apply's plan, a batch its members'
+    # energy_grad plans: the calls that use them need no first call of their own
+    run("""
+m = Model(1, 8, 2, U=4.0)
+assert m.prepare()[0] == 0
+hh.hh_capture(1)
+st, k = m.ansatz()
+assert st == 0 and has(k, "6k_pass") and hh.hh_refused_in_capture() == 0, (st, k)
+hh.hh_capture(0)
+a, b = Model(1, 6, 2, U=4.0), Model(2, 2, 2, U=2.0, V_bond=[0.5] * 4)
+for m in (a, b):
+    m.work(abi.HUBBARD_OP_ENERGY_GRAD)
+st, k = Batch([a, b]).energy_grad()
+assert st == 0 and has(k, "k_sec_whole_batch"), (st, k)
+hh.hh_capture(1)
+for m in (a, b):
+    st, k = m.energy_grad()
+    assert st == 0 and has(k, "k_sec_whole"), (st, k)
+    assert m.noalloc() == (st, k)
+assert hh.hh_refused_in_capture() == 0
+""")
+
+
+def test_a_circuit_that_the_plan_refuses_is_refused(run):
+    # 400 layers of a 2x2 cluster in one tile need more LDS than there is
+    run("""
+m = Model(2, 2, 400, U=4.0)
+assert m.ansatz() == (abi.HUBBARD_ERR_ARG, [])
+assert m.prepare() == (abi.HUBBARD_ERR_ARG, [])
+assert b"more LDS" in L.hubbard_last_error()
+""")
