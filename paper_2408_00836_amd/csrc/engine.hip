@@ -67,8 +67,7 @@ hubbard_status sector_eval(hubbard_t h, int layers, const double *theta, double 
 struct SectorBatch;
 size_t sector_batch_bound(const hubbard_t *hs, int n, const int32_t *layers);
 SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
-                                const int64_t *toff, const int32_t *layers, char *ws, int lanes,
-                                hubbard_status *st);
+                                const int64_t *toff, const int32_t *layers, char *ws, int lanes);
 void sector_batch_free(SectorBatch *b);
 bool sector_batch_uses(const SectorBatch *b, int lane);
 void sector_batch_launch(const SectorBatch *b, const hipStream_t *lane);
@@ -89,6 +88,14 @@ hubbard_status fail(hubbard_status s, const std::string &msg)
     g_err = msg;
     return s;
 }
+
+// Keeps the thread's error message over an attempt whose failure is no error of
+// the call (another route serves it).
+struct QuietError {
+    std::string keep;
+    QuietError() { keep.swap(g_err); }
+    ~QuietError() { g_err.swap(keep); }
+};
 
 // Pass grids: one tile per workgroup while the workgroups fit the chip at
 // once (256 CUs x two tile-sized workgroups), else at least two tiles (or
@@ -975,17 +982,16 @@ VecLayout grad_layout(const hubbard_model *h)
 // form, one evaluation): 8 qubits 75 / 17 us, 16 qubits 486 / 148 us, 24
 // qubits with the general diagonal 16.2 / 0.98 ms, 28 qubits 92.9 / 3.2 ms.
 // The full vector remains for the NP ansatz, for models whose sector plan is
-// refused, for a workspace too small for the sector's vectors, for a capture
+// refused or not to be uploaded, for a workspace too small for the sector's
+// vectors, for a capture
 // before the sector's tables are there (the full vector's are: the caller has
 // them), and under hubbard_set_timing, which times its pass kernels.
 bool sector_route(hubbard_model *h, int layers, bool grad, size_t ws_bytes, hipStream_t s)
 {
     if (h->m.ansatz != 0 || h->timing)
         return false;
-    const std::string err = g_err;   // a refusal is no error of this call
+    QuietError quiet;
     const size_t need = sector_eval_bytes(h, layers, grad, s);
-    if (need == 0)
-        g_err = err;
     return need != 0 && need <= ws_bytes;
 }
 
@@ -1394,12 +1400,8 @@ hubbard_status build_batch(const hubbard_t *hs, int n, const double *theta, cons
     for (int i = 0; i < n; ++i)
         timing = timing || hs[i]->timing;
     if (!timing) {
-        const std::string err = g_err;
-        st = HUBBARD_OK;
-        bp.sector = sector_batch_build(hs, n, theta, toff, layers, ws, cfg.lanes, &st);
-        if (st == HUBBARD_ERR_DEVICE || st == HUBBARD_ERR_NOMEM)
-            return st;
-        g_err = err;
+        QuietError quiet;
+        bp.sector = sector_batch_build(hs, n, theta, toff, layers, ws, cfg.lanes);
     }
     if (bp.sector) {
         const size_t ws_bytes = bp.L.ws_bytes;
@@ -1645,13 +1647,16 @@ hubbard_status hubbard_prepare_state(hubbard_t h, const double *theta_dev, int32
         const hubbard_status st = get_program(h, PROG_ANSATZ, n_layers, &pr, &ds);
         if (st != HUBBARD_OK)
             return st;
-        const std::string err = g_err;   // a refusal is no error of this call
-        if (sector_state_ok(h, n_layers, (hipStream_t)stream)) {
+        bool ok;
+        {
+            QuietError quiet;
+            ok = sector_state_ok(h, n_layers, (hipStream_t)stream);
+        }
+        if (ok) {
             h->ev_used = 0;
             h->kmode.clear();
             return sector_state(h, n_layers, theta_dev, (double2 *)psi_dev, (hipStream_t)stream);
         }
-        g_err = err;
     }
     hubbard_status st = run_init(h, (double2 *)psi_dev, (hipStream_t)stream);
     return st == HUBBARD_OK ? ansatz_apply(h, theta_dev, n_layers, psi_dev, stream) : st;

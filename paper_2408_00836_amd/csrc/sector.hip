@@ -34,6 +34,7 @@
 #include <array>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <functional>
 #include <map>
 #include <memory>
@@ -1923,6 +1924,8 @@ struct Blob {
         if (e == hipSuccess)
             for (auto &p : at)
                 *p.first = *blob + p.second;
+        else
+            (void)hipGetLastError();   // reported by the caller, not by the next launch
         return e;
     }
 };
@@ -2165,7 +2168,7 @@ hubbard_status build_program(const Model &m, const Tables &T, int layers, Progra
 
 // Tables and (layers >= 0) the program of a handle on the current device.
 hubbard_status get(hubbard_t h, int layers, Tables **T, Program **P)
-{
+try {
     const Model *m = handle_model(h);
     if (!m)
         return fail(HUBBARD_ERR_ARG, "null handle");
@@ -2205,6 +2208,8 @@ hubbard_status get(hubbard_t h, int layers, Tables **T, Program **P)
         *P = it->second.get();
     }
     return HUBBARD_OK;
+} catch (const std::exception &) {
+    return fail(HUBBARD_ERR_NOMEM, "out of memory");
 }
 
 size_t vec_elems(const Tables &T) { return (size_t)T.n[0] * (size_t)T.n[1]; }
@@ -2606,13 +2611,11 @@ size_t sector_batch_bound(const hubbard_t *hs, int n, const int32_t *layers)
     return at;
 }
 
-// Plans and uploads a batch (NULL with *st HUBBARD_OK: not available).
+// Plans and uploads a batch; NULL: it has no such form, or no memory for it.
 SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
-                                const int64_t *toff, const int32_t *layers, char *ws, int lanes,
-                                hubbard_status *st)
-{
+                                const int64_t *toff, const int32_t *layers, char *ws, int lanes)
+try {
     using namespace sec;
-    *st = HUBBARD_OK;
     if (sector_batch_bound(hs, n, layers) == 0)
         return nullptr;
     std::unique_ptr<SectorBatch> B(new SectorBatch());
@@ -2621,7 +2624,7 @@ SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
     size_t at = 0;
     std::vector<size_t> voff(n);
     for (int i = 0; i < n; ++i) {
-        if ((*st = get(hs[i], layers[i], &T[i], &P[i])) != HUBBARD_OK)
+        if (get(hs[i], layers[i], &T[i], &P[i]) != HUBBARD_OK)
             return nullptr;
         voff[i] = at;
         at += 2 * align256(vec_elems(*T[i]) * 16);
@@ -2795,12 +2798,11 @@ SectorBatch *sector_batch_build(const hubbard_t *hs, int n, const double *theta,
     blob.add(&B->d_seg_off, seg_off);
     blob.add(&B->d_out_idx, out_idx);
     blob.add(&B->d_scale, scale);
-    const hipError_t e = blob.upload(&B->blob);
-    if (e != hipSuccess) {
-        *st = fail(HUBBARD_ERR_DEVICE, std::string("uploading batch: ") + hipGetErrorString(e));
+    if (blob.upload(&B->blob) != hipSuccess)
         return nullptr;
-    }
     return B.release();
+} catch (const std::exception &) {
+    return nullptr;
 }
 
 void sector_batch_free(SectorBatch *b) { delete b; }

@@ -115,3 +115,80 @@ assert m.ansatz() == (abi.HUBBARD_ERR_ARG, [])
 assert m.prepare() == (abi.HUBBARD_ERR_ARG, [])
 assert b"more LDS" in L.hubbard_last_error()
 """)
+
+
+# the ways in which the sector's tables cannot be had: no device memory for the
+# first allocation of them, and none on the host (any block of 1 KiB or more)
+NO_MEMORY = {"device": ("hh.hh_fail_next(1)", "hh.hh_fail_next(0)"),
+             "host": ("hh.hh_throw_above(1024)", "hh.hh_throw_above(0)")}
+
+
+@pytest.mark.parametrize("where", list(NO_MEMORY))
+@pytest.mark.parametrize("call", ["energy_grad", "energy"])
+def test_full_vector_where_the_sectors_tables_do_not_fit(run, call, where):
+    # with the full vector's plan there: the call runs it, reports nothing and
+    # leaves no error behind; once there is memory the sector is used
+    begin, end = NO_MEMORY[where]
+    run(f"""
+m = Model(2, 6, 2, U=4.0)
+m.timing(True)
+assert m.energy_grad()[0] == 0 and m.energy()[0] == 0
+m.timing(False)
+before = L.hubbard_last_error()
+{begin}
+st, k = m.{call}()
+{end}
+assert st == 0 and has(k, "6k_pass") and not has(k, "k_sec"), (st, k, L.hubbard_last_error())
+assert hh.hh_last_error() == 0 and L.hubbard_last_error() == before
+st, k = m.{call}()
+assert st == 0 and has(k, "k_sec"), (st, k)
+""")
+
+
+@pytest.mark.parametrize("where", list(NO_MEMORY))
+def test_state_and_batch_where_the_sectors_tables_do_not_fit(run, where):
+    begin, end = NO_MEMORY[where]
+    run(f"""
+m = Model(2, 6, 2, U=4.0)
+m.ansatz()
+{begin}
+st, k = m.prepare()
+{end}
+assert st == 0 and has(k, "6k_pass") and not has(k, "k_sec"), (st, k)
+assert hh.hh_last_error() == 0
+assert has(m.prepare()[1], "k_sec_expand")
+if {where!r} == "device":
+    # a batch whose members' plans are there: the sector's tables come first, then
+    # (the second time) the batch's own
+    for fail in (1, 2):
+        ms = [Model(1, 6, 2, U=4.0), Model(1, 8, 2, U=4.0)]
+        b = Batch(ms)
+        for x in ms:
+            x.timing(True)
+            assert x.energy_grad()[0] == 0
+            x.timing(False)
+        if fail == 2:
+            for x in ms:
+                assert x.energy_grad()[0] == 0
+        {begin}
+        st, k = b.energy_grad()
+        assert st == 0 and has(k, "k_batch_pass") and not has(k, "k_sec"), (st, k)
+        assert hh.hh_last_error() == 0
+""")
+
+
+def test_sector_calls_report_what_does_not_fit(run):
+    # the sector's own entry points have no other route: a status, no exception
+    run("""
+m = Model(2, 4, 2, U=4.0)
+n = ctypes.c_size_t()
+size = lambda: L.hubbard_sector_workspace_size(m.h, 2, abi.HUBBARD_SECTOR_ENERGY_GRAD,
+                                               ctypes.byref(n))
+hh.hh_fail_next(1)
+assert size() == abi.HUBBARD_ERR_DEVICE and hh.hh_last_error() == 0
+hh.hh_throw_above(1024)
+st = size()
+hh.hh_throw_above(0)
+assert st == abi.HUBBARD_ERR_NOMEM
+assert size() == 0 and m.sector_eg()[0] == 0
+""")
