@@ -1068,7 +1068,7 @@ struct BatchLayout {
     std::vector<size_t> voff;   // byte offset of instance i's psi (lambda follows)
     size_t partial_at = 0;      // byte offset of the partial sums
     size_t n_partial = 0;       // doubles
-    size_t ws_bytes = 0;
+    size_t ws_bytes = 0;        // on the full vectors
     bool general = false;       // any instance has eps or V terms: the general path for all
     bool np = false;            // any instance runs the NP circuit: gate kernels decode mask phases
 };
@@ -1239,10 +1239,6 @@ hubbard_status batch_layout(const hubbard_t *hs, int n, const int64_t *toff,
         L.seg_ptr.push_back((int32_t)L.seg_off.size());
     }
     L.ws_bytes = L.partial_at + align256(std::max<size_t>(L.n_partial, 1) * sizeof(double));
-    std::vector<int32_t> layers(n);
-    for (int i = 0; i < n; ++i)
-        layers[i] = progs[i]->layers;
-    L.ws_bytes = std::max(L.ws_bytes, sector_batch_bound(hs, n, layers.data()));
     return HUBBARD_OK;
 }
 
@@ -1305,8 +1301,8 @@ struct BatchProgram {
 };
 
 // Batch programs by their signature: the device, theta and workspace
-// pointers (the program's work items point into them) and each instance's
-// handle uid, tile generation, layer count and parameter offset.  A program
+// pointers (the program's work items point into them), whether it may run on
+// the instances' sectors, and each instance's handle uid, tile generation, layer count and parameter offset.  A program
 // points into its instances' device programs, so a change of any member's
 // tiles (hubbard_set_tiles, hubbard_tune) or its destruction evicts every
 // program that uses it; at most kMaxBatches programs are kept, the least
@@ -1358,9 +1354,22 @@ template <typename Pred> hubbard_status make_lanes(BatchProgram &bp, Pred used)
     return HUBBARD_OK;
 }
 
+// Whether a batch runs on its instances' sectors, by the rule of energy_grad:
+// all have that form, none is timed, and the workspace holds it (up to
+// hubbard_batch_workspace_size bytes, which for many instances of a few qubits
+// are more than the full vectors').
+bool batch_on_sectors(const hubbard_t *hs, int n, const int32_t *layers, size_t ws_bytes)
+{
+    for (int i = 0; i < n; ++i)
+        if (hs[i]->timing)
+            return false;
+    const size_t need = sector_batch_bound(hs, n, layers);
+    return need != 0 && need <= ws_bytes;
+}
+
 hubbard_status build_batch(const hubbard_t *hs, int n, const double *theta, const int64_t *toff,
-                           const int32_t *layers, char *ws, const BatchConfig &cfg,
-                           BatchProgram &bp)
+                           const int32_t *layers, char *ws, bool on_sectors,
+                           const BatchConfig &cfg, BatchProgram &bp)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess)
@@ -1392,14 +1401,10 @@ hubbard_status build_batch(const hubbard_t *hs, int n, const double *theta, cons
     hubbard_status st = batch_layout(hs, n, toff, progs, cfg, bp.L);
     if (st != HUBBARD_OK)
         return st;
-    // On the instances' sectors, by the rule of energy_grad: 256 uneven
-    // instances of 8 to 20 qubits take 12.9 ms on the full vectors (each
-    // launch listed below) and 1.48 ms on the sectors.  Only the workspace
+    // 256 uneven instances of 8 to 20 qubits take 12.9 ms on the full vectors
+    // (each launch listed below) and 1.48 ms on the sectors.  Only the workspace
     // size comes from the full vectors' layout then.
-    bool timing = false;
-    for (int i = 0; i < n; ++i)
-        timing = timing || hs[i]->timing;
-    if (!timing) {
+    if (on_sectors) {
         QuietError quiet;
         bp.sector = sector_batch_build(hs, n, theta, toff, layers, ws, cfg.lanes);
     }
@@ -1918,7 +1923,7 @@ hubbard_status hubbard_batch_workspace_size(const hubbard_t *hs, int32_t n,
     st = batch_layout(hs, n, toff.data(), progs, batch_config(), L);
     if (st != HUBBARD_OK)
         return st;
-    *bytes = L.ws_bytes;
+    *bytes = std::max(L.ws_bytes, sector_batch_bound(hs, n, n_layers));
     return HUBBARD_OK;
 }
 
@@ -1936,12 +1941,12 @@ hubbard_status energy_grad_batch(const hubbard_t *hs, int32_t n, const double *t
     int dev = 0;
     (void)hipGetDevice(&dev);
     const BatchConfig cfg = batch_config();
-    std::string key = std::to_string(dev) + ":" + std::to_string((uintptr_t)theta_dev) + ":" +
+    const bool on_sectors = batch_on_sectors(hs, n, n_layers, ws_bytes);
+    std::string key = (on_sectors ? "s" : "v") + std::to_string(dev) + ":" + std::to_string((uintptr_t)theta_dev) + ":" +
                       std::to_string((uintptr_t)ws_dev) + ":" + std::to_string(cfg.items) + "." +
                       std::to_string(cfg.lanes);
     for (int i = 0; i < n; ++i)
-        key += (hs[i]->timing ? ":t" : ":") + std::to_string(hs[i]->uid) + "." +
-               std::to_string(hs[i]->gen) + "/" +
+        key += ":" + std::to_string(hs[i]->uid) + "." + std::to_string(hs[i]->gen) + "/" +
                std::to_string(n_layers[i]) + "/" + std::to_string(theta_off[i]);
     hipStream_t s = (hipStream_t)stream;
     BatchProgram *bp = nullptr;
@@ -1962,7 +1967,7 @@ hubbard_status energy_grad_batch(const hubbard_t *hs, int32_t n, const double *t
             }
             std::unique_ptr<BatchProgram> nb(new BatchProgram());
             hubbard_status st = build_batch(hs, n, theta_dev, theta_off, n_layers,
-                                            (char *)ws_dev, cfg, *nb);
+                                            (char *)ws_dev, on_sectors, cfg, *nb);
             if (st != HUBBARD_OK)
                 return st;
             it = g_batches.emplace(key, std::move(nb)).first;

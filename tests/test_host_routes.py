@@ -192,3 +192,23 @@ hh.hh_throw_above(0)
 assert st == abi.HUBBARD_ERR_NOMEM
 assert size() == 0 and m.sector_eg()[0] == 0
 """)
+
+
+def test_batch_takes_the_workspace_that_the_full_vectors_need(run):
+    # many tiny instances need more bytes on their sectors than on the full
+    # vectors; a caller's buffer of the latter size is taken, and used so
+    run("""
+ms = [Model(1, 2, 3, U=4.0) for _ in range(64)]
+b = Batch(ms)
+# one more member without layers keeps the batch on the full vectors: 64 members'
+# need is less than that of 65, and the sectors' more
+full = Batch(ms + [Model(1, 2, 0, U=4.0)]).need
+assert full < b.need
+st, k = b.energy_grad(full)
+assert st == 0 and has(k, "k_batch_pass") and not has(k, "k_sec"), (st, k)
+st, k = b.energy_grad()
+assert st == 0 and has(k, "k_sec_whole_batch"), (st, k)
+st, k = b.energy_grad(full)        # the same buffers, the smaller size again
+assert st == 0 and has(k, "k_batch_pass"), (st, k)
+assert b.energy_grad(512 * 64 - 1)[0] == abi.HUBBARD_ERR_SIZE
+""")
