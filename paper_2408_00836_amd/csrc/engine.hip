@@ -1066,6 +1066,8 @@ struct BatchLayout {
     std::vector<double> scale;
     std::vector<int64_t> out_idx;
     std::vector<size_t> voff;   // byte offset of instance i's psi (lambda follows)
+    std::vector<int> init;      // instances without a forward pass (no layers), which would
+                                // have built their start state
     size_t partial_at = 0;      // byte offset of the partial sums
     size_t n_partial = 0;       // doubles
     size_t ws_bytes = 0;        // on the full vectors
@@ -1088,6 +1090,8 @@ hubbard_status batch_layout(const hubbard_t *hs, int n, const int64_t *toff,
     L.voff.resize(n);
     for (int i = 0; i < n; ++i) {
         L.voff[i] = at;
+        if (progs[i]->fwd.pass.empty())
+            L.init.push_back(i);
         at += 2 * align256(vec_bytes(hs[i]));
     }
     L.partial_at = at;
@@ -1979,6 +1983,11 @@ hubbard_status energy_grad_batch(const hubbard_t *hs, int32_t n, const double *t
     if (ws_bytes < L.ws_bytes)
         return fail(HUBBARD_ERR_SIZE, "workspace too small for energy_grad_batch");
     double *partial = (double *)((char *)ws_dev + L.partial_at);
+    for (int i : L.init) {
+        const hubbard_status st = run_init(hs[i], (double2 *)((char *)ws_dev + L.voff[i]), s);
+        if (st != HUBBARD_OK)
+            return st;
+    }
     if (bp->fork && hipEventRecord(bp->fork, s) != hipSuccess)
         return fail(HUBBARD_ERR_DEVICE, "forking the batch lane streams");
     for (int l = 1; l < kBatchLanes; ++l)

@@ -212,3 +212,17 @@ st, k = b.energy_grad(full)        # the same buffers, the smaller size again
 assert st == 0 and has(k, "k_batch_pass"), (st, k)
 assert b.energy_grad(512 * 64 - 1)[0] == abi.HUBBARD_ERR_SIZE
 """)
+
+
+def test_batch_builds_the_start_state_of_a_member_without_layers(run):
+    # it has no forward pass that would; H's pass reads the state
+    run("""
+ms = [Model(1, 4, 2, U=4.0), Model(1, 4, 0, U=4.0), Model(2, 2, 0, U=4.0)]
+for timed in (False, True):
+    ms[0].timing(timed)
+    b = Batch(ms)
+    for _ in range(2):
+        st, k = b.energy_grad()
+        assert st == 0 and sum("k_init_basis" in x for x in k) == 2, (st, k)
+        assert k.index([x for x in k if "k_batch_pass" in x][0]) == 2
+""")
