@@ -12,6 +12,12 @@ path:
     stream lanes: autotune_batch times one batched evaluation per
     candidate; `Batch` applies the cached winner before its first call.
 
+Tiles and work items shape the full vector's launches, which evaluations of the
+HVA circuit from the start state leave to the sector form where a model has one:
+they are timed on the full vector, and steer the calls that run there (the NP
+ansatz, ansatz_apply, H with energies, overlaps, models and batches without a
+sector form, hubbard_set_timing).
+
 Cache file: $HUBVQE_TUNE_CACHE, else tune_cache.json next to this module.
 Model key: lattice shape and boundaries, qubits, the diagonal's kind (U only,
 or with eps/V terms, derived from the model) and the GPU name.  The layer
@@ -134,32 +140,52 @@ def apply_member_tiles(models, policy: str, path: str | None = None) -> None:
             m.tiles_source = "library default"
 
 
+def _timed(batch, theta, reps):
+    """Best of `reps` seconds of one batched evaluation, planned before."""
+    batch.energy_grad(theta)
+    torch.cuda.synchronize()
+    best = None
+    for _ in range(reps):
+        t0 = time.perf_counter()
+        batch.energy_grad(theta)
+        torch.cuda.synchronize()
+        dt = time.perf_counter() - t0
+        best = dt if best is None else min(best, dt)
+    return best
+
+
 def autotune_batch(batch, theta: torch.Tensor, *, reps: int = 3, path: str | None = None,
                    save: bool = True) -> dict:
-    """Time one batched evaluation per (work items, lanes) candidate (each a
-    plan of its own) and store the fastest for this batch composition; the
-    batch is left on it."""
+    """Time one batched evaluation per (tiles, work items, lanes) candidate (each
+    a plan of its own) and store the fastest for this batch composition; the
+    batch is left on it.  Tiles and work items shape the full vectors' launches
+    alone, so the candidates run there (hubbard_set_timing); the lanes, which
+    every batch has, are then chosen by ordinary calls."""
     table = []
-    for tiles in BATCH_TILES:
-        apply_member_tiles(batch.models, tiles, path)
-        for items in BATCH_ITEMS:
-            for lanes in BATCH_LANES:
-                batch.set_config(items, lanes, tiles)
-                batch.energy_grad(theta)          # plans this configuration
-                torch.cuda.synchronize()
-                best = None
-                for _ in range(reps):
-                    t0 = time.perf_counter()
-                    batch.energy_grad(theta)
-                    torch.cuda.synchronize()
-                    dt = time.perf_counter() - t0
-                    best = dt if best is None else min(best, dt)
-                table.append(dict(tiles=tiles, items=items, lanes=lanes, ms=best * 1e3))
+    for m in batch.models:
+        abi.hubbard_set_timing(m.handle, True)
+    try:
+        for tiles in BATCH_TILES:
+            apply_member_tiles(batch.models, tiles, path)
+            for items in BATCH_ITEMS:
+                for lanes in BATCH_LANES:
+                    batch.set_config(items, lanes, tiles)
+                    t = _timed(batch, theta, reps)
+                    table.append(dict(tiles=tiles, items=items, lanes=lanes, ms=t * 1e3))
+    finally:
+        for m in batch.models:
+            abi.hubbard_set_timing(m.handle, False)
     win = min(table, key=lambda r: r["ms"])
     apply_member_tiles(batch.models, win["tiles"], path)
-    batch.set_config(win["items"], win["lanes"], win["tiles"])
+    lane_table = []
+    for lanes in BATCH_LANES:
+        batch.set_config(win["items"], lanes, win["tiles"])
+        lane_table.append(dict(lanes=lanes, ms=_timed(batch, theta, reps) * 1e3))
+    lanes = min(lane_table, key=lambda r: r["ms"])["lanes"]
+    batch.set_config(win["items"], lanes, win["tiles"])
     batch.config_source = "autotuned"
-    ent = {"best": [win["items"], win["lanes"], win["tiles"]], "table": table}
+    ent = {"best": [win["items"], lanes, win["tiles"]], "table": table,
+           "lane_table": lane_table}
     if save:
         _store(path or cache_path(), batch_key(batch.models, batch.layers), ent)
     return ent
