@@ -221,7 +221,8 @@ hubbard_status hamiltonian_apply(hubbard_t h, const void *psi_dev, void *out_dev
  * The HVA circuit is evaluated on the particle-number sector of |b0> (below:
  * every other amplitude is zero throughout), as energy_grad and
  * energy_grad_batch do; the NP circuit, a model the sector form refuses, and
- * any handle under hubbard_set_timing on the full vector. */
+ * any handle under hubbard_set_timing on the full vector.  The two round
+ * differently: they agree to about 1e-12 of |E|. */
 hubbard_status energy(hubbard_t h, const double *theta_dev, int32_t n_layers,
                       double *E_dev, void *ws_dev, size_t ws_bytes, void *stream);
 
@@ -233,7 +234,10 @@ hubbard_status energy(hubbard_t h, const double *theta_dev, int32_t n_layers,
  * contents on entry are not read, and on return they are scratch (psi and
  * lambda are kept there in a layout of the library's own).  The first call
  * per handle, device and layer count uploads the full vector's plan and the
- * sector's tables. */
+ * sector's tables.  A call under graph capture uploads nothing: it runs on
+ * the full vector if only that plan is there.  Where the sector's tables
+ * cannot be uploaded, it runs on the full vector, too.  (The same holds for
+ * energy, hubbard_prepare_state and hamiltonian_apply with their tables.) */
 hubbard_status energy_grad(hubbard_t h, const double *theta_dev, int32_t n_layers,
                            double *E_dev, double *grad_dev, void *ws_dev,
                            size_t ws_bytes, void *stream);
@@ -355,7 +359,10 @@ hubbard_status hubbard_vqe(hubbard_t h, int32_t n_layers, int32_t n_starts, doub
  *     qubits used here have fewer than 70); larger: HUBBARD_ERR_SIZE.
  *   - The handle's plan for this device and layer count must already be
  *     uploaded by one earlier energy_grad call (HUBBARD_ERR_STATE
- *     otherwise).
+ *     otherwise).  If that call ran on the full vector (under
+ *     hubbard_set_timing, or while the sector's tables could not be
+ *     uploaded), this one does, too, until a later energy_grad has uploaded
+ *     the tables: the results of the two agree to rounding.
  *   - Every call on a device shares that device's array and keeps the last
  *     call's contents; each call writes the parts it reads before reading
  *     them.  Calls that overlap on one device (other streams, other host
@@ -366,10 +373,12 @@ hubbard_status energy_grad_noalloc(hubbard_t h, const double *theta_dev, int32_t
 /* Batched energy and gradient of many independent instances (different
  * lattices, sizes, U, disorder, V and layer counts; each its own parameters)
  * with no host work per call: a fixed sequence of launches on `stream`.
- * Instances that all run the HVA circuit in rows of at most 6500 sector
- * amplitudes (up to 15 sites) are evaluated on their sectors, pass by pass,
- * each with energy_grad's results bit for bit.  Any other batch runs on the
- * full vectors:
+ * A batch is evaluated on its instances' sectors, pass by pass, each with
+ * energy_grad's results bit for bit, if every instance runs the HVA circuit
+ * with at least one layer and at most seven hopping groups, in rows of at
+ * most 6500 sector amplitudes (always up to 15 sites), none is under
+ * hubbard_set_timing, and ws_bytes holds it.  Any other batch runs on the
+ * full vectors, all its instances with it:
  * for each position j of the forward, H and reverse schedules, launches that
  * run pass j of every instance that has one (two: passes whose tiles fill the
  * workgroup's registers exactly, and the others; a large instance's tiles
@@ -391,7 +400,10 @@ hubbard_status energy_grad_noalloc(hubbard_t h, const double *theta_dev, int32_t
  *   E_dev[i]        energy of instance i (device, n doubles)
  *   grad_dev        gradient of instance i at grad_dev + theta_off[i] (device)
  *   ws_dev          hubbard_batch_workspace_size bytes (device): each
- *                   instance's psi and lambda, then the partial sums
+ *                   instance's psi and lambda, then the partial sums (at
+ *                   least what the full vectors need, HUBBARD_ERR_SIZE;
+ *                   for many instances of a few qubits the sectors need
+ *                   more, and a buffer in between keeps the full vectors)
  * The first call with a given set of handles, layer counts, offsets, theta
  * and workspace pointers plans the batch and uploads its tables (it must not
  * be under graph capture); later calls only launch kernels, allocate
@@ -440,8 +452,9 @@ hubbard_status energy_grad_batch(const hubbard_t *hs, int32_t n, const double *t
 enum {
     HUBBARD_SECTOR_ANSATZ = 0,        /* sector_ansatz_apply: one sector vector */
     HUBBARD_SECTOR_ENERGY_GRAD = 1,   /* sector_energy_grad: four vectors + partial sums */
-    HUBBARD_SECTOR_HAMILTONIAN = 2,   /* sector_hamiltonian_apply: two vectors */
-    HUBBARD_SECTOR_LANCZOS = 3        /* hubbard_sector_lanczos: five vectors + partial sums */
+    HUBBARD_SECTOR_HAMILTONIAN = 2,   /* sector_hamiltonian_apply: two vectors (uses one) */
+    HUBBARD_SECTOR_LANCZOS = 3        /* hubbard_sector_lanczos: five vectors (uses four) +
+                                         partial sums */
 };
 
 /* C(Ns, N_up) and C(Ns, N_dn) of the handle's start state (host outputs). */
@@ -482,7 +495,7 @@ hubbard_status sector_energy_grad(hubbard_t h, const double *theta_dev, int32_t 
  * (same stopping rule, same arithmetic order) with sector_hamiltonian_apply
  * as H.  start_dev and gs_dev (NULL or the unit Ritz vector) are sector
  * vectors; ws_dev: HUBBARD_SECTOR_LANCZOS bytes (three Krylov vectors, H's
- * two layout-B vectors, partial sums), overlapping neither.  Synchronises
+ * transposed input, one vector unused, partial sums), overlapping neither.  Synchronises
  * `stream` at every step. */
 hubbard_status hubbard_sector_lanczos(hubbard_t h, const void *start_dev, int32_t max_iter,
                                       double tol, double *E0, int32_t *iters, double *residual,

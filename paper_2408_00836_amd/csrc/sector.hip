@@ -166,8 +166,8 @@ __device__ __forceinline__ double xor_sign(double x, uint32_t mask)
 
 // x <- x m + q computed in the registers of x: the orbit is updated in place.
 // (Left to itself the allocator writes a hop's results to fresh registers and
-// copies the orbits back where the six cases of a hop meet: twice the
-// registers, and hundreds of bytes per lane in scratch memory.)
+// copies the orbits back where branches meet: twice the registers, and hundreds
+// of bytes per lane in scratch memory.)
 __device__ __forceinline__ void fma_ip(double &x, double m, double q)
 {
     asm("v_fma_f64 %0, %0, %1, %2" : "+v"(x) : "v"(m), "v"(q));
@@ -776,9 +776,6 @@ __device__ __forceinline__ void rows_short(const AT &A, int bid, int vsel, char 
             if (REV && st == n_pre && A.l_diag >= 0)
                 diag();
         }
-        // no step after the diagonal (a model without bonds)
-        if (n_pre == n_steps && A.l_diag >= 0)
-            diag();
         if (!(A.flags & SF_NO_STORE) && live) {
             each([&](int, int col) __attribute__((always_inline)) {
                 const double2 x = vec[(colslot[col] << lr) + row];
@@ -2431,8 +2428,9 @@ hubbard_status check(const char *what)
     return HUBBARD_OK;
 }
 
-// Workspace of an evaluation: psi and lambda in both layouts, the partial rows
-// (of the energy alone: two).
+// Workspace of an evaluation: psi and lambda, each in both layouts (short rows
+// have one layout and use the first buffer of each), and the partial rows (of the
+// energy alone: two).
 size_t eval_bytes(const Tables &T, const Program &P, bool grad = true)
 {
     return 4 * align256(vec_elems(T) * 16) + align256((size_t)(grad ? P.n_rows : 2) * kGrid * 8);
