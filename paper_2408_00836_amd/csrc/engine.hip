@@ -51,6 +51,16 @@ hubbard_status lanczos_run(const ApplyH &apply, uint64_t n, const double2 *start
                            double *residual, double2 *gs_dev, double2 *const buf[3],
                            double2 *partial, hipStream_t s);
 size_t lanczos_partial_bytes();
+// Whether nothing may be allocated for a call on s: it is being captured, or
+// cannot be asked because another stream's capture forbids it.
+bool under_capture(hipStream_t s)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess)
+        return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
 // ham.hip: H on full vectors by gathering
 bool ham_gather_ok(const Model &m);
 std::vector<double> ham_site_table(const Model &m);
@@ -907,8 +917,7 @@ bool gather_route(hubbard_model *h, DeviceState &ds, hipStream_t s)
     std::lock_guard<std::mutex> lk(h->mu);
     if (ds.d_site)
         return true;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
+    if (under_capture(s))
         return false;
     try {
         const std::vector<double> e = ham_site_table(h->m);
@@ -983,9 +992,9 @@ VecLayout grad_layout(const hubbard_model *h)
 // qubits with the general diagonal 16.2 / 0.98 ms, 28 qubits 92.9 / 3.2 ms.
 // The full vector remains for the NP ansatz, for models whose sector plan is
 // refused or not to be uploaded, for a workspace too small for the sector's
-// vectors, for a capture
-// before the sector's tables are there (the full vector's are: the caller has
-// them), and under hubbard_set_timing, which times its pass kernels.
+// vectors, for a capture before the sector's tables are there (the full vector's
+// are: the caller has them), and under hubbard_set_timing, which times its pass
+// kernels.
 bool sector_route(hubbard_model *h, int layers, bool grad, size_t ws_bytes, hipStream_t s)
 {
     if (h->m.ansatz != 0 || h->timing)
@@ -1306,10 +1315,10 @@ struct BatchProgram {
 
 // Batch programs by their signature: the device, theta and workspace
 // pointers (the program's work items point into them), whether it may run on
-// the instances' sectors, and each instance's handle uid, tile generation, layer count and parameter offset.  A program
-// points into its instances' device programs, so a change of any member's
-// tiles (hubbard_set_tiles, hubbard_tune) or its destruction evicts every
-// program that uses it; at most kMaxBatches programs are kept, the least
+// the instances' sectors, and each instance's handle uid, tile generation,
+// layer count and parameter offset.  A program points into its instances'
+// device programs, so a change of any member's tiles (hubbard_set_tiles,
+// hubbard_tune) or its destruction evicts every program that uses it; at most kMaxBatches programs are kept, the least
 // recently called one is evicted first.  Eviction waits for the device to go
 // idle before freeing (work queued with those tables may still run).
 constexpr size_t kMaxBatches = 16;
@@ -1946,7 +1955,8 @@ hubbard_status energy_grad_batch(const hubbard_t *hs, int32_t n, const double *t
     (void)hipGetDevice(&dev);
     const BatchConfig cfg = batch_config();
     const bool on_sectors = batch_on_sectors(hs, n, n_layers, ws_bytes);
-    std::string key = (on_sectors ? "s" : "v") + std::to_string(dev) + ":" + std::to_string((uintptr_t)theta_dev) + ":" +
+    std::string key = (on_sectors ? "s" : "v") + std::to_string(dev) + ":" +
+                      std::to_string((uintptr_t)theta_dev) + ":" +
                       std::to_string((uintptr_t)ws_dev) + ":" + std::to_string(cfg.items) + "." +
                       std::to_string(cfg.lanes);
     for (int i = 0; i < n; ++i)

@@ -6,8 +6,8 @@
 // the result gathers its neighbours psi[i ^ m_b], all bonds of one spin in one
 // sweep: a workgroup holds a piece of a spin-up row (or of eight neighbouring
 // spin-down columns, 128 bytes wide) in LDS and reads the neighbours inside it
-// there.  The others lie in the same row, or columns, which stays in the L2 of
-// the XCD that works on it, so psi is read from HBM about once per sweep:
+// there.  The others lie in the same row, or columns, which the same XCD works on:
+// a row stays in its L2, the columns do not.
 //   down: out <- H_dn psi                  (read psi, write out)
 //   up:   out <- out + (D + H_up) psi      (read psi and out, write out)
 #include <hip/hip_runtime.h>
@@ -104,11 +104,11 @@ __device__ __forceinline__ void bond_term(const GatherBond &B, uint32_t first, u
 
 }  // namespace
 
-// Bound by HBM and the fabric: at 28 qubits and 19 bonds 4.8 ms down and 3.3 up
-// (the five passes 13.7), with 18.7 and 14.3 GB through the L2s.  A slab of
-// columns at a power-of-two stride meets few of an L2's sets, so two fifths of
-// the neighbours outside the tile are read again, whichever the order of the
-// slabs (4.7 to 6 ms).  With all neighbours gathered from L2 the texture path
+// Bound by what lies behind the L2s: at 28 qubits and 19 bonds 4.8 ms down and 3.1
+// up (the five passes 13.7), with 33.8 and 15.0 GB moved there (least: 8.6 and
+// 12.9), 7.0 and 4.8 TB/s.  A slab of columns at a power-of-two stride meets few of
+// an L2's sets, so the neighbours outside the tile (12 bonds, half of the elements
+// each) are all read again, whichever the order of the slabs (4.7 to 6 ms).  With all neighbours gathered from L2 the texture path
 // bound it, 30 cycles per load of 64 amplitudes: 10.5 ms.  512 threads of four
 // amplitudes: 256 x 4, 512 x 2, 1024 x 4 and 256 x 8 took 3 to 12 % longer.
 template <bool UP, bool GEN, int T, int R>

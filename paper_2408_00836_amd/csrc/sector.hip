@@ -52,10 +52,11 @@
 namespace hv {
 
 // engine.hip: the handle's model, its unique id, the thread's last error,
-// the Lanczos recurrence on a Hamiltonian given as a callback
+// whether a stream is being captured, the Lanczos recurrence on a Hamiltonian given as a callback
 const Model *handle_model(hubbard_t h);
 uint64_t handle_uid(hubbard_t h);
 hubbard_status set_error(hubbard_status s, const std::string &msg);
+bool under_capture(hipStream_t s);
 using ApplyH = std::function<hubbard_status(const double2 *, double2 *)>;
 hubbard_status lanczos_run(const ApplyH &apply, uint64_t n, const double2 *start_dev,
                            int32_t max_iter, double tol, double *E0, int32_t *iters,
@@ -2900,10 +2901,7 @@ bool find_or_upload(hubbard_t h, int layers, hipStream_t s, Tables **T, Program 
 {
     if (find(h, layers, T, P))
         return true;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
-        return false;
-    return get(h, layers, T, P) == HUBBARD_OK;
+    return !under_capture(s) && get(h, layers, T, P) == HUBBARD_OK;
 }
 
 }  // namespace sec
