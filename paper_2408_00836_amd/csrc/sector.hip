@@ -893,7 +893,7 @@ k_sec_rows_batch(const RowsArgs *__restrict__ args, const SecWork *__restrict__ 
 // Modes, vectors and reductions as in k_sec_rows_short.
 // Bound by LDS traffic and VALU: 206 KB go through LDS in each direction per
 // phase, eight phases per layer and spin at 4x4 periodic where an exchange per
-// hop needed 32.  At 12870 x 12870 (5.3 GB moved) a forward pass of 64 hops
+// hop needed 32.  At 12870 x 12870 (5.3 GB, 9.2 by the counters) a forward pass of 64 hops
 // with its transposed store takes 3.9 ms (an exchange per hop and a transpose:
 // 9.1 ms), the reverse pass of both vectors 8.6 (20.9).  The diagonal's
 // products must not be put off past flush: kept waiting there they spilled 750
